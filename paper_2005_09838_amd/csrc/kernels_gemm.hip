@@ -1,14 +1,14 @@
 // The three batched complex slice products of one iteration (per stored frequency b):
 //   Z~_b = X~_b Y~_b                       (step 3)                   k_zgemm
-//   A_b  = W~_b Y~_b^*  and the X right-hand side                      k_agemm
+//   A_b  = W~_b Y~_b^*  and the X-update, or its right-hand side       k_agemm
 //          R_b = eta A_b G_Y^+ + H_rho1 X~_b (I - eta P_Y)   (step 1, eq. (updataXYW1))
 //   X~_b^* W~_b partial sums over row chunks (step 2), and in extra blocks of the same
 //   launch G_X = X~_b^* X~_b + rho1 (H X~_b)^*(H X~_b), G_X^+ and I - eta P_X  k_bgemm
 // The complex products run on the matrix cores as real FP32 products (16 x 16 x 4 tiles):
 // a complex m x k by k x n product is an m x 2k by 2k x n' real one whose operands are the
 // interleaved (re, im) storage itself, with the signs of the complex product placed in the
-// operand that is built on the fly.  X~^* W~ runs on the FP64 matrix cores (FP64 partial
-// sums over row chunks); r x r Grams and the X right-hand side epilogue are FP64.  Mixed mode reads W~ from its
+// operand that is built on the fly.  X~^* W~ and the X-update's r x r products run on the FP64
+// matrix cores; r x r Grams are FP64.  Mixed mode reads W~ from its
 // BF16 storage (stochastically rounded by the slice kernel) and converts to FP32 before
 // the product.
 #include <type_traits>
@@ -285,283 +285,298 @@ void launch_zgemm(const Plan& p, int with_pinv) {
 #undef TCTF_ZGEMM
 }
 
-// ---------------------------------------------------------------- A = W~ Y~^*, X right-hand side
+// ---------------------------------------------------------------- A = W~ Y~^* and the X-update
 // Real form: A'[i][2s + e] = sum_kk W'[i][kk] Y'[kk][2s + e], kk = 2j + c, W' the
 // interleaved W~ row and Y'[2j][2s] = Yr, Y'[2j+1][2s] = Yi, Y'[2j][2s+1] = -Yi,
 // Y'[2j+1][2s+1] = Yr (Y = Y~(s, j)).  Within a group of 16 K values the K order is
 // permuted so that lane (m, q) feeds the four products of the group from the four
 // consecutive floats W'[m][16 g + 4 q ..] (two complex entries of W~), and the matching
 // Y' values are the same two complex entries of Y~ row s (with the sign pattern).
-// Block: 64 rows x one frequency, 4 wavefronts of 16 rows, up to AG_COLS columns of W~ per
-// pass with every W~ load of the pass issued before the products.
-// Epilogue, in FP64, with U = X~ (I - eta P_Y) (U = 0 when I - eta P_Y is exactly 0):
+// Block: 16 RT rows x one frequency, RT x WC wavefronts; wavefront (rt, c) takes 16 rows and
+// every WC-th run of up to AG_GROUPS groups of 8 columns, all its W~ loads of a pass issued
+// before the products.  FP32 sums run over one pass (at most 48 columns) and are added in
+// FP64 across passes and wavefronts: FP32 sums over all 288 columns of 144 x 288 x 28 were the
+// largest error of the iteration (W after six iterations 5e-7 from the FP64 result, 1.8e-7 so).
+// Epilogue on the FP64 matrix cores, with U = X~ (I - eta P_Y) (absent when I - eta P_Y is
+// exactly 0):
 // * hk >= 0: the whole X-update.  Since X~_new = H_rho1^{-1} (eta A G_Y^+ + H_rho1 U) =
 //   U + eta H_rho1^{-1} V with V = A G_Y^+, and H_rho1^{-1} is the stencil of hinv_stencil,
-//   the block forms V on its 64 rows (zero outside the matrix) and writes X~_new on the
-//   64 - 2 hk rows whose stencil lies inside them; consecutive blocks overlap by 2 hk rows.
-//   U needs X~ on the output rows only, which no other block writes, so X~ is updated in
-//   place.  Real bins (b = 0, n3 / 2) keep a zero imaginary part.
+//   the block forms V on its rows (zero outside the matrix), multiplies it by the banded
+//   matrix of the stencil's taps and writes X~_new on the 16 RT - 2 hk rows whose stencil lies
+//   inside the block; consecutive blocks overlap by 2 hk rows.  U needs X~ on the output rows
+//   only, which no other block writes, so X~ is updated in place.  Real bins (b = 0, n3 / 2)
+//   keep a zero imaginary part.
 // * hk = -1: the right-hand side R = eta A G_Y^+ + H_rho1 U for k_hsolve.
-#define AG_ROWS 64
-#define AG_COLS 128
+// What bounds it: at 529 x 96 x 112, r = 16 no single unit (21.2 us; 19 without any product, 10
+// without loads and stores of the epilogue either): the chain of loads, products and two LDS
+// hand-overs of blocks that all start together.  Before (one wavefront column, the epilogue on
+// the VALU) 20.5 us with FP32 sums over all columns; 144 x 288 x 28, r = 8 16.2 before, 10.1 now;
+// 300 x 120 x 24, r = 24 16.2 before, 13.3 now.
+#define AG_GROUPS 6   // groups of 8 columns per wavefront and pass
 struct HStencil {
   int k;                            // half-width, -1: right-hand side only
   double tap[2 * HINV_KMAX + 2];    // c lambda^d
 };
-template <int RM, bool MIXED>   // r <= RM; MIXED: W~ stored as packed bf16 pairs
-__global__ void __launch_bounds__(256) k_agemm(const void* wt, const float2* __restrict__ yt,
-                                               const float2* xt, const cd* __restrict__ gyp,   // xt may be xout
-                                               const cd* __restrict__ qy, const int* __restrict__ qy_zero,
-                                               float2* __restrict__ rhs, int n1, int n2, int r, int nb,
-                                               double eta, double rho1, int raw_a, uint32_t* ctr,
-                                               float2* xout, int n3, HStencil hs) {
-  __shared__ __align__(16) float2 ysh[RM * AG_COLS];   // [s][j] of the column chunk (MIXED: split words)
-  __shared__ __align__(16) float2 ash[AG_ROWS * RM];   // A rows, then the results
-  __shared__ __align__(16) cd gs[RM * RM];             // G_Y^+
-  __shared__ __align__(16) cd vsh[RM <= 16 ? AG_ROWS * RM : 1];   // V = A G_Y^+ [s][row] (stencil only)
-  __shared__ double tsh[2 * HINV_KMAX + 2];                        // the stencil's taps
-  const int hk = (RM <= 16 && !raw_a) ? hs.k : -1;
+// LDS of a block: the Y~ chunk as the products' B operands (a column pair of row s with the
+// signs of e = 0 and of e = 1, 16 bytes each; mixed: hi and lo BF16 parts), then in its place
+// the FP64 partial A' of each wavefront column (the sums in the first, V in the second); rows of
+// both padded against bank conflicts.
+__host__ __device__ constexpr int ag_ystride(int wc) { return wc * AG_GROUPS * 4 + 1; }   // column pairs
+__host__ __device__ constexpr int ag_astride(int rm) { return 2 * rm + 1; }
+static size_t agemm_lds_bytes(int rm, int rt, int wc) {
+  const size_t y = (size_t)2 * rm * ag_ystride(wc) * sizeof(float4);
+  const size_t a = (size_t)(wc > 2 ? wc : 2) * 16 * rt * ag_astride(rm) * sizeof(double);
+  return y > a ? y : a;
+}
+template <int RM, bool MIXED, int RT>   // r <= RM; MIXED: W~ stored as packed bf16 pairs
+__global__ void __launch_bounds__(RM == 32 ? 512 : 1024) k_agemm(const void* wt, const float2* __restrict__ yt,
+                                                const float2* xt, const cd* __restrict__ gyp,   // xt may be xout
+                                                const cd* __restrict__ qy, const int* __restrict__ qy_zero,
+                                                float2* __restrict__ rhs, int n1, int n2, int r, int nb,
+                                                double eta, double rho1, int raw_a, uint32_t* ctr,
+                                                float2* xout, int n3, HStencil hs) {
+  constexpr int ROWS = 16 * RT, NNT = RM / 8, CT = RM / 8, LDA = ag_astride(RM), KV = RM / 2;
+  constexpr int YPER = (RM * AG_GROUPS * 4 + 64 * RT - 1) / (64 * RT);
+  extern __shared__ __align__(16) unsigned char asm_[];
+  __shared__ double tsh[2 * HINV_KMAX + 2];   // the stencil's taps
+  float4* ysh = (float4*)asm_;                // [2 s + e][column pair]
+  double* ash = (double*)asm_;                // [c][row][2s + e]
+  const int tid = threadIdx.x, nt = blockDim.x, wc = nt / (64 * RT);
+  const int lane = tid & 63, w = tid >> 6, m = lane & 15, q = lane >> 4, rt = w % RT, cg = w / RT;
+  const int ystride = ag_ystride(wc);
+  const int hk = raw_a ? -1 : hs.k;
 #pragma unroll
   for (int d = 0; d < 2 * HINV_KMAX + 2; ++d)   // constant indices: the taps stay in the argument segment
-    if ((int)threadIdx.x == d && d <= 2 * hk + 1) tsh[d] = hs.tap[d];   // read after the first barrier
-  // with the stencil, block x covers rows x (64 - 2 hk) - hk .. + 63 (some outside the matrix)
-  const int i0 = hk >= 0 ? (int)blockIdx.x * (AG_ROWS - 2 * hk) - hk : (int)blockIdx.x * AG_ROWS;
-  const int b = blockIdx.y, tid = threadIdx.x;
-  const int lane = tid & 63, w = tid >> 6, m = lane & 15, q = lane >> 4;
-  const int row = i0 + 16 * w + m;
+    if (tid == d && d <= 2 * hk + 1) tsh[d] = hs.tap[d];   // read after the first barrier
+  // with the stencil, block x covers rows x (ROWS - 2 hk) - hk .. (some outside the matrix)
+  const int i0 = hk >= 0 ? (int)blockIdx.x * (ROWS - 2 * hk) - hk : (int)blockIdx.x * ROWS;
+  const int b = blockIdx.y;
+  const int row = i0 + 16 * rt + m;
   const bool row_in = row >= 0 && row < n1;
   // one thread of the launch advances the counter of the rounding bits that this
   // iteration's slice kernel (a later launch) uses for the BF16 W~
   if (ctr && blockIdx.x == 0 && blockIdx.y == 0 && tid == 0) ctr[0] += 1u;
-  constexpr int NNT = RM / 8;          // 16-column tiles of A' (2 RM columns)
-  constexpr int YPER = RM * AG_COLS / 256;
-  const bool eodd = m & 1;             // this lane's output column 2s + e has e = 1
-  v4f acc[NNT];
+  // G_Y^+ as the B operand of V = A G_Y^+ for this wavefront's column tile, in real form
+  // G'[2s][2t] = Gr, G'[2s+1][2t] = -Gi, G'[2s][2t+1] = Gi, G'[2s+1][2t+1] = Gr; likewise Q
+  auto load_g = [&](const cd* mat, int ct, double (&bg)[KV]) {
+    const double* base = (const double*)(mat + (size_t)b * r * r);
+    const int sc = (16 * ct + m) >> 1, dd = q & 1, ee = m & 1;
 #pragma unroll
-  for (int u = 0; u < NNT; ++u) acc[u] = v4f{0.f, 0.f, 0.f, 0.f};
-  // One pass per AG_COLS columns.  The Y~ chunk is loaded first (its LDS stage must not wait
-  // for the W~ loads, the memory counter being in order), then every W~ load of the pass,
-  // unconditional from one base (row clamped into range, immediate offsets; the W~ buffer
-  // has AG_COLS elements of slack past its end) and kept raw: masks and conversions are
-  // applied at the products, so that the products of group g wait only for its own loads.
-  for (int j0 = 0; j0 < n2; j0 += AG_COLS) {
+    for (int ks = 0; ks < KV; ++ks) {
+      const int sr = (4 * ks + q) >> 1;
+      const bool ok = sr < r && sc < r;
+      const double v = base[ok ? (uint32_t)(2 * (sr * r + sc) + (dd != ee)) : 0u];
+      bg[ks] = ok ? (dd > ee ? -v : v) : 0.0;
+    }
+  };
+  v4f acc[NNT];
+  v4d accd[NNT];
+#pragma unroll
+  for (int u = 0; u < NNT; ++u) accd[u] = v4d{0.0, 0.0, 0.0, 0.0};
+  const int pcols = wc * AG_GROUPS * 8;   // columns per pass
+  for (int j0 = 0; j0 < n2; j0 += pcols) {
     using raw_t = typename std::conditional<MIXED, uint32_t, float2>::type;
-    const int nc = min(AG_COLS, n2 - j0), ngroups = (nc + 7) / 8;
-    float2 yv[YPER];
+    const int nc = min(pcols, n2 - j0);
+    // The Y~ chunk is loaded first (its LDS stage must not wait for the W~ loads, the memory
+    // counter being in order): the threads of a wavefront column load its own columns.
+    float2 y0[YPER], y1[YPER];
+    const int jw = cg * AG_GROUPS * 8, tl = tid - cg * 64 * RT;
 #pragma unroll
     for (int u = 0; u < YPER; ++u) {
-      const int e = tid + 256 * u, s = e / AG_COLS, jj = e % AG_COLS;
-      yv[u] = yt[((size_t)b * r + min(s, r - 1)) * n2 + j0 + min(jj, nc - 1)];
+      const int e = tl + 64 * RT * u, sx = e / (AG_GROUPS * 4), jj = jw + 2 * (e % (AG_GROUPS * 4));
+      const float2* src = yt + ((size_t)b * r + min(sx, r - 1)) * n2 + j0;
+      y0[u] = src[min(jj, nc - 1)];
+      y1[u] = src[min(jj + 1, nc - 1)];
     }
-    // group g covers columns j0 + 8 g .. + 7; this lane takes 2 (groups past the last valid
-    // one load the last one again: no extra memory traffic, the values are dropped)
-    raw_t lo[AG_COLS / 8], hi[AG_COLS / 8];
-    const raw_t* wrow = (const raw_t*)wt + ((size_t)min(max(row, 0), n1 - 1) * nb + b) * n2 + j0 + 2 * q;
+    // Every W~ load of the pass: unconditional from one base (row clamped into range; the buffer
+    // has slack past its end), kept raw so that the products of group g wait for its own loads.
+    // Group g of this wavefront covers columns jw + 8 g .. + 7; this lane takes 2
+    const int ng = min(AG_GROUPS, (nc - jw + 7) / 8);   // <= 0: no columns left
+    raw_t lo[AG_GROUPS], hi[AG_GROUPS];
+    const raw_t* wrow = (const raw_t*)wt + ((size_t)min(max(row, 0), n1 - 1) * nb + b) * n2 + j0 + (ng > 0 ? jw : 0) + 2 * q;
 #pragma unroll
-    for (int g = 0; g < AG_COLS / 8; ++g) {
-      const int gc = min(g, ngroups - 1);
+    for (int g = 0; g < AG_GROUPS; ++g) {
+      const int gc = max(0, min(g, ng - 1));
       lo[g] = wrow[8 * gc];
       hi[g] = wrow[8 * gc + 1];
     }
     if (j0 > 0) __syncthreads();   // every wavefront is done with the previous chunk
 #pragma unroll
     for (int u = 0; u < YPER; ++u) {
-      const int e = tid + 256 * u, s = e / AG_COLS, jj = e % AG_COLS;
-      const float2 y = (s < r && jj < nc) ? yv[u] : make_float2(0.f, 0.f);
-      if constexpr (MIXED) ((uint2*)ysh)[e] = make_uint2(bf16_split(y.x), bf16_split(y.y));
-      else ysh[e] = y;
+      const int e = tl + 64 * RT * u, sx = e / (AG_GROUPS * 4), pr = cg * AG_GROUPS * 4 + e % (AG_GROUPS * 4), jj = 2 * pr;
+      const float2 z = make_float2(0.f, 0.f), a = sx < r && jj < nc ? y0[u] : z, c = sx < r && jj + 1 < nc ? y1[u] : z;
+      if (sx < RM) {
+        // e = 0: (Yr, Yi, Yr', Yi');  e = 1: (-Yi, Yr, -Yi', Yr')
+        float4 o0, o1;
+        if constexpr (MIXED) {   // four hi parts, then four lo parts
+          const uint32_t ar = bf16_split(a.x), ai = bf16_split(a.y), cr = bf16_split(c.x), ci = bf16_split(c.y), sg = 0x80008000u;
+          const uint32_t an = ai ^ sg, cn = ci ^ sg;
+          auto his = [](uint32_t x, uint32_t y) { return __uint_as_float((x & 0xffffu) | (y << 16)); };
+          auto los = [](uint32_t x, uint32_t y) { return __uint_as_float((x >> 16) | (y & 0xffff0000u)); };
+          o0 = make_float4(his(ar, ai), his(cr, ci), los(ar, ai), los(cr, ci));
+          o1 = make_float4(his(an, ar), his(cn, cr), los(an, ar), los(cn, cr));
+        } else {
+          o0 = make_float4(a.x, a.y, c.x, c.y);
+          o1 = make_float4(-a.y, a.x, -c.y, c.x);
+        }
+        ysh[(2 * sx) * ystride + pr] = o0;
+        ysh[(2 * sx + 1) * ystride + pr] = o1;
+      }
     }
     __syncthreads();
 #pragma unroll
-    for (int g = 0; g < AG_COLS / 8; ++g) {
-      if (g < ngroups) {
-        const int valid = row_in ? min(2, nc - (8 * g + 2 * q)) : 0;
+    for (int u = 0; u < NNT; ++u) acc[u] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int g = 0; g < AG_GROUPS; ++g) {
+      if (g < ng) {
+        // columns past the end hold other data: dropped in the last group only (rows outside
+        // the matrix hold a clamped row's product, dropped when A' is stored)
+        if (jw + 8 * g + 8 > nc) {
+          const int valid = nc - jw - (8 * g + 2 * q);
+          const raw_t z = raw_t();
+          lo[g] = valid > 0 ? lo[g] : z;
+          hi[g] = valid > 1 ? hi[g] : z;
+        }
+        const float4* yg = ysh + m * ystride + (jw >> 1) + 4 * g + q;
         if constexpr (MIXED) {
           // BF16 matrix cores: this lane's four K values are the two packed W~ words as they
           // are (exact), Y~ enters split into its hi and lo BF16 parts (two products)
-          const uint32_t w0 = valid > 0 ? lo[g] : 0u, w1 = valid > 1 ? hi[g] : 0u;
-          const v4s av = v4s{(short)(w0 & 0xffffu), (short)(w0 >> 16), (short)(w1 & 0xffffu), (short)(w1 >> 16)};
+          const v4s av = __builtin_bit_cast(v4s, make_uint2(lo[g], hi[g]));
 #pragma unroll
           for (int u = 0; u < NNT; ++u) {
-            const int s = min((16 * u + m) >> 1, r - 1);   // columns past 2r are dropped below
-            const uint4 y2 = *(const uint4*)&((const uint2*)ysh)[s * AG_COLS + 8 * g + 2 * q];   // split (re, im) of Y~(s, j), Y~(s, j + 1)
-            // e = 0: (Yr, Yi, Yr', Yi');  e = 1: (-Yi, Yr, -Yi', Yr'), per part
-            v4s bh, bl;
-            if (eodd) {
-              bh = v4s{(short)((y2.y & 0xffffu) ^ 0x8000u), (short)(y2.x & 0xffffu), (short)((y2.w & 0xffffu) ^ 0x8000u),
-                       (short)(y2.z & 0xffffu)};
-              bl = v4s{(short)((y2.y >> 16) ^ 0x8000u), (short)(y2.x >> 16), (short)((y2.w >> 16) ^ 0x8000u),
-                       (short)(y2.z >> 16)};
-            } else {
-              bh = v4s{(short)(y2.x & 0xffffu), (short)(y2.y & 0xffffu), (short)(y2.z & 0xffffu), (short)(y2.w & 0xffffu)};
-              bl = v4s{(short)(y2.x >> 16), (short)(y2.y >> 16), (short)(y2.z >> 16), (short)(y2.w >> 16)};
-            }
-            acc[u] = mfma16bf(av, bl, acc[u]);
-            acc[u] = mfma16bf(av, bh, acc[u]);
+            const float4 y2 = yg[16 * u * ystride];
+            acc[u] = mfma16bf(av, __builtin_bit_cast(v4s, make_float2(y2.z, y2.w)), acc[u]);
+            acc[u] = mfma16bf(av, __builtin_bit_cast(v4s, make_float2(y2.x, y2.y)), acc[u]);
           }
         } else {
-          const float2 a0 = lo[g], a1 = hi[g], z = make_float2(0.f, 0.f);
-          const float4 wa = make_float4(valid > 0 ? a0.x : z.x, valid > 0 ? a0.y : z.y, valid > 1 ? a1.x : z.x,
-                                        valid > 1 ? a1.y : z.y);
+          const float2 a0 = lo[g], a1 = hi[g];
 #pragma unroll
           for (int u = 0; u < NNT; ++u) {
-            const int s = min((16 * u + m) >> 1, r - 1);   // columns past 2r are dropped below
-            const float4 y2 = *(const float4*)&ysh[s * AG_COLS + 8 * g + 2 * q];   // Y~(s, j), Y~(s, j + 1)
-            // e = 0: (Yr, Yi, Yr', Yi');  e = 1: (-Yi, Yr, -Yi', Yr')
-            const float b0 = eodd ? -y2.y : y2.x, b1 = eodd ? y2.x : y2.y;
-            const float b2 = eodd ? -y2.w : y2.z, b3 = eodd ? y2.z : y2.w;
-            acc[u] = mfma4(wa.x, b0, acc[u]);
-            acc[u] = mfma4(wa.y, b1, acc[u]);
-            acc[u] = mfma4(wa.z, b2, acc[u]);
-            acc[u] = mfma4(wa.w, b3, acc[u]);
+            const float4 y2 = yg[16 * u * ystride];
+            acc[u] = mfma4(a0.x, y2.x, acc[u]);
+            acc[u] = mfma4(a0.y, y2.y, acc[u]);
+            acc[u] = mfma4(a1.x, y2.z, acc[u]);
+            acc[u] = mfma4(a1.y, y2.w, acc[u]);
           }
         }
       }
     }
+#pragma unroll
+    for (int u = 0; u < NNT; ++u)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) accd[u][t] += (double)acc[u][t];
   }
-  // A tile to LDS: element t of tile u is A'[16 w + 4 q + t][16 u + m] = (re, im)_e A(i, s)
-  float* af = (float*)ash;
+  double bg[KV];
+  if (!raw_a) load_g(gyp, cg % CT, bg);
+  const int noqy = raw_a || qy_zero[b];
+  __syncthreads();   // every wavefront is done with the Y~ chunk
+  // partial A' of this wavefront: element t of tile u is A'[16 rt + 4 q + t][16 u + m]
 #pragma unroll
-  for (int u = 0; u < NNT; ++u) {
-    const int col = 16 * u + m;
-    if (col < 2 * r) {
+  for (int u = 0; u < NNT; ++u)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) af[(16 * w + 4 * q + t) * 2 * r + col] = acc[u][t];
+    for (int t = 0; t < 4; ++t)
+      {
+        const int ro = 16 * rt + 4 * q + t;
+        ash[(cg * ROWS + ro) * LDA + 16 * u + m] = 16 * u + m < 2 * r && i0 + ro >= 0 && i0 + ro < n1 ? accd[u][t] : 0.0;
+      }
+  __syncthreads();
+  if (wc > 1) {
+    for (int e = tid; e < ROWS * 2 * RM; e += nt) {   // the sum over the wavefront columns, in order
+      const int at = e / (2 * RM) * LDA + e % (2 * RM);
+      double v = ash[at];
+      for (int c = 1; c < wc; ++c) v += ash[c * ROWS * LDA + at];
+      ash[at] = v;
     }
+    __syncthreads();
   }
   if (raw_a) {
-    __syncthreads();
-    for (int e = tid; e < AG_ROWS * r; e += 256) {
-      const int s = e / AG_ROWS, rr = e % AG_ROWS;
-      if (i0 + rr < n1) rhs[((size_t)b * r + s) * n1 + i0 + rr] = ash[rr * r + s];
+    for (int e = tid; e < ROWS * r; e += nt) {
+      const int s = e / ROWS, rr = e % ROWS;
+      if (i0 + rr < n1)
+        rhs[((size_t)b * r + s) * n1 + i0 + rr] = make_float2((float)ash[rr * LDA + 2 * s], (float)ash[rr * LDA + 2 * s + 1]);
     }
     return;
   }
-  const int noqy = qy_zero[b];
-  cd* qs = (cd*)ysh;   // I - eta P_Y reuses the Y~ chunk (16 KB of its 32 KB)
-  __syncthreads();     // every wavefront is done with the Y~ chunk
-  for (int e = tid; e < r * r; e += 256) {
-    gs[e] = gyp[(size_t)b * r * r + e];
-    if (!noqy) qs[e] = qy[(size_t)b * r * r + e];
+  // V' = A' G' tile by tile: lane (m, q) holds rows q + 4 t, column m of its tile
+  double* vsh = ash + ROWS * LDA;
+  v4d res[CT];
+#pragma unroll
+  for (int k = 0; k < CT; ++k) {
+    const int ct = cg + k * wc;
+    if (ct >= CT) break;   // the same in the whole wavefront
+    if (k > 0) load_g(gyp, ct, bg);
+    v4d v = v4d{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int ks = 0; ks < KV; ++ks) v = mfma4d(ash[(16 * rt + m) * LDA + 4 * ks + q], bg[ks], v);
+    res[k] = v;
+    if (hk >= 0) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) vsh[(16 * rt + q + 4 * t) * LDA + 16 * ct + m] = v[t];
+    }
   }
-  __syncthreads();
-  // thread (il, qq) = (tid / 4, tid % 4) takes row i0 + il, columns s = qq, qq + 4, ...
-  const int il = tid >> 2, qq = tid & 3, i = i0 + il;
-  constexpr int SP = RM / 4;
+  __syncthreads();   // V of every row of the block is in LDS
   if (hk >= 0) {
-    {
-      cd ag[SP];   // V(i, :) = A(i, :) G_Y^+, one independent chain per column
+    // (H_rho1^{-1} V)(i, s): direct tap c lambda^|i - j| plus the reflections in the two
+    // ends, c lambda^(i + j + 1) and c lambda^(2 n1 - 1 - i - j), where within the table
 #pragma unroll
-      for (int us = 0; us < SP; ++us) ag[us] = cd_make(0.0, 0.0);
-      if (i >= 0 && i < n1) {
-        for (int u = 0; u < r; ++u) {
-          const float2 av = ash[il * r + u];
-          const cd a = cd_make(av.x, av.y);
-#pragma unroll
-          for (int us = 0; us < SP; ++us) cd_fma(ag[us], a, gs[u * r + min(qq + 4 * us, r - 1)]);
-        }
+    for (int k = 0; k < CT; ++k) res[k] = v4d{0.0, 0.0, 0.0, 0.0};
+    const int k0 = max(0, 16 * rt - hk) >> 2, k1 = (min(ROWS, 16 * rt + 16 + hk) + 3) >> 2, tmax = 2 * hk + 1;
+    const bool ends = i0 <= hk || i0 + ROWS >= n1 - hk - 1;   // the same in the whole block
+    for (int kk = k0; kk < k1; ++kk) {
+      const int j = i0 + 4 * kk + q, dist = abs(row - j);
+      double wgt = tsh[min(dist, tmax)];
+      if (ends) {
+        const int e1 = row + j + 1, e2 = 2 * n1 - 1 - row - j;
+        wgt += (e1 >= 0 && e1 <= tmax ? tsh[min(max(e1, 0), tmax)] : 0.0) +
+               (e2 >= 0 && e2 <= tmax ? tsh[min(max(e2, 0), tmax)] : 0.0);
+        if (j < 0 || j >= n1) wgt = 0.0;
       }
+      wgt = dist <= hk ? wgt : 0.0;
 #pragma unroll
-      for (int us = 0; us < SP; ++us)
-        if (qq + 4 * us < r) vsh[(qq + 4 * us) * AG_ROWS + il] = ag[us];
-    }
-    __syncthreads();   // V of every row of the block is in LDS
-    // thread (ro, sg) = (tid % 64, tid / 64): row i0 + ro, columns s = sg, sg + 4, ...
-    const int ro = tid & 63, sg = tid >> 6, io = i0 + ro;
-    const bool out = io >= 0 && io < n1 && ro >= hk && ro < AG_ROWS - hk;
-    cd t[SP];
-#pragma unroll
-    for (int us = 0; us < SP; ++us) t[us] = cd_make(0.0, 0.0);
-    if (out) {
-      // (H_rho1^{-1} V)(io, s): direct tap c lambda^|io - j| plus the reflections in the two
-      // ends, c lambda^(io + j + 1) and c lambda^(2 n1 - 1 - io - j), where within the table
-      const int tmax = 2 * hk + 1;
-      for (int d = -hk; d <= hk; ++d) {
-        const int j = io + d;
-        if (j < 0 || j >= n1) continue;
-        const int e1 = io + j + 1, e2 = 2 * n1 - 1 - io - j;
-        const double wgt = tsh[d < 0 ? -d : d] + (e1 <= tmax ? tsh[min(e1, tmax)] : 0.0) +
-                           (e2 <= tmax ? tsh[min(e2, tmax)] : 0.0);
-#pragma unroll
-        for (int us = 0; us < SP; ++us) {
-          const cd v = vsh[min(sg + 4 * us, r - 1) * AG_ROWS + ro + d];
-          t[us].re = fma(wgt, v.re, t[us].re);
-          t[us].im = fma(wgt, v.im, t[us].im);
-        }
+      for (int k = 0; k < CT; ++k) {
+        const int ct = cg + k * wc;
+        if (ct >= CT) break;
+        res[k] = mfma4d(wgt, vsh[(4 * kk + q) * LDA + 16 * ct + m], res[k]);
       }
-#pragma unroll
-      for (int us = 0; us < SP; ++us) t[us] = cd_scale(t[us], eta);
-      if (!noqy) {
-        for (int v2 = 0; v2 < r; ++v2) {
-          const float2 x0 = xt[((size_t)b * r + v2) * n1 + io];
-          const cd xv = cd_make(x0.x, x0.y);
-#pragma unroll
-          for (int us = 0; us < SP; ++us) cd_fma(t[us], xv, qs[v2 * r + min(sg + 4 * us, r - 1)]);
-        }
-      }
-    }
-    __syncthreads();   // every X~ read of the block is done before X~ is overwritten
-    if (out) {
-      const bool real_bin = bin_is_real(b, n3);
-#pragma unroll
-      for (int us = 0; us < SP; ++us) {
-        const int s = sg + 4 * us;
-        if (s < r) xout[((size_t)b * r + s) * n1 + io] = make_float2((float)t[us].re, real_bin ? 0.0f : (float)t[us].im);
-      }
-    }
-    return;
-  }
-  float2 res[SP];
-  if (i < n1) {
-    const double deg = (n1 == 1) ? 0.0 : ((i == 0 || i == n1 - 1) ? 1.0 : 2.0);
-    const double dii = 1.0 + rho1 * deg;
-    // eta A(i, :) G_Y^+ for this thread's SP columns, one independent chain per column
-    cd ag[SP];
-#pragma unroll
-    for (int us = 0; us < SP; ++us) ag[us] = cd_make(0.0, 0.0);
-    for (int u = 0; u < r; ++u) {
-      const float2 av = ash[il * r + u];
-      const cd a = cd_make(av.x, av.y);
-#pragma unroll
-      for (int us = 0; us < SP; ++us) {
-        const int s = min(qq + 4 * us, r - 1);   // columns past r are discarded below
-        cd_fma(ag[us], a, gs[u * r + s]);
-      }
-    }
-#pragma unroll
-    for (int us = 0; us < SP; ++us) {
-      const int s = qq + 4 * us;
-      if (s >= r) break;
-      cd t = cd_scale(ag[us], eta);
-      if (!noqy) {
-        // (H_rho1 U)_i = (1 + rho1 deg_i) U_i - rho1 (U_{i-1} + U_{i+1}); outside rows are 0
-        cd um = cd_make(0.0, 0.0), u0 = cd_make(0.0, 0.0), up = cd_make(0.0, 0.0);
-        for (int v2 = 0; v2 < r; ++v2) {
-          const float2* xc = xt + ((size_t)b * r + v2) * n1;
-          const cd qv = qs[v2 * r + s];
-          const float2 z = make_float2(0.f, 0.f);
-          const float2 x0 = xc[i], x1 = ld_or(xc, i - 1, i > 0, z), x2 = ld_or(xc, i + 1, i + 1 < n1, z);
-          cd_fma(u0, cd_make(x0.x, x0.y), qv);
-          cd_fma(um, cd_make(x1.x, x1.y), qv);
-          cd_fma(up, cd_make(x2.x, x2.y), qv);
-        }
-        t = cd_add(t, cd_sub(cd_scale(u0, dii), cd_scale(cd_add(um, up), rho1)));
-      }
-      res[us] = make_float2((float)t.re, (float)t.im);
     }
   }
-  __syncthreads();   // every thread has read A; its rows now take the results
-  if (i < n1) {
 #pragma unroll
-    for (int us = 0; us < SP; ++us) {
-      const int s = qq + 4 * us;
-      if (s < r) ash[il * r + s] = res[us];
+  for (int k = 0; k < CT; ++k) {
+    const int ct = cg + k * wc;
+    if (ct >= CT) break;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) res[k][t] *= eta;
+    if (!noqy) {   // + U, or + H_rho1 U = (H_rho1 X~) (I - eta P_Y)
+      load_g(qy, ct, bg);
+      const double deg = (n1 == 1) ? 0.0 : ((row == 0 || row == n1 - 1) ? 1.0 : 2.0);
+#pragma unroll
+      for (int ks = 0; ks < KV; ++ks) {
+        const int kk = 4 * ks + q, s = min(kk >> 1, r - 1), ic = min(max(row, 0), n1 - 1);
+        const float2* xc = xt + ((size_t)b * r + s) * n1;
+        const float2 x0 = xc[ic];
+        double xv = (kk & 1) ? x0.y : x0.x;
+        if (hk < 0) {
+          const float2 xm = xc[max(ic - 1, 0)], xp = xc[min(ic + 1, n1 - 1)];
+          xv = (1.0 + rho1 * deg) * xv - rho1 * ((ic > 0 ? (double)((kk & 1) ? xm.y : xm.x) : 0.0) +
+                                                (ic + 1 < n1 ? (double)((kk & 1) ? xp.y : xp.x) : 0.0));
+        }
+        res[k] = mfma4d(kk < 2 * r && row_in ? xv : 0.0, bg[ks], res[k]);
+      }
     }
   }
-  __syncthreads();
-  for (int e = tid; e < AG_ROWS * r; e += 256) {   // coalesced along i
-    const int s = e / AG_ROWS, rr = e % AG_ROWS;
-    if (i0 + rr < n1) rhs[((size_t)b * r + s) * n1 + i0 + rr] = ash[rr * r + s];
+  __syncthreads();   // every X~ read of the block is done before X~ is overwritten
+  const bool real_bin = hk >= 0 && bin_is_real(b, n3);
+  float* out = (float*)(hk >= 0 ? xout : rhs);
+#pragma unroll
+  for (int k = 0; k < CT; ++k) {
+    const int ct = cg + k * wc, col = 16 * ct + m;
+    if (ct >= CT || col >= 2 * r) break;
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const int ro = 16 * rt + q + 4 * t, io = i0 + ro;
+      const bool in = io >= 0 && io < n1 && (hk < 0 || (ro >= hk && ro < ROWS - hk));
+      if (in) out[(((size_t)b * r + (col >> 1)) * n1 + io) * 2 + (col & 1)] = (real_bin && (col & 1)) ? 0.0f : (float)res[k][t];
+    }
   }
 }
 
@@ -598,26 +613,48 @@ int hinv_stencil(double rho1, int n1, int r, double* tap) {
   return k;
 }
 
+// Row tiles and wavefront columns of an X-update block.  64 rows while that gives the device
+// two rounds of blocks, else 32 (the stencil's halo permitting: 1.5 times the rows read, but
+// twice the blocks; 144 x 288 x 28 10.1 us against 13.0), and 32 where they hold the matrix
+// (12 x 12 x 8064 18.2 us against 28.6).  The columns of W~ are split over wavefronts, 48 each,
+// while the grid has fewer than 2048 of them (144 x 288 x 28 12.9 us with one column, 10.1 with
+// three or more; 529 x 96 x 112, whose grid fills the device, 21.2 with one, 26.6 with two).
+static void agemm_shape(const Plan& p, int hk, int rm, int* rt, int* wc) {
+  const int halo = hk >= 0 ? 2 * hk : 0;
+  const long blocks4 = (long)((p.n1 + 63 - halo) / (64 - halo)) * p.nb;
+  *rt = rm == 32 || (halo <= 16 && (blocks4 < 512 || p.n1 <= 32 - halo)) ? 2 : 4;
+  const long waves = (long)((p.n1 + 16 * *rt - halo - 1) / (16 * *rt - halo)) * p.nb * *rt;
+  const int most = (rm == 32 ? 8 : 16) / *rt, want = (p.n2 + 8 * AG_GROUPS - 1) / (8 * AG_GROUPS);
+  *wc = (int)(2048 / waves);
+  if (*wc < 1) *wc = 1;
+  if (*wc > want) *wc = want;
+  if (*wc > most) *wc = most;
+}
+
+typedef void (*AgemmKernel)(const void*, const float2*, const float2*, const cd*, const cd*, const int*, float2*, int, int,
+                            int, int, double, double, int, uint32_t*, float2*, int, HStencil);
+template <int RM>
+static AgemmKernel agemm_kernel(int mixed, int rt) {
+  if constexpr (RM == 32) return mixed ? k_agemm<32, true, 2> : k_agemm<32, false, 2>;
+  else if (rt == 4) return mixed ? k_agemm<RM, true, 4> : k_agemm<RM, false, 4>;
+  else return mixed ? k_agemm<RM, true, 2> : k_agemm<RM, false, 2>;
+}
+
 void launch_agemm(const Plan& p, int raw_a, int advance, int scratch_out) {
   HStencil hs;
   hs.k = raw_a ? -1 : p.hk;
   for (int d = 0; d < 2 * HINV_KMAX + 2; ++d) hs.tap[d] = d <= 2 * hs.k + 1 ? p.htap[d] : 0.0;
-  const int rows = hs.k >= 0 ? AG_ROWS - 2 * hs.k : AG_ROWS;
+  const int rm = p.r <= 8 ? 8 : (p.r <= 16 ? 16 : 32);
+  int rt, wc;
+  agemm_shape(p, hs.k, rm, &rt, &wc);
+  const int rows = hs.k >= 0 ? 16 * rt - 2 * hs.k : 16 * rt;
   float2* xout = scratch_out ? p.rhs : p.xt;
-  dim3 grid((p.n1 + rows - 1) / rows, p.nb);
-#define TCTF_AGEMM(RM, MX)                                                                                    \
-  k_agemm<RM, MX><<<grid, 256, 0, p.stream>>>(p.wt, p.yt, p.xt, p.gyp, p.qy, p.qy_zero, p.rhs, p.n1, p.n2, p.r, \
-                                              p.nb, p.eta, p.rho1, raw_a, advance ? p.ctr : nullptr, xout, p.n3, hs)
-  if (p.mixed) {
-    if (p.r <= 8) TCTF_AGEMM(8, true);
-    else if (p.r <= 16) TCTF_AGEMM(16, true);
-    else TCTF_AGEMM(32, true);
-  } else {
-    if (p.r <= 8) TCTF_AGEMM(8, false);
-    else if (p.r <= 16) TCTF_AGEMM(16, false);
-    else TCTF_AGEMM(32, false);
-  }
-#undef TCTF_AGEMM
+  const dim3 grid((p.n1 + rows - 1) / rows, p.nb);
+  const AgemmKernel kernel = rm == 8 ? agemm_kernel<8>(p.mixed, rt) : (rm == 16 ? agemm_kernel<16>(p.mixed, rt) : agemm_kernel<32>(p.mixed, rt));
+  const size_t lds = agemm_lds_bytes(rm, rt, wc);
+  if (lds > 65536) (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  kernel<<<grid, 64 * rt * wc, lds, p.stream>>>(p.wt, p.yt, p.xt, p.gyp, p.qy, p.qy_zero, p.rhs, p.n1, p.n2, p.r, p.nb,
+                                                p.eta, p.rho1, raw_a, advance ? p.ctr : nullptr, xout, p.n3, hs);
 }
 
 // Outputs of the G_X launches, per frequency b ([nb][r][r] FP64 complex unless noted).

@@ -1,0 +1,34 @@
+"""The products of the iteration at the edges of their tiles (needs an MI355X), each run against
+the FP64 oracle with the tolerances of the parity tests."""
+import pytest
+
+from tests.gpu_helpers import gpu_run, make_inputs, oracle_run
+from tests.test_gpu_parity import _compare
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n1,n2,n3,r,rho1,eta", [
+    (22, 48, 3, 8, 1e-2, 1.0),     # one block of 32 rows less the halo, one pass of 48 columns
+    (23, 49, 3, 9, 1e-2, 0.7),     # a second block, a second wavefront column with one column
+    (32, 97, 4, 16, 0.0, 1.0),     # no halo: exactly 32 rows; three wavefront columns
+    (40, 300, 3, 8, 0.1, 0.8),     # halo 22: 64-row blocks; a pass of four wavefront columns, then another
+    (20, 1000, 2, 5, 1e-2, 1.0),   # 32-row blocks, three passes of eight wavefront columns
+    (55, 17, 80, 7, 1e-2, 1.0),    # a tube length outside the fused set, one row past a 64-row block's 54
+    (70, 60, 5, 17, 1e-2, 0.7),    # r > 16: the right-hand side, two wavefront columns
+    (45, 200, 4, 32, 0.3, 1.0),    # the largest rank, four wavefront columns and a second pass
+    (1200, 10, 56, 3, 1e-2, 1.0),  # enough blocks for 64 rows each
+])
+@pytest.mark.parametrize("precision", ["fp32", "mixed"])
+def test_x_update_edges(n1, n2, n3, r, rho1, eta, precision):
+    d = make_inputs(n1, n2, n3, r, p=0.5, seed=n1 + n2 + r, sigma_od=1.0, noise=0.02)
+    print(f"{n1}x{n2}x{n3} r{r} rho1 {rho1} eta {eta} {precision}", flush=True)
+    iters = 6 if precision == "fp32" else 1
+    g = gpu_run(d, r, iters, rho1=rho1, eta=eta, precision=precision)
+    st, info = oracle_run(d, r, iters, rho1=rho1, eta=eta, history=True)
+    if precision == "fp32":
+        _compare(g, st, info, label=f"{n1}x{n2}x{n3} r{r}")
+    else:
+        # one iteration from BF16 W~ (relative rounding up to 2^-8 per entry): W is a smoothed
+        # product of sums over it
+        _compare(g, st, None, label=f"{n1}x{n2}x{n3} r{r} mixed", tol=2.0**-7, tol_max=2.0**-5, tol_row=2.0**-5)
