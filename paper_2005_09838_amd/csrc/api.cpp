@@ -18,8 +18,7 @@
 #include "kernels.h"
 
 namespace tctf {
-size_t slice_lds_bytes(int n2, int n3);
-void slice_set_attr(int n3, size_t lds);
+void slice_set_attr(int n2, int n3, size_t lds);
 }  // namespace tctf
 
 using tctf::Plan;
@@ -230,7 +229,7 @@ static void fill_plan(tctf_ctx* c, hipStream_t stream) {
   q.nb = p.n3 / 2 + 1;
   q.spath = c->knobs.spath;
   q.ncu = c->ncu;
-  q.g_rows = q.spath == tctf::SPATH_COOP ? 1 : 0;   // the packed G's layout follows the slice path
+  q.gseg = q.spath == tctf::SPATH_SPLIT ? 0 : tctf::slice_segments(p.n2, p.n3);   // the packed G's order follows the slice path
   q.bcg = c->knobs.bcg;
   q.ycw = c->knobs.ycw;
   q.ny = (p.n2 + q.ycw - 1) / q.ycw;
@@ -371,7 +370,7 @@ static tctf_status ctx_init(tctf_ctx* c, const tctf_params* prm, const float* G,
   if (e != hipSuccess) return fail(TCTF_E_HIP, "hipDeviceGetAttribute: %s", hipGetErrorString(e));
   fill_plan(c, (hipStream_t)hip_stream);
   const Plan& p = c->plan;
-  tctf::slice_set_attr(p.n3, tctf::slice_launch_lds_bytes(p));
+  if (p.spath != tctf::SPATH_SPLIT) tctf::slice_set_attr(p.n2, p.n3, tctf::slice_launch_lds_bytes(p));
   tctf::ystep_set_attr(tctf::ystep_lds_bytes(p.r, p.ycw));
   tctf::bgemm_set_attr();
   tctf::gramx_set_attr(p.r);

@@ -74,15 +74,29 @@ __host__ __device__ __forceinline__ float2 unpack_bf16x2(uint32_t v) {
   return make_float2(bf16_to_f32((uint16_t)(v & 0xffffu)), bf16_to_f32((uint16_t)(v >> 16)));
 }
 
-// Unobserved entries of the packed observation tensor are quiet NaNs whose payload holds
-// the position t of the entry inside its run of consecutive unobserved entries along
-// mode 2 (bits 0..19) and whether that run starts at the first slot of the row (bit 20).
-__host__ __device__ __forceinline__ uint32_t pack_unobserved(uint32_t t, uint32_t starts_row) {
-  return 0x7fc00000u | (starts_row << 20) | (t & 0xfffffu);
+// Unobserved entries of the packed observation tensor are quiet NaNs whose payload is the
+// entry's index into the W-step's table of reciprocal pivots (Plan::wtab, below 4 n2): its
+// position in its run of consecutive unobserved entries along mode 2, in the table for the
+// kind of run (starting at the first slot of the row or after an observed entry) and of entry
+// (the last slot or not).
+__host__ __device__ __forceinline__ uint32_t pack_unobserved(uint32_t index) {
+  return 0x7fc00000u | (index & 0x3fffffu);
 }
 __device__ __forceinline__ bool is_unobserved(float g) { return (__float_as_uint(g) & 0x7f800000u) == 0x7f800000u; }
-__device__ __forceinline__ uint32_t unobs_pos(float g) { return __float_as_uint(g) & 0xfffffu; }
-__device__ __forceinline__ uint32_t unobs_starts_row(float g) { return (__float_as_uint(g) >> 20) & 1u; }
+__device__ __forceinline__ uint32_t unobs_index(float g) { return __float_as_uint(g) & 0x3fffffu; }
+
+// Offset of entry (i, j, k) in the packed G.  seg = 0: as in G, [n1][n2][n3].  seg = S > 0: each
+// OD row in the order in which the fused slice kernel's lanes read it.  S lanes share a row
+// (i, :, k); segment s holds n2 / S consecutive columns and the first n2 % S segments one more.
+// Column u of every segment comes before column u + 1, at (u n3 + k) S + s; the odd columns
+// u = n2 / S of the longer segments are last, at k (n2 % S) + s.
+__host__ __device__ __forceinline__ size_t packed_g_at(long i, int j, int k, int n2, int n3, int seg) {
+  if (seg == 0) return ((size_t)i * n2 + j) * n3 + k;
+  const int lf = n2 / seg, rem = n2 % seg, cut = rem * (lf + 1);
+  const int s = j < cut ? j / (lf + 1) : rem + (j - cut) / lf;
+  const int u = j < cut ? j % (lf + 1) : (j - cut) % lf;
+  return (size_t)i * n2 * n3 + (u < lf ? (size_t)(u * n3 + k) * seg + s : (size_t)lf * n3 * seg + (size_t)k * rem + s);
+}
 
 // Weight of stored frequency b in a sum over all n3 frequencies (conjugate pairs).
 __host__ __device__ __forceinline__ double bin_weight(int b, int n3) {

@@ -370,6 +370,17 @@ def main(path):
     for n, pl in plans.items():
         if pl:
             parts.append(f"template <> struct TubePlan<{n}> {{ static constexpr int M1 = {pl[0]}, M2 = {pl[1]}; }};")
+    # the LDS transforms' twiddles exp(+2 pi i n1 k2 / M) at n1 + M1 k2, then exp(+2 pi i b / N),
+    # b <= M, rounded from FP64 (device code only, on request)
+    parts.append("#ifdef TUBE_TWIDDLES")
+    parts.append("template <int N> struct TubeTwiddles { static constexpr __device__ float2 w[1] = {}; };")
+    for n, pl in plans.items():
+        if pl:
+            m = n // 2
+            ang = [2 * math.pi * n1 * k2 / m for k2 in range(pl[1]) for n1 in range(pl[0])] + [2 * math.pi * b / n for b in range(m + 1)]
+            vals = ", ".join("{%sf, %sf}" % (repr(snap(math.cos(t))), repr(snap(math.sin(t)))) for t in ang)
+            parts.append(f"template <> struct TubeTwiddles<{n}> {{ static constexpr __device__ float2 w[{n + 1}] = {{{vals}}}; }};")
+    parts.append("#endif")
     stats = []
     for n in SIZES:
         f, cf = gen_forward(n)

@@ -23,11 +23,9 @@ struct Plan {
   int mixed, force_eigen;
   hipStream_t stream;
 
-  float* gp;        // observed values, unobserved entries NaN-coded (run position); g_rows = 1:
-                    // [n1][n3][n2] (entry (i, j, k) at (i n3 + k) n2 + j: the cooperative slice
-                    // kernel reads 64 tubes per wave instruction), 0: [n1][n2][n3] (one thread
-                    // per tube or per row reads its own run of entries)
-  int g_rows;
+  float* gp;        // observed values, unobserved entries NaN-coded (pivot index), at packed_g_at
+  int gseg;         // its order: lanes per row of the fused slice kernel's W-step, 0 on the
+                    // three-launch path
   void* wt;         // W~ [n1][nb][n2] float2 (FP32) or packed bf16x2 (mixed)
   float2* zt;       // Z~ [n1][nb][n2]
   float2* xt;       // X~ [nb][r][n1]
@@ -84,7 +82,8 @@ void launch_zero(const Plan& p, void* dst, size_t bytes);
 // iteration
 enum SliceMode { SLICE_INIT = 0, SLICE_ITER = 1, SLICE_RESULT = 2, SLICE_KKT = 3 };
 // How steps 3, 4 and 7 run: one fused kernel per OD row with several threads per tube
-// (COOP) or one thread per tube (THREAD), or three launches through spatial buffers (SPLIT).
+// (COOP) or one thread per tube (THREAD), as the tube length has it, or three launches through
+// spatial buffers (SPLIT).
 enum SlicePath { SPATH_COOP = 1, SPATH_THREAD = 2, SPATH_SPLIT = 3 };
 int slice_default_path(int n2, int n3);
 bool slice_path_valid(int path, int n2, int n3);
@@ -94,6 +93,7 @@ void launch_gen_twiddles(const Plan& p);
 void launch_slice_generic(const Plan& p, int mode, float* w_out, float* z_out, int w_from_g);
 bool slice_hosts_pinvy(const Plan& p);   // the iteration's slice launch also forms G_Y^+
 size_t slice_launch_lds_bytes(const Plan& p);
+int slice_segments(int n2, int n3);              // lanes per row of the fused kernel's W-step
 void launch_slice(const Plan& p, int mode, float* w_out, float* z_out, int w_from_g);
 void launch_zgemm(const Plan& p, int with_pinv = 0);   // with_pinv: also G_Y^+ (pinvy_block)
 // advance: next rounding-bit counter; scratch_out: with the stencil, X~ goes to the rhs

@@ -7,39 +7,44 @@ namespace tctf {
 size_t wt_elem_bytes(const Plan& p) { return p.mixed ? 4 : 8; }
 
 // One thread per row (i, k) along mode 2.  Observed entries keep their value (they must
-// be finite); unobserved ones become NaNs carrying their position in the run of
-// consecutive unobserved entries (section 3.3: the equality constraints of the W-step
-// are eliminated row by row, leaving one tridiagonal system per run).  The packed copy is
-// stored row by row, [n1][n3][n2], for the cooperative slice kernel (a wavefront reads entry
-// (i, j, k) for 64 consecutive tubes j at once), else like G, [n1][n2][n3]: kernels with
-// one thread per tube or per row then read contiguous runs, and each wavefront keeps more
-// cache lines in flight.
+// be finite); unobserved ones become NaNs carrying their index into the pivot table
+// (section 3.3: the equality constraints of the W-step are eliminated row by row, leaving
+// one tridiagonal system per run of unobserved entries).  seg: the order (packed_g_at).
 __global__ void k_pack_g(const float* __restrict__ g, const uint8_t* __restrict__ om,
-                         float* __restrict__ gp, int n1, int n2, int n3, int rows, int* flag) {
+                         float* __restrict__ gp, int n1, int n2, int n3, int seg, int* flag) {
   const long row = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (row >= (long)n1 * n3) return;
   const long i = row / n3, k = row % n3;
   int run_start = -1;          // index of the first unobserved entry of the current run
   bool seen_obs = false;
+  // packed_g_at without its divisions: column j is column u of segment s
+  const int lf = seg ? n2 / seg : 0, rem = seg ? n2 % seg : 0;
+  float* row_out = gp + (size_t)i * n2 * n3;
+  int s = 0, u = 0;
   for (int j = 0; j < n2; ++j) {
-    const long idx = (i * n2 + j) * n3 + k, out = rows ? (i * n3 + k) * n2 + j : idx;
+    const long idx = (i * n2 + j) * n3 + k;
+    const size_t at = seg == 0 ? (size_t)j * n3 + k : (u < lf ? (size_t)(u * n3 + k) * seg + s : (size_t)lf * n3 * seg + (size_t)k * rem + s);
+    if (++u == lf + (s < rem ? 1 : 0)) {
+      u = 0;
+      ++s;
+    }
     if (om[idx]) {
       const float v = g[idx];
       if (!isfinite(v)) atomicOr(flag, 1);
-      gp[out] = v;
+      row_out[at] = v;
       seen_obs = true;
       run_start = -1;
     } else {
       if (run_start < 0) run_start = j;
-      const uint32_t starts_row = seen_obs ? 0u : 1u;
-      gp[out] = __uint_as_float(pack_unobserved((uint32_t)(j - run_start), starts_row));
+      const uint32_t table = (j == n2 - 1 ? 2u : 0u) + (seen_obs ? 1u : 0u);
+      row_out[at] = __uint_as_float(pack_unobserved(table * (uint32_t)n2 + (uint32_t)(j - run_start)));
     }
   }
 }
 
 void launch_pack_g(const Plan& p, const float* G, const uint8_t* omega) {
   const long rows = (long)p.n1 * p.n3;
-  k_pack_g<<<(unsigned)((rows + 255) / 256), 256, 0, p.stream>>>(G, omega, p.gp, p.n1, p.n2, p.n3, p.g_rows,
+  k_pack_g<<<(unsigned)((rows + 255) / 256), 256, 0, p.stream>>>(G, omega, p.gp, p.n1, p.n2, p.n3, p.gseg,
                                                                   p.flag);
 }
 
