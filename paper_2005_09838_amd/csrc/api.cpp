@@ -51,7 +51,7 @@ struct StateHeader {
 };
 
 struct Layout {
-  size_t gp, wt, zt, xt, yt, rhs, bpart, gxpart, gxm, dmat, gxp, qx, qx_zero, gym, gyp, qy, qy_zero, slice_obj, bin_obj, wtab, htab,
+  size_t gp, wt, zt, xt, yt, rhs, bpart, gxm, dmat, gxp, qx, qx_zero, gym, gyp, qy, qy_zero, slice_obj, bin_obj, wtab, htab,
       flag, ctr, zsp, wsp, csp, twg, rsig, rtx, rty, ranks, scal, xt_prev, yt_prev, wt_prev, stat_work, kkt, total;
   size_t state_bytes;
   bool split;   // the three-launch slice path's buffers exist
@@ -59,9 +59,9 @@ struct Layout {
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Complex columns per X~^* W~ block: 32 (half the re-reads of X~, and fewer blocks than
-// compute units at 529 x 96 x 112, so that the G_X launches beside it find free ones)
-// unless that leaves fewer than 128 blocks, then 16.
+// Complex columns per X~^* W~ block: 32 (half the re-reads of X~, and with the G_X blocks of
+// the same launch fewer blocks than compute units at 529 x 96 x 112) unless that leaves fewer
+// than 128 blocks, then 16.
 static int default_bcg(int n2, int nb, int r) {
   (void)r;
   return (long)((n2 + 31) / 32) * nb >= 128 ? 32 : 16;
@@ -103,7 +103,6 @@ static Layout make_layout(const tctf_params& p) {
   L.yt = take(nb * r * n2 * 8);
   L.rhs = take(nb * r * n1 * 8);
   L.bpart = take(nb * r * n2 * 16);
-  L.gxpart = take(nb * (size_t)tctf::gramx_groups(p.n1) * 2 * r * r * 16);
   L.gxm = take(nb * r * r * 16);
   L.dmat = take(nb * r * r * 16);
   L.gxp = take(nb * r * r * 16);
@@ -148,7 +147,6 @@ struct tctf_ctx {
   Layout lay;
   unsigned char* ws;
   int device;
-  int ncu;   // compute units of the device
   int64_t iters;
   bool term_valid;
   Knobs knobs;
@@ -165,10 +163,6 @@ struct tctf_ctx {
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
-  // inside the captured graph, G_X and its inverse run on a branch beside the X~^* W~ products
-  hipStream_t br_stream = nullptr;
-  hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-  bool capturing = false;
 };
 
 #define GRAPH_ITERS 10
@@ -228,7 +222,6 @@ static void fill_plan(tctf_ctx* c, hipStream_t stream) {
   q.r = p.r;
   q.nb = p.n3 / 2 + 1;
   q.spath = c->knobs.spath;
-  q.ncu = c->ncu;
   q.gseg = q.spath == tctf::SPATH_SPLIT ? 0 : tctf::slice_segments(p.n2, p.n3);   // the packed G's order follows the slice path
   q.bcg = c->knobs.bcg;
   q.ycw = c->knobs.ycw;
@@ -248,7 +241,6 @@ static void fill_plan(tctf_ctx* c, hipStream_t stream) {
   q.yt = (float2*)(w + L.yt);
   q.rhs = (float2*)(w + L.rhs);
   q.bpart = (double2*)(w + L.bpart);
-  q.gxpart = (cd*)(w + L.gxpart);
   q.gxm = (cd*)(w + L.gxm);
   q.dmat = (cd*)(w + L.dmat);
   q.gxp = (cd*)(w + L.gxp);
@@ -312,26 +304,7 @@ static tctf_status enqueue_iteration(tctf_ctx* c) {
   tctf_status s = TCTF_OK;
   if (s == TCTF_OK) s = stage(c, 2, [&] { tctf::launch_agemm(p, 0, 1); });
   if (s == TCTF_OK && p.hk < 0) s = stage(c, 3, [&] { tctf::launch_hsolve(p); });   // else inside the X-update
-  if (s == TCTF_OK && c->capturing) {
-    // G_X, its pseudo-inverse and I - eta P_X are needed first by the Y-step: in the graph they
-    // form a branch that runs beside the X~^* W~ chunk products and joins before the Y-step
-    hipError_t e = hipEventRecord(c->ev_fork, p.stream);
-    if (e == hipSuccess) e = hipStreamWaitEvent(c->br_stream, c->ev_fork, 0);
-    if (e == hipSuccess) {
-      Plan pb = p;
-      pb.stream = c->br_stream;
-      tctf::launch_gramx(pb);
-      e = hipEventRecord(c->ev_join, c->br_stream);
-    }
-    tctf::launch_bgemm(p);
-    if (e == hipSuccess) e = hipStreamWaitEvent(p.stream, c->ev_join, 0);
-    if (e != hipSuccess) s = fail(TCTF_E_HIP, "branch of the G_X launches: %s", hipGetErrorString(e));
-  } else if (s == TCTF_OK) {
-    s = stage(c, 4, [&] {
-      tctf::launch_gramx(p);
-      tctf::launch_bgemm(p);
-    });
-  }
+  if (s == TCTF_OK) s = stage(c, 4, [&] { tctf::launch_bgemm(p); });
   if (s == TCTF_OK) s = stage(c, 5, [&] { tctf::launch_ystep(p, 0); });
   // Z~ = X~Y~; G_Y^+ and I - eta P_Y for the next X-step ride along in extra blocks of the
   // cooperative slice launch, or of this launch on the other slice paths
@@ -366,14 +339,10 @@ static tctf_status ctx_init(tctf_ctx* c, const tctf_params* prm, const float* G,
   c->knobs = knobs ? *knobs : default_knobs(*prm);
   hipError_t e = hipGetDevice(&c->device);
   if (e != hipSuccess) return fail(TCTF_E_HIP, "hipGetDevice: %s", hipGetErrorString(e));
-  e = hipDeviceGetAttribute(&c->ncu, hipDeviceAttributeMultiprocessorCount, c->device);
-  if (e != hipSuccess) return fail(TCTF_E_HIP, "hipDeviceGetAttribute: %s", hipGetErrorString(e));
   fill_plan(c, (hipStream_t)hip_stream);
   const Plan& p = c->plan;
   if (p.spath != tctf::SPATH_SPLIT) tctf::slice_set_attr(p.n2, p.n3, tctf::slice_launch_lds_bytes(p));
   tctf::ystep_set_attr(tctf::ystep_lds_bytes(p.r, p.ycw));
-  tctf::bgemm_set_attr();
-  tctf::gramx_set_attr(p.r);
   tctf::pinvy_set_attr(p.r);
   tctf::zgemm_set_attr(p.r);
   tctf::launch_zero(p, p.flag, 64);
@@ -394,7 +363,6 @@ static tctf_status ctx_init(tctf_ctx* c, const tctf_params* prm, const float* G,
   tctf::launch_tube_dft_setup(p, y0, p.yt, p.r, p.n2, (long)p.r * p.n2, p.n2, 1);
   tctf::launch_zgemm(p);
   tctf::launch_slice(p, tctf::SLICE_INIT, nullptr, nullptr, 1);
-  tctf::launch_gramx(p);
   tctf::launch_bgemm(p);
   tctf::launch_ystep(p, 1);
   tctf::launch_pinvy(p, p.stream);
@@ -421,11 +389,6 @@ static void ctx_release(tctf_ctx* c) {
   c->graph = nullptr;
   if (c->cap_stream) hipStreamDestroy(c->cap_stream);
   c->cap_stream = nullptr;
-  if (c->br_stream) hipStreamDestroy(c->br_stream);
-  c->br_stream = nullptr;
-  if (c->ev_fork) hipEventDestroy(c->ev_fork);
-  if (c->ev_join) hipEventDestroy(c->ev_join);
-  c->ev_fork = c->ev_join = nullptr;
 }
 
 static tctf_status enqueue_iteration(tctf_ctx* c);
@@ -549,17 +512,12 @@ tctf_status tctf_create(const tctf_params* prm, const float* G, const uint8_t* o
 static tctf_status ensure_graph(tctf_ctx* c) {
   if (c->graph_exec) return TCTF_OK;
   if (!c->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
-  if (!c->br_stream) HIP_TRY(hipStreamCreateWithFlags(&c->br_stream, hipStreamNonBlocking));
-  if (!c->ev_fork) HIP_TRY(hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming));
-  if (!c->ev_join) HIP_TRY(hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming));
   const hipStream_t user = c->plan.stream;
   c->plan.stream = c->cap_stream;
   hipError_t e = hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal);
   tctf_status s = TCTF_OK;
   if (e == hipSuccess) {
-    c->capturing = true;
     for (int k = 0; k < GRAPH_ITERS && s == TCTF_OK; ++k) s = enqueue_iteration(c);
-    c->capturing = false;
     hipGraph_t g = nullptr;
     const hipError_t e2 = hipStreamEndCapture(c->cap_stream, &g);
     if (s == TCTF_OK && e2 == hipSuccess) {
@@ -906,7 +864,7 @@ tctf_status tctf_time_stage(tctf_ctx* c, int32_t stage, int32_t reps, double* me
       case 1: tctf::launch_zgemm(p); break;
       case 2: tctf::launch_agemm(p, 0, 0, 1); break;
       case 3: if (p.hk < 0) tctf::launch_hsolve(p); break;
-      case 4: tctf::launch_gramx(p); tctf::launch_bgemm(p); break;
+      case 4: tctf::launch_bgemm(p); break;
       case 5: tctf::launch_ystep(p, 1); break;
       case 6: tctf::launch_pinvy(p, p.stream); break;
       case 7: enqueue_iteration(c); c->iters++; break;
@@ -1147,12 +1105,9 @@ static tctf_status batch_graph(tctf_batch* b, int k) {
       for (size_t m = q; m < b->members.size() && s == TCTF_OK; m += nbr) {
         tctf_ctx* c = b->members[m];
         const hipStream_t user = c->plan.stream;
-        const int ncu = c->plan.ncu;
         c->plan.stream = b->streams[q];
-        c->plan.ncu = 0;   // members share the compute units: no launch reserves one for itself
         s = enqueue_iteration(c);
         c->plan.stream = user;
-        c->plan.ncu = ncu;
       }
     }
     if (e == hipSuccess) e = hipEventRecord(b->done_ev[q], b->streams[q]);

@@ -14,7 +14,6 @@ struct Plan {
   int bcg;                     // complex columns per X~^* W~ block (16 or 32)
   int ny, ycw;                 // column blocks of the Y-step per frequency, columns per block
   int spath;                   // slice path: SPATH_COOP, SPATH_THREAD or SPATH_SPLIT
-  int ncu;                     // compute units of the device
   double mu, rho1, rho2, eta;
   // H_rho1^{-1} as a stencil of half-width hk inside the X-update (k_agemm), hk = -1: the
   // X-update forms the right-hand side and k_hsolve solves (see hinv_stencil)
@@ -32,7 +31,6 @@ struct Plan {
   float2* yt;       // Y~ [nb][r][n2]
   float2* rhs;      // right-hand side of the H_rho1 solve [nb][r][n1]
   double2* bpart;   // X~^* W~ [nb][r][n2] (FP64)
-  cd* gxpart;       // partial Grams of X~ over row groups [nb][ngroup][2][r][r] (FP64)
   cd* gxm;          // G_X = X~^* H_rho1 X~ [nb][r][r]
   cd* dmat;         // (H X~)^* (H X~) [nb][r][r]
   cd* gxp;          // G_X^+ [nb][r][r]
@@ -103,14 +101,8 @@ void launch_agemm(const Plan& p, int raw_a = 0, int advance = 0, int scratch_out
 // where the stencil would be wider than HINV_KMAX, r > 16 or n1 < 2k + 2
 int hinv_stencil(double rho1, int n1, int r, double* tap);
 void launch_hsolve(const Plan& p);
-void launch_bgemm(const Plan& p);   // X~^* W~ over all rows
-void launch_gramx(const Plan& p);   // G_X, (H X~)^*(H X~), G_X^+ and I - eta P_X
-int gramx_groups(int n1);
-void gramx_set_attr(int r);
-size_t bgemm_lds_bytes(int r, int bcg);
+void launch_bgemm(const Plan& p);   // X~^* W~; G_X, (H X~)^*(H X~), G_X^+ and I - eta P_X
 bool bgemm_cols_valid(int r, int bcg);
-
-void bgemm_set_attr();
 void launch_ystep(const Plan& p, int init);
 void ystep_split(int n2, int r, int nb, int* ny, int* cw);
 size_t ystep_lds_bytes(int r, int cw);

@@ -194,9 +194,7 @@ __global__ void __launch_bounds__(256) k_adj_inv(const double2* __restrict__ g, 
   PinvScratch ps;
   ps.work = p + rr;
   ps.vec = ps.work + rr;
-  ps.colk = ps.vec + rr;
-  ps.rowk = ps.colk + r;
-  ps.rot = (double*)(ps.rowk + r);
+  ps.rot = (double*)(ps.vec + rr);
   ps.red = ps.rot + 96;
   for (int e = threadIdx.x; e < rr; e += blockDim.x) a[e] = cd_make(g[(long)b * rr + e].x, g[(long)b * rr + e].y);
   __syncthreads();
@@ -380,13 +378,13 @@ void adjoint_carve(const Plan& p, void* ws, AdjWork* w) {
 }
 
 void adjoint_set_attr(int r) {
-  if (pinvy_lds_bytes(r) > 65536)
+  if (pinv_lds_bytes(r) > 65536)
     (void)hipFuncSetAttribute((const void*)k_adj_inv, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)pinvy_lds_bytes(r));
+                              (int)pinv_lds_bytes(r));
 }
 
 static void inv(const Plan& p, const AdjWork& w, const double2* g, double2* gi) {
-  k_adj_inv<<<p.nb, 256, pinvy_lds_bytes(p.r), p.stream>>>(g, gi, p.r, w.flag);
+  k_adj_inv<<<p.nb, 256, pinv_lds_bytes(p.r), p.stream>>>(g, gi, p.r, w.flag);
 }
 
 static void wdot_add(const Plan& p, const AdjWork& w, const double2* A, const double2* B, long per, double coef,

@@ -2,8 +2,8 @@
 //   Z~_b = X~_b Y~_b                       (step 3)                   k_zgemm
 //   A_b  = W~_b Y~_b^*  and the X-update, or its right-hand side       k_agemm
 //          R_b = eta A_b G_Y^+ + H_rho1 X~_b (I - eta P_Y)   (step 1, eq. (updataXYW1))
-//   X~_b^* W~_b partial sums over row chunks (step 2), and in extra blocks of the same
-//   launch G_X = X~_b^* X~_b + rho1 (H X~_b)^*(H X~_b), G_X^+ and I - eta P_X  k_bgemm
+//   X~_b^* W~_b (step 2), and in extra blocks of the same launch
+//   G_X = X~_b^* X~_b + rho1 (H X~_b)^*(H X~_b), G_X^+ and I - eta P_X   k_bgemm
 // The complex products run on the matrix cores as real FP32 products (16 x 16 x 4 tiles):
 // a complex m x k by k x n product is an m x 2k by 2k x n' real one whose operands are the
 // interleaved (re, im) storage itself, with the signs of the complex product placed in the
@@ -37,18 +37,21 @@ __device__ __forceinline__ v4d mfma4d(double a, double b, v4d c) {
 // Block: 64 rows x one frequency, 4 wavefronts of 16 rows; Y~ staged in LDS by column
 // chunks of ZG_COLS; each wavefront sweeps its rows across the chunk in groups of 4
 // 16-column tiles.  Output tiles go straight to the interleaved Z~ rows.
-// The first npinv blocks instead form G_Y^+ and I - eta P_Y of frequency blockIdx.x for
-// the next X-step (pinvy_block): independent work that runs beside the product.
+// PINV: the first npinv blocks instead form G_Y^+ and I - eta P_Y of frequency blockIdx.x for
+// the next X-step (pinvy_block): independent work that runs beside the product (an instance of
+// its own, since its registers would halve the product's wavefronts).
 #define ZG_ROWS 64
 #define ZG_COLS 128
-template <int RM>   // r <= RM: every loop below has a compile-time trip count
+template <int RM, bool PINV>   // r <= RM: every loop below has a compile-time trip count
 __global__ void __launch_bounds__(256) k_zgemm(const float2* __restrict__ xt, const float2* __restrict__ yt,
                                                float2* __restrict__ zt, int n1, int n2, int r, int nb,
                                                int npinv, PinvyArgs pa) {
   extern __shared__ __align__(16) unsigned char zsm[];
-  if ((int)blockIdx.x < npinv) {
-    pinvy_block(blockIdx.x, pa, zsm);
-    return;
+  if constexpr (PINV) {
+    if ((int)blockIdx.x < npinv) {
+      pinvy_block(blockIdx.x, pa, zsm);
+      return;
+    }
   }
   float2* ysh = (float2*)zsm;   // [s][j] of the column chunk
   const int bid = blockIdx.x - npinv, ntile = (n1 + ZG_ROWS - 1) / ZG_ROWS;
@@ -152,14 +155,16 @@ __device__ __forceinline__ uint32_t bf16_split(float x) {
   const uint16_t h = f32_to_bf16(x);
   return (uint32_t)h | ((uint32_t)f32_to_bf16(x - bf16_to_f32(h)) << 16);
 }
-template <int RM>
+template <int RM, bool PINV>
 __global__ void __launch_bounds__(256) k_zgemm_bf(const float2* __restrict__ xt, const float2* __restrict__ yt,
                                                   float2* __restrict__ zt, int n1, int n2, int r, int nb,
                                                   int npinv, PinvyArgs pa) {
   extern __shared__ __align__(16) unsigned char zsm[];
-  if ((int)blockIdx.x < npinv) {
-    pinvy_block(blockIdx.x, pa, zsm);
-    return;
+  if constexpr (PINV) {
+    if ((int)blockIdx.x < npinv) {
+      pinvy_block(blockIdx.x, pa, zsm);
+      return;
+    }
   }
   uint2* ysh = (uint2*)zsm;   // [s][j] of the column chunk: (re, im) split words
   const int bid = blockIdx.x - npinv, ntile = (n1 + ZG_ROWS - 1) / ZG_ROWS;
@@ -257,11 +262,11 @@ __global__ void __launch_bounds__(256) k_zgemm_bf(const float2* __restrict__ xt,
 }
 
 void zgemm_set_attr(int r) {
-  if (pinvy_lds_bytes(r) > 65536) {
-    (void)hipFuncSetAttribute((const void*)k_zgemm<32>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)pinvy_lds_bytes(r));
-    (void)hipFuncSetAttribute((const void*)k_zgemm_bf<32>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)pinvy_lds_bytes(r));
+  if (pinv_lds_bytes(r) > 65536) {
+    (void)hipFuncSetAttribute((const void*)k_zgemm<32, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)pinv_lds_bytes(r));
+    (void)hipFuncSetAttribute((const void*)k_zgemm_bf<32, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)pinv_lds_bytes(r));
   }
 }
 
@@ -270,19 +275,23 @@ void launch_zgemm(const Plan& p, int with_pinv) {
   const int grid = npinv + (p.n1 + ZG_ROWS - 1) / ZG_ROWS * p.nb;
   const int rm = p.r <= 8 ? 8 : (p.r <= 16 ? 16 : 32);
   size_t lds = (size_t)rm * ZG_COLS * sizeof(float2);
-  if (with_pinv && pinvy_lds_bytes(p.r) > lds) lds = pinvy_lds_bytes(p.r);
+  if (with_pinv && pinv_lds_bytes(p.r) > lds) lds = pinv_lds_bytes(p.r);
   const PinvyArgs pa = pinvy_args(p);
-#define TCTF_ZGEMM(RM)                                                                                         \
-  do {                                                                                                         \
-    if (p.mixed)                                                                                               \
-      k_zgemm_bf<RM><<<grid, 256, lds, p.stream>>>(p.xt, p.yt, p.zt, p.n1, p.n2, p.r, p.nb, npinv, pa);        \
-    else                                                                                                       \
-      k_zgemm<RM><<<grid, 256, lds, p.stream>>>(p.xt, p.yt, p.zt, p.n1, p.n2, p.r, p.nb, npinv, pa);           \
+#define TCTF_ZGEMM_P(K, RM)                                                                                   \
+  do {                                                                                                        \
+    if (npinv) K<RM, true><<<grid, 256, lds, p.stream>>>(p.xt, p.yt, p.zt, p.n1, p.n2, p.r, p.nb, npinv, pa); \
+    else K<RM, false><<<grid, 256, lds, p.stream>>>(p.xt, p.yt, p.zt, p.n1, p.n2, p.r, p.nb, npinv, pa);      \
+  } while (0)
+#define TCTF_ZGEMM(RM)                      \
+  do {                                      \
+    if (p.mixed) TCTF_ZGEMM_P(k_zgemm_bf, RM); \
+    else TCTF_ZGEMM_P(k_zgemm, RM);         \
   } while (0)
   if (p.r <= 8) TCTF_ZGEMM(8);
   else if (p.r <= 16) TCTF_ZGEMM(16);
   else TCTF_ZGEMM(32);
 #undef TCTF_ZGEMM
+#undef TCTF_ZGEMM_P
 }
 
 // ---------------------------------------------------------------- A = W~ Y~^* and the X-update
@@ -657,7 +666,8 @@ void launch_agemm(const Plan& p, int raw_a, int advance, int scratch_out) {
                                                 p.eta, p.rho1, raw_a, advance ? p.ctr : nullptr, xout, p.n3, hs);
 }
 
-// Outputs of the G_X launches, per frequency b ([nb][r][r] FP64 complex unless noted).
+// ---------------------------------------------------------------- X~^* W~ and G_X in one launch
+// Outputs of the G_X blocks, per frequency b ([nb][r][r] FP64 complex unless noted).
 struct GramOut {
   cd* gxm;       // G_X
   cd* dmat;      // (H X~)^*(H X~)
@@ -668,208 +678,49 @@ struct GramOut {
   int force_eigen;
 };
 
-// ---------------------------------------------------------------- G_X in two launches
-// k_gramx_part: block (row group g, frequency b) forms over its GXR rows i0 .. i0 + GXR - 1
-// the FP64 partial Grams S_g = sum_i X~(i, :)^* X~(i, :) and, with the next row staged too,
-// D_g = sum_i (X~(i+1, :) - X~(i, :))^* (X~(i+1, :) - X~(i, :)) (no difference past the last
-// row), as the real Gram C = X'^T X' of X'[i][2s + d] = (re, im)_d X~(i, s) on the FP64
-// matrix cores: the rows are staged column by column (X'^T; zeros past n1 and r), and within
-// 16 rows the K order is permuted so that lane (m, q) feeds rows 4q .. 4q + 3, one 16-byte LDS
-// read (and one float of the next row) serving four steps.  At r <= 8 the four wavefronts
-// share the one tile and split the rows; otherwise each takes its tiles.  The lanes holding
-// C[2s][2t] gather the 2 x 2 real block by shuffles: X~^* X~ (s, t) = (C[2s][2t] +
-// C[2s+1][2t+1], C[2s][2t+1] - C[2s+1][2t]), likewise D.
-// k_gramx_inv: per frequency, the partials summed in a fixed order, G_X = S + rho1 D
-// (= X~^* H_rho1 X~), its pseudo-inverse (Lemma SVPMPI, pinv_herm) and I - eta P_X.
-#define GXR 64
-template <int RM>
-__global__ void __launch_bounds__(256) k_gramx_part(const float2* __restrict__ xt, int n1, int r, int ngrp,
-                                                    cd* __restrict__ part) {
-  constexpr int MT = RM / 8, NT = MT * MT;         // 16 x 16 tiles of the real Gram
-  constexpr int KS = NT >= 4 ? 1 : 4 / NT;         // wavefronts sharing a tile (row split)
-  constexpr int TPW = NT >= 4 ? NT / 4 : 1;        // tiles per wavefront
-  constexpr int LD = GXR + 4;                      // LDS stride of a staged column (floats)
-  constexpr int PER = ((GXR + 1) * RM + 255) / 256;
-  __shared__ __align__(16) float xs[2 * RM * LD];
-  __shared__ cd red[KS > 1 ? 2 * KS * RM * RM : 1];
-  const int g = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, w = tid >> 6, m = lane & 15,
-            q = lane >> 4;
-  const int i0 = g * GXR, rr = r * r, kp = KS > 1 ? w : 0;
-  const int nrows = min(GXR, n1 - i0);
-  {
-    float2 pf[PER];
+// (re, im) tiles of a complex product conj(x) w summed over rows: lane (m, q) supplies
+// x = X(row q of the K step, column m) and w = W(row q, column m).
+struct BgTile {
+  v4d re, im;
+};
+__device__ __forceinline__ void bg_fma(BgTile& t, double xr, double xi, double wr, double wi) {
+  t.re = mfma4d(xr, wr, t.re);
+  t.im = mfma4d(xr, wi, t.im);
+  t.re = mfma4d(xi, wi, t.re);
+  t.im = mfma4d(-xi, wr, t.im);
+}
+// Adds the tiles of the W wavefronts into wavefront 0's, in a fixed tree order through LDS
+// (buf: W / 2 x NT x 4 x 64 double2): the result does not depend on timing.
+template <int W, int NT>
+__device__ __forceinline__ void bg_reduce(BgTile (&t)[NT], double2* buf, int w, int lane) {
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int e = tid + 256 * u, s = e / (GXR + 1), h = e % (GXR + 1);
-      pf[u] = ld_or(xt, ((size_t)b * r + s) * n1 + i0 + h, s < r && i0 + h < n1, make_float2(0.f, 0.f));
+  for (int h = W / 2; h >= 1; h >>= 1) {
+    if (w >= h && w < 2 * h) {
+#pragma unroll
+      for (int k = 0; k < NT; ++k)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) buf[(((w - h) * NT + k) * 4 + e) * 64 + lane] = make_double2(t[k].re[e], t[k].im[e]);
     }
-#pragma unroll
-    for (int u = 0; u < PER; ++u) {
-      const int e = tid + 256 * u, s = e / (GXR + 1), h = e % (GXR + 1);
-      if (s < RM) {
-        xs[(2 * s) * LD + h] = pf[u].x;
-        xs[(2 * s + 1) * LD + h] = pf[u].y;
-      }
-    }
-  }
-  __syncthreads();
-  v4d acs[TPW], acd[TPW];
-#pragma unroll
-  for (int tu = 0; tu < TPW; ++tu) {
-    acs[tu] = v4d{0.0, 0.0, 0.0, 0.0};
-    acd[tu] = v4d{0.0, 0.0, 0.0, 0.0};
-    const int tile = KS > 1 ? 0 : w + 4 * tu;
-    const float* pa = xs + (16 * (tile / MT) + m) * LD;   // column 2 s + d of X'
-    const float* pb = xs + (16 * (tile % MT) + m) * LD;
-    for (int jb = kp; 16 * jb < nrows; jb += KS) {
-      const int h0 = 16 * jb + 4 * q;
-      const float4 a4 = *(const float4*)(pa + h0), b4 = *(const float4*)(pb + h0);
-      const double av[5] = {a4.x, a4.y, a4.z, a4.w, pa[h0 + 4]};
-      const double bv[5] = {b4.x, b4.y, b4.z, b4.w, pb[h0 + 4]};
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        const bool dif = i0 + h0 + jj + 1 < n1;   // the row pair (i, i + 1) exists
-        const double a1 = dif ? av[jj + 1] - av[jj] : 0.0, b1 = dif ? bv[jj + 1] - bv[jj] : 0.0;
-        acs[tu] = mfma4d(av[jj], bv[jj], acs[tu]);
-        acd[tu] = mfma4d(a1, b1, acd[tu]);
-      }
-    }
-  }
-  // element t of lane (q, m): real row 16 ta + q + 4 t, column 16 tb + m
-  cd* out = part + (size_t)(b * ngrp + g) * 2 * rr;
-#pragma unroll
-  for (int tu = 0; tu < TPW; ++tu) {
-    const int tile = KS > 1 ? 0 : w + 4 * tu, ta = tile / MT, tb = tile % MT;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-      const double s0 = acs[tu][t], s1 = __shfl_down(s0, 1), s16 = __shfl_down(s0, 16), s17 = __shfl_down(s0, 17);
-      const double d0 = acd[tu][t], d1 = __shfl_down(d0, 1), d16 = __shfl_down(d0, 16), d17 = __shfl_down(d0, 17);
-      const int sr = (16 * ta + q + 4 * t) >> 1, sc = (16 * tb + m) >> 1;
-      if (!(q & 1) && !(m & 1) && sr < r && sc < r) {
-        const cd vs = cd_make(s0 + s17, s1 - s16), vd = cd_make(d0 + d17, d1 - d16);
-        if (KS > 1) {
-          red[(2 * kp) * rr + sr * r + sc] = vs;
-          red[(2 * kp + 1) * rr + sr * r + sc] = vd;
-        } else {
-          out[sr * r + sc] = vs;
-          out[rr + sr * r + sc] = vd;
-        }
-      }
-    }
-  }
-  if constexpr (KS > 1) {
     __syncthreads();
-    for (int e = tid; e < 2 * rr; e += 256) {
-      const int which = e / rr, k = e % rr;
-      cd v = red[which * rr + k];
-      for (int j = 1; j < KS; ++j) v = cd_add(v, red[(2 * j + which) * rr + k]);   // fixed order
-      out[e] = v;
-    }
-  }
-}
-
-#define GXI_B 12   // row-group partials loaded at once
-__global__ void __launch_bounds__(256) k_gramx_inv(const cd* __restrict__ part, int ngrp, int r, GramOut go) {
-  // this small launch runs beside the X~^* W~ product on the same compute units: its
-  // wavefronts take issue priority there, since the Y-step waits for the later of the two
-  __builtin_amdgcn_s_setprio(3);
-  extern __shared__ __align__(16) unsigned char sm[];
-  const int b = blockIdx.x, tid = threadIdx.x, rr = r * r;
-  cd* gx = (cd*)sm;
-  cd* gp = gx + rr;
-  PinvScratch ps;
-  ps.work = gp + rr;
-  ps.vec = ps.work + rr;
-  ps.colk = ps.vec + rr;
-  ps.rowk = ps.colk + r;
-  ps.rot = (double*)(ps.rowk + r);
-  ps.red = ps.rot + 96;
-  for (int e = tid; e < rr; e += 256) {
-    cd sv = cd_make(0.0, 0.0), dv = cd_make(0.0, 0.0);
-    const cd* pb = part + (size_t)b * ngrp * 2 * rr + e;
-    for (int g0 = 0; g0 < ngrp; g0 += GXI_B) {   // GXI_B groups' loads in flight, summed in group order
-      cd vs[GXI_B], vd[GXI_B];
+    if (w < h) {
 #pragma unroll
-      for (int k = 0; k < GXI_B; ++k) {
-        const bool ok = g0 + k < ngrp;
-        vs[k] = ld_or(pb, (size_t)(g0 + k) * 2 * rr, ok, cd_make(0.0, 0.0));
-        vd[k] = ld_or(pb, (size_t)(g0 + k) * 2 * rr + rr, ok, cd_make(0.0, 0.0));
-      }
+      for (int k = 0; k < NT; ++k)
 #pragma unroll
-      for (int k = 0; k < GXI_B; ++k) {
-        if (g0 + k < ngrp) {
-          sv = cd_add(sv, vs[k]);
-          dv = cd_add(dv, vd[k]);
+        for (int e = 0; e < 4; ++e) {
+          const double2 o = buf[((w * NT + k) * 4 + e) * 64 + lane];
+          t[k].re[e] += o.x;
+          t[k].im[e] += o.y;
         }
-      }
     }
-    const cd gv = cd_add(sv, cd_scale(dv, go.rho1));
-    go.gxm[(size_t)b * rr + e] = gv;
-    go.dmat[(size_t)b * rr + e] = dv;
-    gx[e] = gv;
+    __syncthreads();
   }
-  __syncthreads();
-  const int fullr = pinv_herm(gx, gp, r, go.force_eigen, ps);
-  const bool qzero = fullr && go.eta == 1.0;
-  for (int e = tid; e < rr; e += 256) {
-    go.gxp[(size_t)b * rr + e] = gp[e];
-    if (!qzero) {   // q = I - eta G_X^+ G_X
-      const int s = e / r, t = e % r;
-      cd acc = cd_make(0.0, 0.0);
-      for (int u = 0; u < r; ++u) cd_fma(acc, gp[s * r + u], gx[u * r + t]);
-      go.qx[(size_t)b * rr + e] = cd_make((s == t ? 1.0 : 0.0) - go.eta * acc.re, -go.eta * acc.im);
-    }
-  }
-  if (tid == 0) go.qx_zero[b] = qzero ? 1 : 0;
 }
 
-int gramx_groups(int n1) { return (n1 + GXR - 1) / GXR; }
-
-// LDS the inversion launch asks for when the X~^* W~ product beside it leaves compute units
-// free: more than a compute unit (160 KB) holds next to one product block, so the inversions
-// run on the free units instead of sharing one with the product (FP64 arithmetic beside FP64
-// matrix-core work there ran 2.5 times slower)
-#define GXI_LDS_ALONE (150 * 1024)
-void gramx_set_attr(int r) {
-  (void)r;
-  (void)hipFuncSetAttribute((const void*)k_gramx_inv, hipFuncAttributeMaxDynamicSharedMemorySize, GXI_LDS_ALONE);
-}
-
-void launch_gramx(const Plan& p) {
-  GramOut go;
-  go.gxm = p.gxm;
-  go.dmat = p.dmat;
-  go.gxp = p.gxp;
-  go.qx = p.qx;
-  go.qx_zero = p.qx_zero;
-  go.rho1 = p.rho1;
-  go.eta = p.eta;
-  go.force_eigen = p.force_eigen;
-  const int ngrp = gramx_groups(p.n1);
-  const dim3 grid(ngrp, p.nb);
-  if (p.r <= 8) k_gramx_part<8><<<grid, 256, 0, p.stream>>>(p.xt, p.n1, p.r, ngrp, p.gxpart);
-  else if (p.r <= 16) k_gramx_part<16><<<grid, 256, 0, p.stream>>>(p.xt, p.n1, p.r, ngrp, p.gxpart);
-  else k_gramx_part<32><<<grid, 256, 0, p.stream>>>(p.xt, p.n1, p.r, ngrp, p.gxpart);
-  size_t lds = pinvy_lds_bytes(p.r);
-  if ((long)((p.n2 + p.bcg - 1) / p.bcg) * p.nb < p.ncu && lds < GXI_LDS_ALONE) lds = GXI_LDS_ALONE;
-  k_gramx_inv<<<p.nb, 256, lds, p.stream>>>(p.gxpart, ngrp, p.r, go);
-}
-
-// ---------------------------------------------------------------- X~^* W~
-// Real form with the real and imaginary parts in separate tiles: X''[p RM + s][i] =
-// (re, im)_p X~(i, s) and W''[i][p CW + c] = (re, im)_p W~(i, j0 + c), C = X''^T W'', so
-// (X~^* W~)(s, j0 + c) = (C[s][c] + C[RM + s][CW + c], C[s][CW + c] - C[RM + s][c]) and the
-// four terms of one output sit in the same lane and element of four tiles.  Each lane loads
-// X~(i, s) and W~(i, j) once per K step and feeds both parts to the FP64 matrix cores.
-// Block: one frequency b and CW = 16 WL complex columns, reduced over every row i in the
-// block: its BG_W wavefronts take contiguous ranges of 4-row K steps (XL = RM / 16 row
-// tiles and WL column tiles of each part), with two groups of loads in flight.  X~ and W~
-// are FP32 or BF16 values, exact in FP64, so the sums carry FP64 rounding only (the Y-step's
-// G_X^+ amplifies any rounding of X~^* W~).  The wavefronts' complex results are added in a
-// fixed tree order through LDS, so the result does not depend on timing.  Block order: the
-// column groups of one frequency run on one XCD (blocks are dealt to the eight XCDs in
-// turn), so each XCD's L2 holds the X~ rows of its own frequencies only.
-#define BG_W 8    // wavefronts per block
+// X~^* W~.  Block: one frequency b and CW = 16 WL complex columns, reduced over every row i in
+// the block: its W wavefronts take contiguous ranges of 4-row K steps, with two groups of
+// loads in flight; each lane loads X~(i, s) and W~(i, j) once per K step and feeds both parts
+// to the FP64 matrix cores.  X~ and W~ are FP32 or BF16 values, exact in FP64, so the sums
+// carry FP64 rounding only (the Y-step's G_X^+ amplifies any rounding of X~^* W~).
 template <int XL, int WL>
 struct BgShape {
   static constexpr int KG = 16 / (XL + WL);   // K steps per load group (two groups in flight)
@@ -897,46 +748,183 @@ __device__ __forceinline__ void bg_load(const void* __restrict__ wt, const float
     }
   }
 }
-
 template <int XL, int WL>
 __device__ __forceinline__ void bg_mfma(const float2 (&xv)[BgShape<XL, WL>::KG][XL],
-                                        const float2 (&wv)[BgShape<XL, WL>::KG][WL], int cnt,
-                                        v4d (&acc)[2 * XL][2 * WL]) {
+                                        const float2 (&wv)[BgShape<XL, WL>::KG][WL], int cnt, BgTile (&acc)[XL * WL]) {
   constexpr int KG = BgShape<XL, WL>::KG;
 #pragma unroll
   for (int k = 0; k < KG; ++k) {
     if (k < cnt) {   // the same in the whole wavefront
 #pragma unroll
-      for (int a = 0; a < 2 * XL; ++a) {
-        const double av = (double)(a < XL ? xv[k][a].x : xv[k][a - XL].y);
+      for (int a = 0; a < XL; ++a)
 #pragma unroll
-        for (int u = 0; u < 2 * WL; ++u) {
-          const double bv = (double)(u < WL ? wv[k][u].x : wv[k][u - WL].y);
-          acc[a][u] = mfma4d(av, bv, acc[a][u]);
-        }
-      }
+        for (int u = 0; u < WL; ++u) bg_fma(acc[a * WL + u], xv[k][a].x, xv[k][a].y, wv[k][u].x, wv[k][u].y);
     }
   }
 }
 
-template <int XL, int WL, bool MX>   // r <= 16 XL, 16 WL complex columns per block, MX: W~ in BF16
-__global__ void __launch_bounds__(64 * BG_W) __attribute__((amdgpu_waves_per_eu(XL + WL <= 2 ? 4 : 2))) k_bgemm(const void* __restrict__ wt, const float2* __restrict__ xt,
+// G_X of frequency b: S = X~^* X~ and D = (H X~)^*(H X~) over every row (H X~: differences of
+// neighbouring rows, exact in FP64; none past the last row), in 16 x 16 tiles (a, c), c >= a,
+// of the real part re_a re_c + im_a im_c and of M = re_a im_c (on the diagonal, where the
+// imaginary part is M - M^T) or M - im_a re_c (beside it); then G_X = S + rho1 D (= X~^* H_rho1
+// X~), its pseudo-inverse (Lemma SVPMPI, pinv_herm) and I - eta P_X, all by one block.  Lane
+// (m, q) holds the rows i, i + 1 and i + 2 (i = 2 q of a run of eight), which serve two K steps
+// and their differences.  What bounds it is a chain: at 529 rows and r = 16 about 5 us of FP64
+// matrix-core work on one compute unit, then 8 pivot steps; the product blocks of the same
+// launch take as long.  Launch at 529 x 96 x 112, r = 16: 19.6 us, product blocks alone 17.6;
+// before, the Gram in two launches on a graph branch beside the product: 7.3 + 11.5 us beside
+// 16.6, and 14 us for the branch's fork and join.  144 x 288 x 28, r = 8: 10.4 us (5.1 + 7.6
+// beside 6.6, and the fork and join, before).
+template <int XL, int W>
+__device__ __forceinline__ void gramx_block(const float2* __restrict__ xt, int b, int n1, int r, const GramOut& go,
+                                            unsigned char* sm) {
+  constexpr int NT = XL * (XL + 1) / 2, KG = XL == 1 ? 4 : 2;
+  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, w = tid >> 6, m = lane & 15, q = lane >> 4, rr = r * r;
+  const int nks = (n1 + 7) >> 3, per = (nks + W - 1) / W, ks0 = min(nks, w * per), ks1 = min(nks, ks0 + per);
+  BgTile gs[NT], gd[NT];
+#pragma unroll
+  for (int k = 0; k < NT; ++k) gs[k].re = gs[k].im = gd[k].re = gd[k].im = v4d{0.0, 0.0, 0.0, 0.0};
+  const float2* xb = xt + (size_t)b * r * n1;
+  float2 xa[KG][XL][3], xn[KG][XL][3];
+  auto load = [&](int ks, float2 (&x)[KG][XL][3]) {
+#pragma unroll
+    for (int k = 0; k < KG; ++k) {
+      const int i = 8 * min(ks + k, max(ks1 - 1, 0)) + 2 * q;
+#pragma unroll
+      for (int a = 0; a < XL; ++a)
+#pragma unroll
+        for (int h = 0; h < 3; ++h) x[k][a][h] = xb[(uint32_t)(min(16 * a + m, r - 1) * n1 + min(i + h, n1 - 1))];
+    }
+  };
+  auto prod = [&](int ks, const float2 (&x)[KG][XL][3]) {
+#pragma unroll
+    for (int k = 0; k < KG; ++k) {
+      if (ks + k < ks1) {   // the same in the whole wavefront
+        const int i = 8 * (ks + k) + 2 * q;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          double xr[XL], xi[XL], dr[XL], di[XL];
+#pragma unroll
+          for (int a = 0; a < XL; ++a) {
+            const bool ok = i + h < n1 && 16 * a + m < r;   // past the last row its copies meet: no difference
+            xr[a] = ok ? x[k][a][h].x : 0.0f;
+            xi[a] = ok ? x[k][a][h].y : 0.0f;
+            dr[a] = ok ? (double)x[k][a][h + 1].x - (double)x[k][a][h].x : 0.0;
+            di[a] = ok ? (double)x[k][a][h + 1].y - (double)x[k][a][h].y : 0.0;
+          }
+          int t = 0;
+#pragma unroll
+          for (int a = 0; a < XL; ++a)
+#pragma unroll
+            for (int c = a; c < XL; ++c, ++t) {
+              gs[t].re = mfma4d(xr[a], xr[c], gs[t].re);
+              gd[t].re = mfma4d(dr[a], dr[c], gd[t].re);
+              gs[t].im = mfma4d(xr[a], xi[c], gs[t].im);
+              gd[t].im = mfma4d(dr[a], di[c], gd[t].im);
+              gs[t].re = mfma4d(xi[a], xi[c], gs[t].re);
+              gd[t].re = mfma4d(di[a], di[c], gd[t].re);
+              if (c > a) {
+                gs[t].im = mfma4d(-xi[a], xr[c], gs[t].im);
+                gd[t].im = mfma4d(-di[a], dr[c], gd[t].im);
+              }
+            }
+        }
+      }
+    }
+  };
+  load(ks0, xa);
+  for (int ks = ks0; ks < ks1; ks += 2 * KG) {
+    load(ks + KG, xn);   // clamped: past the wavefront's rows nothing new is read
+    prod(ks, xa);
+    if (ks + KG >= ks1) break;
+    load(ks + 2 * KG, xa);
+    prod(ks + KG, xn);
+  }
+  bg_reduce<W>(gs, (double2*)sm, w, lane);
+  bg_reduce<W>(gd, (double2*)sm, w, lane);
+  // (the reductions end with a barrier: their LDS is free again)
+  cd* gx = (cd*)sm;
+  cd* gp = gx + rr;
+  PinvScratch ps;
+  ps.work = gp + rr;
+  ps.vec = ps.work + rr;
+  ps.rot = (double*)(ps.vec + rr);
+  ps.red = ps.rot + 96;
+  cd* dx = gp;   // D and G_X by way of LDS: the diagonal tiles' imaginary parts need M^T
+  if (w == 0) {
+    int t = 0;
+#pragma unroll
+    for (int a = 0; a < XL; ++a)
+#pragma unroll
+      for (int c = a; c < XL; ++c, ++t) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          // element e of lane (q, m): row q + 4 e, column m of the tile
+          const int s = 16 * a + q + 4 * e, u = 16 * c + m;
+          if (s < r && u < r) {
+            const cd d = cd_make(gd[t].re[e], gd[t].im[e]);
+            const cd v = cd_add(cd_make(gs[t].re[e], gs[t].im[e]), cd_scale(d, go.rho1));
+            ps.work[s * r + u] = v;
+            dx[s * r + u] = d;
+            if (c > a) {
+              ps.work[u * r + s] = cd_conj(v);
+              dx[u * r + s] = cd_conj(d);
+            }
+          }
+        }
+      }
+  }
+  __syncthreads();
+  for (int e = tid; e < rr; e += nt) {
+    const int s = e / r, u = e - s * r;
+    cd v = ps.work[e], d = dx[e];
+    if (XL == 1 || (s >> 4) == (u >> 4)) {
+      v.im -= ps.work[u * r + s].im;
+      d.im -= dx[u * r + s].im;
+    }
+    gx[e] = v;
+    go.gxm[(size_t)b * rr + e] = v;
+    go.dmat[(size_t)b * rr + e] = d;
+  }
+  __syncthreads();
+  const int fullr = pinv_herm(gx, gp, r, go.force_eigen, ps);
+  const bool qzero = fullr && go.eta == 1.0;
+  for (int e = tid; e < rr; e += nt) {
+    go.gxp[(size_t)b * rr + e] = gp[e];
+    if (!qzero) {   // q = I - eta G_X^+ G_X
+      const int s = e / r, t = e % r;
+      cd acc = cd_make(0.0, 0.0);
+      for (int u = 0; u < r; ++u) cd_fma(acc, gp[s * r + u], gx[u * r + t]);
+      go.qx[(size_t)b * rr + e] = cd_make((s == t ? 1.0 : 0.0) - go.eta * acc.re, -go.eta * acc.im);
+    }
+  }
+  if (tid == 0) go.qx_zero[b] = qzero ? 1 : 0;
+}
+
+// Blocks 0 .. nb - 1: G_X of frequency blockIdx.x (the longest chain, so they start first);
+// the others: the product.  Block order of the product: the column groups of one frequency run
+// on one XCD (blocks are dealt to the eight XCDs in turn), so each XCD's L2 holds the X~ rows of
+// its own frequencies only.
+template <int XL, int WL, bool MX, int W>   // r <= 16 XL, 16 WL complex columns and W wavefronts per block, MX: W~ in BF16
+__global__ void __launch_bounds__(64 * W) k_bgemm(const void* __restrict__ wt, const float2* __restrict__ xt,
                                                       double2* __restrict__ bout, int n1, int n2, int r, int nb,
-                                                      int ncg) {
+                                                      int ncg, GramOut go) {
   constexpr int KG = BgShape<XL, WL>::KG;
-  extern __shared__ __align__(16) double2 bred[];   // [BG_W / 2][XL][WL][4][64]
+  extern __shared__ __align__(16) unsigned char bsm[];
+  if ((int)blockIdx.x < nb) {
+    gramx_block<XL, W>(xt, (int)blockIdx.x, n1, r, go, bsm);
+    return;
+  }
   // XCD-aware order: block id -> (frequency, column group)
-  const int nblk = (int)gridDim.x, id = (int)blockIdx.x, x = id & 7, qd = nblk >> 3, rem = nblk & 7;
+  const int nblk = (int)gridDim.x - nb, id = (int)blockIdx.x - nb, x = id & 7, qd = nblk >> 3, rem = nblk & 7;
   const int lid = x * qd + min(x, rem) + (id >> 3);
   const int b = lid / ncg, cg = lid % ncg, j0 = 16 * WL * cg;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, m = lane & 15, q = lane >> 4;
-  const int nks = (n1 + 3) >> 2, per = (nks + BG_W - 1) / BG_W;
+  const int nks = (n1 + 3) >> 2, per = (nks + W - 1) / W;
   const int ks0 = min(nks, w * per), ks1 = min(nks, ks0 + per);
-  v4d acc[2 * XL][2 * WL];
+  BgTile acc[XL * WL];
 #pragma unroll
-  for (int a = 0; a < 2 * XL; ++a)
-#pragma unroll
-    for (int u = 0; u < 2 * WL; ++u) acc[a][u] = v4d{0.0, 0.0, 0.0, 0.0};
+  for (int k = 0; k < XL * WL; ++k) acc[k].re = acc[k].im = v4d{0.0, 0.0, 0.0, 0.0};
   float2 xa[KG][XL], wa[KG][WL], xb[KG][XL], wb[KG][WL];
   bg_load<XL, WL, MX>(wt, xt, ks0, ks1, q, m, b, r, n1, n2, nb, j0, xa, wa);
   for (int ks = ks0; ks < ks1; ks += 2 * KG) {
@@ -946,42 +934,7 @@ __global__ void __launch_bounds__(64 * BG_W) __attribute__((amdgpu_waves_per_eu(
     if (ks + 2 * KG < ks1) bg_load<XL, WL, MX>(wt, xt, ks + 2 * KG, ks1, q, m, b, r, n1, n2, nb, j0, xa, wa);
     bg_mfma<XL, WL>(xb, wb, ks1 - ks - KG, acc);
   }
-  // complex results of this wavefront: element t of lane (q, m) is row q + 4 t, column m of
-  // each tile, i.e. s = 16 a + q + 4 t, j = j0 + 16 u + m
-  double2 cz[XL][WL][4];
-#pragma unroll
-  for (int a = 0; a < XL; ++a)
-#pragma unroll
-    for (int u = 0; u < WL; ++u)
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        cz[a][u][t] = make_double2(acc[a][u][t] + acc[XL + a][WL + u][t], acc[a][WL + u][t] - acc[XL + a][u][t]);
-  // fixed-order tree over the wavefronts: w += w + h for h = BG_W / 2, ..., 1
-#pragma unroll
-  for (int h = BG_W / 2; h >= 1; h >>= 1) {
-    if (w >= h && w < 2 * h) {
-#pragma unroll
-      for (int a = 0; a < XL; ++a)
-#pragma unroll
-        for (int u = 0; u < WL; ++u)
-#pragma unroll
-          for (int t = 0; t < 4; ++t) bred[((((w - h) * XL + a) * WL + u) * 4 + t) * 64 + lane] = cz[a][u][t];
-    }
-    __syncthreads();
-    if (w < h) {
-#pragma unroll
-      for (int a = 0; a < XL; ++a)
-#pragma unroll
-        for (int u = 0; u < WL; ++u)
-#pragma unroll
-          for (int t = 0; t < 4; ++t) {
-            const double2 o = bred[(((w * XL + a) * WL + u) * 4 + t) * 64 + lane];
-            cz[a][u][t].x += o.x;
-            cz[a][u][t].y += o.y;
-          }
-    }
-    __syncthreads();
-  }
+  bg_reduce<W>(acc, (double2*)bsm, w, lane);
   if (w != 0) return;
 #pragma unroll
   for (int a = 0; a < XL; ++a)
@@ -990,38 +943,49 @@ __global__ void __launch_bounds__(64 * BG_W) __attribute__((amdgpu_waves_per_eu(
 #pragma unroll
       for (int t = 0; t < 4; ++t) {
         const int s = 16 * a + q + 4 * t, j = j0 + 16 * u + m;
-        if (s < r && j < n2) bout[((size_t)b * r + s) * n2 + j] = cz[a][u][t];
+        if (s < r && j < n2) bout[((size_t)b * r + s) * n2 + j] = make_double2(acc[a * WL + u].re[t], acc[a * WL + u].im[t]);
       }
 }
 
-size_t bgemm_lds_bytes(int r, int bcg) {
-  const int xl = r <= 16 ? 1 : 2, wl = bcg / 16;
-  return (size_t)(BG_W / 2) * xl * wl * 4 * 64 * sizeof(double2);
+// Wavefronts per block: 8, or 2 where there are many frequencies of few rows (12 x 12 x 8064:
+// 139 us with 8, 36 with 2).
+static int bgemm_waves(const Plan& p) { return p.n1 <= 64 && p.nb >= 256 ? 2 : 8; }
+
+static size_t bgemm_lds_bytes(int r, int bcg, int waves) {
+  const int xl = r <= 16 ? 1 : 2, tiles = xl * (bcg / 16), gtiles = xl * (xl + 1) / 2;
+  const size_t red = (size_t)(waves / 2) * (tiles > gtiles ? tiles : gtiles) * 4 * 64 * sizeof(double2);
+  return red > pinv_lds_bytes(r) ? red : pinv_lds_bytes(r);
 }
 
 bool bgemm_cols_valid(int r, int bcg) { return (bcg == 16 || bcg == 32) && r <= 32; }
 
-void bgemm_set_attr() {}   // at most 64 KB of LDS per block
+typedef void (*BgemmKernel)(const void*, const float2*, double2*, int, int, int, int, int, GramOut);
+template <int XL, int W>
+static BgemmKernel bgemm_kernel(int bcg, int mixed) {
+  if (bcg == 32) return mixed ? k_bgemm<XL, 2, true, W> : k_bgemm<XL, 2, false, W>;
+  return mixed ? k_bgemm<XL, 1, true, W> : k_bgemm<XL, 1, false, W>;
+}
+template <int XL>
+static BgemmKernel bgemm_kernel_of(int bcg, int mixed, int waves) {
+  return waves == 2 ? bgemm_kernel<XL, 2>(bcg, mixed) : bgemm_kernel<XL, 8>(bcg, mixed);
+}
 
-// X~^* W~ -> bpart [nb][r][n2] (G_X: launch_gramx).
+// X~^* W~ -> bpart [nb][r][n2]; G_X, (H X~)^*(H X~), G_X^+ and I - eta P_X.
 void launch_bgemm(const Plan& p) {
-  const int ncg = (p.n2 + p.bcg - 1) / p.bcg;
-  const int grid = ncg * p.nb;
-  const size_t lds = bgemm_lds_bytes(p.r, p.bcg);
-#define TCTF_BGEMM(XL, WL)                                                                                       \
-  do {                                                                                                           \
-    if (p.mixed) k_bgemm<XL, WL, true><<<grid, 64 * BG_W, lds, p.stream>>>(p.wt, p.xt, p.bpart, p.n1, p.n2, p.r, p.nb, ncg);  \
-    else k_bgemm<XL, WL, false><<<grid, 64 * BG_W, lds, p.stream>>>(p.wt, p.xt, p.bpart, p.n1, p.n2, p.r, p.nb, ncg); \
-  } while (0)
-  const bool wide = p.bcg == 32;
-  if (p.r <= 16) {
-    if (wide) TCTF_BGEMM(1, 2);
-    else TCTF_BGEMM(1, 1);
-  } else {
-    if (wide) TCTF_BGEMM(2, 2);
-    else TCTF_BGEMM(2, 1);
-  }
-#undef TCTF_BGEMM
+  GramOut go;
+  go.gxm = p.gxm;
+  go.dmat = p.dmat;
+  go.gxp = p.gxp;
+  go.qx = p.qx;
+  go.qx_zero = p.qx_zero;
+  go.rho1 = p.rho1;
+  go.eta = p.eta;
+  go.force_eigen = p.force_eigen;
+  const int ncg = (p.n2 + p.bcg - 1) / p.bcg, waves = bgemm_waves(p);
+  const size_t lds = bgemm_lds_bytes(p.r, p.bcg, waves);
+  const BgemmKernel kernel = p.r <= 16 ? bgemm_kernel_of<1>(p.bcg, p.mixed, waves) : bgemm_kernel_of<2>(p.bcg, p.mixed, waves);
+  if (lds > 65536) (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  kernel<<<p.nb + ncg * p.nb, 64 * waves, lds, p.stream>>>(p.wt, p.xt, p.bpart, p.n1, p.n2, p.r, p.nb, ncg, go);
 }
 
 }  // namespace tctf

@@ -36,9 +36,7 @@ __global__ void __launch_bounds__(256) k_rank_svd(const float2* __restrict__ xt,
   PinvScratch ps;
   ps.work = Qv + rr;
   ps.vec = ps.work + rr;
-  ps.colk = ps.vec + rr;
-  ps.rowk = ps.colk + r;
-  ps.rot = (double*)(ps.rowk + r);
+  ps.rot = (double*)(ps.vec + rr);
   ps.red = ps.rot + 96;
   int* order = (int*)(ps.red + 48);
   const float2* X = xt + (size_t)b * r * n1;

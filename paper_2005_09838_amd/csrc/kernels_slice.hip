@@ -80,7 +80,7 @@ static int slice_threads(const Plan& p) {
 
 size_t slice_launch_lds_bytes(const Plan& p) {
   if (p.spath == SPATH_SPLIT) return 0;
-  const size_t a = slice_lds_bytes(p.n2, p.n3), b = pinvy_lds_bytes(p.r);
+  const size_t a = slice_lds_bytes(p.n2, p.n3), b = pinv_lds_bytes(p.r);
   return a > b ? a : b;
 }
 

@@ -203,8 +203,8 @@ void ystep_split(int n2, int r, int nb, int* ny, int* cw) {
   *ny = (n2 + c - 1) / c;
 }
 
-// Block (column block jb, frequency b), 256 threads, r <= RM; G_X^+ and I - eta P_X come
-// from the G_X launch (k_gramx_inv), X~^* W~ from k_bgemm.  Every load of the block is
+// Block (column block jb, frequency b), 256 threads, r <= RM; G_X^+, I - eta P_X
+// and X~^* W~ come from the launch before (k_bgemm).  Every load of the block is
 // issued before any use: G_X^+ and q, the old columns and X~^* W~ on the block's columns.
 // Then Y~ <- (I - eta P_X) Y~ + eta G_X^+ X~^* W~ (eq. (updataXYW1)) is formed on the
 // block's columns in FP64 and stored in FP32, and the block's FP64 partial of G_Y = Y~ Y~^*
@@ -307,13 +307,13 @@ __global__ void __launch_bounds__(256) k_pinvy(PinvyArgs pa) {
 }
 
 void pinvy_set_attr(int r) {
-  if (pinvy_lds_bytes(r) > 65536)
+  if (pinv_lds_bytes(r) > 65536)
     (void)hipFuncSetAttribute((const void*)k_pinvy, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)pinvy_lds_bytes(r));
+                              (int)pinv_lds_bytes(r));
 }
 
 void launch_pinvy(const Plan& p, hipStream_t stream) {
-  k_pinvy<<<p.nb, 256, pinvy_lds_bytes(p.r), stream>>>(pinvy_args(p));
+  k_pinvy<<<p.nb, 256, pinv_lds_bytes(p.r), stream>>>(pinvy_args(p));
 }
 
 size_t ystep_lds_bytes(int r, int cw) { return ystep_layout(r, cw).total; }

@@ -4,9 +4,7 @@
 //
 // Rule: eigenvalues lambda_i <= tau = r * eps64 * lambda_max are dropped (a zero matrix
 // gives 0).  Fast path: Gauss-Jordan elimination (the sweep operator, no pivoting, valid
-// for positive-definite input); for r <= 16 the first wavefront runs it alone with the
-// matrix in registers, for larger r the block runs it in LDS.  Its result
-// is accepted only if it proves that every eigenvalue exceeds 8 tau:
+// for positive-definite input) in LDS, pinv_sweep.  Its result is accepted only if it proves that every eigenvalue exceeds 8 tau:
 // lambda_min >= 1/||A^-1||_F > 8 r eps ||A||_F >= 8 tau.  Then the rule keeps every
 // eigenvalue and A^+ = A^-1.  Otherwise (or when forced) a cyclic Jacobi
 // eigen-decomposition with parallel (round-robin) pair ordering is used by the whole block
@@ -20,119 +18,78 @@
 struct PinvScratch {
   cd* work;    // r*r
   cd* vec;     // r*r
-  cd* colk;    // r
-  cd* rowk;    // r
   double* rot; // 6 * 16 doubles (rotation parameters of one round)
-  double* red; // >= 16 doubles
+  double* red; // >= 48 doubles
 };
 
-// Wavefront-level fast path for r <= 16 (called by the 64 lanes of one wavefront).  The
-// matrix, padded with the identity to 16 x 16, lives in registers: lane l holds row
-// l / 4, columns 4 (l % 4) .. 4 (l % 4) + 3.  Pivot row, pivot column and pivot reach the
-// lanes by cross-lane shuffles.
-// Returns 1: accepted, P = A^-1;  2: A is not finite, P = NaN;  3: A has no positive
-// diagonal entry (the zero PSD matrix), P = 0;  0: rejected, P untouched.
-__device__ inline int pinv_gj_wave16(const cd* A, cd* P, int r) {
-  const int lane = threadIdx.x & 63, p = lane >> 2, q0 = (lane & 3) * 4, rr = r * r;
-  double vr[4], vi[4];
-  double f2 = 0.0, dmax = -1.0;
+// Fast path: the sweep operator on the 2 x 2 pivot blocks K = {k, k + 1} (a last 1 x 1 block at
+// odd r), every thread of the block on its own entries:
+//   A_KK -> -E, A_Kj -> E A_Kj, A_iK -> A_iK E, A_ij -> A_ij - A_iK E A_Kj,  E = A_KK^-1;
+// sweeping every index gives -A^-1.  Each step reads one LDS copy and writes another, so it
+// costs one barrier, and every thread forms E for itself: about 0.6 us a step at r <= 16 (r = 16
+// with its Gram read and results written 8.5 us; one wavefront with the matrix in registers,
+// passing pivots by cross-lane moves, 10.1; r = 24 19.4 us, 33 with two barriers and 1 x 1
+// pivots).  Returns 1 when every pivot was positive; then *out holds -A^-1 (one of w0, w1).
+template <int PER>   // entries of a thread in flight
+__device__ __forceinline__ int pinv_sweep(const cd* A, cd* w0, cd* w1, int r, const cd** out) {
+  const int tid = threadIdx.x, nt = blockDim.x, rr = r * r;
+  const int p0 = tid / r, q0 = tid - p0 * r, dp = nt / r, dq = nt - dp * r;
+  const cd* src = A;
+  cd* dst = w0;
+  int ok = 1;
+  for (int k = 0; k < r; k += 2) {
+    const bool two = k + 1 < r;
+    const int k1 = two ? k + 1 : k;
+    const cd pa = src[k * r + k], pb = src[k * r + k1], pd = src[k1 * r + k1];
+    int p = p0, q = q0;
+    for (int e0 = tid; e0 < rr; e0 += PER * nt) {
+      // every LDS read of the batch is issued before any use
+      cd c0[PER], c1[PER], u0[PER], u1[PER], v[PER];
+      int ph[PER], qh[PER];
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int q = q0 + i;
-    if (p < r && q < r) {
-      const cd a = A[p * r + q];
-      vr[i] = a.re;
-      vi[i] = a.im;
-      f2 += a.re * a.re + a.im * a.im;
-      if (p == q) dmax = fmax(dmax, a.re);
-    } else {
-      vr[i] = (p == q) ? 1.0 : 0.0;
-      vi[i] = 0.0;
+      for (int h = 0; h < PER; ++h) {
+        const bool in = e0 + h * nt < rr;
+        ph[h] = in ? p : 0;
+        qh[h] = in ? q : 0;
+        p += dp;
+        q += dq;
+        if (q >= r) {
+          q -= r;
+          ++p;
+        }
+        c0[h] = src[ph[h] * r + k];
+        c1[h] = src[ph[h] * r + k1];
+        u0[h] = src[k * r + qh[h]];
+        u1[h] = src[k1 * r + qh[h]];
+        v[h] = src[ph[h] * r + qh[h]];
+      }
+      const double det = two ? pa.re * pd.re - (pb.re * pb.re + pb.im * pb.im) : pa.re;
+      const double idet = 1.0 / det, e00 = two ? pd.re * idet : idet, e11 = two ? pa.re * idet : 0.0;
+      const cd e01 = cd_make(two ? -pb.re * idet : 0.0, two ? -pb.im * idet : 0.0), e10 = cd_conj(e01);
+#pragma unroll
+      for (int h = 0; h < PER; ++h) {
+        const bool row0 = ph[h] == k, row1 = ph[h] == k1, col0 = qh[h] == k, col1 = qh[h] == k1;
+        // (R0, R1): A_pK E, or in a pivot row minus that row of E
+        cd r0 = cd_add(cd_scale(c0[h], e00), cd_mul(c1[h], e10)), r1 = cd_add(cd_mul(c0[h], e01), cd_scale(c1[h], e11));
+        r0.re = row0 ? -e00 : (row1 ? -e10.re : r0.re);
+        r0.im = row0 ? 0.0 : (row1 ? -e10.im : r0.im);
+        r1.re = row0 ? -e01.re : (row1 ? -e11 : r1.re);
+        r1.im = row0 ? -e01.im : (row1 ? 0.0 : r1.im);
+        cd o = row0 || row1 ? cd_make(0.0, 0.0) : v[h];
+        o = cd_sub(cd_sub(o, cd_mul(r0, u0[h])), cd_mul(r1, u1[h]));
+        o.re = col0 ? r0.re : (col1 ? r1.re : o.re);
+        o.im = col0 ? r0.im : (col1 ? r1.im : o.im);
+        if (e0 + h * nt < rr) dst[e0 + h * nt] = o;
+      }
     }
+    // the same in every thread
+    ok &= pa.re > 0.0 && (two ? pa.re * pd.re - (pb.re * pb.re + pb.im * pb.im) : pa.re) > 0.0;
+    __syncthreads();
+    src = dst;
+    dst = dst == w0 ? w1 : w0;
   }
-  for (int off = 32; off > 0; off >>= 1) {
-    f2 += __shfl_xor(f2, off);
-    dmax = fmax(dmax, __shfl_xor(dmax, off));
-  }
-  if (!isfinite(f2)) {
-    for (int e = lane; e < rr; e += 64) P[e] = cd_make(NAN, NAN);
-    return 2;
-  }
-  if (!(dmax > 0.0)) {
-    for (int e = lane; e < rr; e += 64) P[e] = cd_make(0.0, 0.0);
-    return 3;
-  }
-  // Sweeps on the 2 x 2 pivot blocks K = {k0, k0 + 1} (an odd r ends with a block that
-  // holds one padding index; sweeping it leaves the leading r x r block unchanged):
-  // A_KK -> -A_KK^-1, A_iK -> A_iK A_KK^-1, A_Kj -> A_KK^-1 A_Kj,
-  // A_ij -> A_ij - A_iK A_KK^-1 A_Kj.  Sweeping every index yields -A^-1.
-  bool ok = true;
-  const int pin = p & 1;                     // this lane's row offset within a pivot block
-  for (int k0 = 0; k0 < r; k0 += 2) {
-    const int g = k0 >> 2, sl = k0 & 3;      // column group and slot of the pivot columns
-    // pivot rows k0, k0 + 1 at this lane's columns
-    double w0r[4], w0i[4], w1r[4], w1i[4];
-    const int src0 = 4 * k0 + (lane & 3), src1 = src0 + 4;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      w0r[i] = __shfl(vr[i], src0);
-      w0i[i] = __shfl(vi[i], src0);
-      w1r[i] = __shfl(vr[i], src1);
-      w1i[i] = __shfl(vi[i], src1);
-    }
-    // pivot columns k0, k0 + 1 of this lane's row (both in lane 4 p + g, slots sl, sl + 1)
-    const double o0r = sl == 0 ? vr[0] : vr[2], o0i = sl == 0 ? vi[0] : vi[2];
-    const double o1r = sl == 0 ? vr[1] : vr[3], o1i = sl == 0 ? vi[1] : vi[3];
-    const int srcc = 4 * p + g;
-    const double c0r = __shfl(o0r, srcc), c0i = __shfl(o0i, srcc);
-    const double c1r = __shfl(o1r, srcc), c1i = __shfl(o1i, srcc);
-    // the pivot block [[pa, pb], [conj(pb), pd]] from rows k0 and k0 + 1
-    const int sp0 = 4 * k0 + g, sp1 = sp0 + 4;
-    const double pa = __shfl(o0r, sp0), pbr = __shfl(o1r, sp0), pbi = __shfl(o1i, sp0);
-    const double pd = __shfl(o1r, sp1);
-    const double det = pa * pd - (pbr * pbr + pbi * pbi);
-    ok = ok && pa > 0.0 && det > 0.0;        // the same in every lane
-    const double idet = det > 0.0 ? 1.0 / det : 0.0;
-    // A_KK^-1 = [[e00, e01], [e10, e11]]
-    const double e00 = pd * idet, e11 = pa * idet;
-    const double e01r = -pbr * idet, e01i = -pbi * idet;   // -pb / det
-    const double e10r = -pbr * idet, e10i = pbi * idet;    // -conj(pb) / det
-    // (R0, R1) = A_pK A_KK^-1 for this lane's row
-    const double r0r = c0r * e00 + (c1r * e10r - c1i * e10i), r0i = c0i * e00 + (c1r * e10i + c1i * e10r);
-    const double r1r = (c0r * e01r - c0i * e01i) + c1r * e11, r1i = (c0r * e01i + c0i * e01r) + c1i * e11;
-    const bool inrow = (p >> 1) == (k0 >> 1);   // p is k0 or k0 + 1
-    // this lane's pivot-block row of A_KK^-1: (f0, f1) = row (p - k0)
-    const double f0r = pin ? e10r : e00, f0i = pin ? e10i : 0.0;
-    const double f1r = pin ? e11 : e01r, f1i = pin ? 0.0 : e01i;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int q = q0 + i;
-      const bool incol = (q >> 1) == (k0 >> 1);
-      const int qin = q & 1;
-      // general entry: v - R0 w0 - R1 w1
-      const double gr = vr[i] - (r0r * w0r[i] - r0i * w0i[i]) - (r1r * w1r[i] - r1i * w1i[i]);
-      const double gi = vi[i] - (r0r * w0i[i] + r0i * w0r[i]) - (r1r * w1i[i] + r1i * w1r[i]);
-      // pivot rows: f0 w0 + f1 w1
-      const double hr = (f0r * w0r[i] - f0i * w0i[i]) + (f1r * w1r[i] - f1i * w1i[i]);
-      const double hi = (f0r * w0i[i] + f0i * w0r[i]) + (f1r * w1i[i] + f1i * w1r[i]);
-      // pivot columns: R_qin; pivot block: -(A_KK^-1)_(p - k0, q - k0) = -f_qin
-      const double cr = qin ? r1r : r0r, ci = qin ? r1i : r0i;
-      const double br = qin ? -f1r : -f0r, bi = qin ? -f1i : -f0i;
-      vr[i] = inrow ? (incol ? br : hr) : (incol ? cr : gr);
-      vi[i] = inrow ? (incol ? bi : hi) : (incol ? ci : gi);
-    }
-  }
-  if (!ok) return 0;
-  double g2 = 0.0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (p < r && q0 + i < r) g2 += vr[i] * vr[i] + vi[i] * vi[i];
-  for (int off = 32; off > 0; off >>= 1) g2 += __shfl_xor(g2, off);
-  if (!(isfinite(g2) && 8.0 * r * TCTF_EPS64 * sqrt(f2) * sqrt(g2) < 1.0)) return 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    if (p < r && q0 + i < r) P[p * r + q0 + i] = cd_make(-vr[i], -vi[i]);
-  return 1;
+  *out = src;
+  return ok;
 }
 
 // Cyclic Jacobi eigen-decomposition of a Hermitian r x r matrix A by the whole block, with
@@ -214,16 +171,29 @@ __device__ inline void jacobi_herm(const cd* A, int r, double fro, PinvScratch s
 // Returns 1 (to every thread) if all eigenvalues were kept, 0 otherwise.
 __device__ inline int pinv_herm(const cd* A, cd* P, int r, int force_eigen, PinvScratch s) {
   const int tid = threadIdx.x, nt = blockDim.x, rr = r * r;
-  if (!force_eigen && r <= 16) {
-    if (tid < 64) {
-      const int f = pinv_gj_wave16(A, P, r);
-      if (tid == 0) s.rot[0] = (double)f;
+  if (!force_eigen) {
+    const cd* swept;
+    // a matrix that is not finite, zero or indefinite has no positive pivot somewhere: not ok
+    const int ok = rr <= nt ? pinv_sweep<1>(A, s.work, s.vec, r, &swept) : pinv_sweep<2>(A, s.work, s.vec, r, &swept);
+    if (ok) {
+      // the norms, by every wavefront for itself: no barrier
+      double f2 = 0.0, g2 = 0.0;
+      for (int e = tid & 63; e < rr; e += 64) {
+        const cd a = A[e], v = swept[e];
+        f2 += a.re * a.re + a.im * a.im;
+        g2 += v.re * v.re + v.im * v.im;
+      }
+      for (int off = 32; off > 0; off >>= 1) {
+        f2 += __shfl_xor(f2, off);
+        g2 += __shfl_xor(g2, off);
+      }
+      if (isfinite(g2) && isfinite(f2) && 8.0 * r * TCTF_EPS64 * sqrt(f2) * sqrt(g2) < 1.0) {
+        for (int e = tid; e < rr; e += nt) P[e] = cd_make(-swept[e].re, -swept[e].im);
+        __syncthreads();
+        return 1;
+      }
     }
-    __syncthreads();
-    const int f = (int)s.rot[0];
-    __syncthreads();
-    if (f == 1) return 1;
-    if (f == 2 || f == 3) return 0;
+    __syncthreads();   // the other paths write over the copies
   }
   double f2 = 0.0, dmax = -1.0;
   for (int e = tid; e < rr; e += nt) {
@@ -244,39 +214,6 @@ __device__ inline int pinv_herm(const cd* A, cd* P, int r, int force_eigen, Pinv
     return 0;
   }
   const double fro = sqrt(f2);
-
-  if (!force_eigen && r > 16) {   // block-level Gauss-Jordan for the larger ranks
-    for (int e = tid; e < rr; e += nt) s.work[e] = A[e];
-    __syncthreads();
-    bool ok = true;
-    for (int k = 0; k < r; ++k) {
-      const double piv = s.work[k * r + k].re;
-      if (!(piv > 0.0)) { ok = false; break; }            // uniform across the block
-      for (int e = tid; e < r; e += nt) { s.colk[e] = s.work[e * r + k]; s.rowk[e] = s.work[k * r + e]; }
-      __syncthreads();
-      const double ip = 1.0 / piv;
-      for (int e = tid; e < rr; e += nt) {
-        const int p = e / r, q = e % r;
-        cd v;
-        if (p == k && q == k) v = cd_make(-ip, 0.0);
-        else if (p == k) v = cd_scale(s.rowk[q], ip);
-        else if (q == k) v = cd_scale(s.colk[p], ip);
-        else v = cd_sub(s.work[e], cd_scale(cd_mul(s.colk[p], s.rowk[q]), ip));
-        s.work[e] = v;
-      }
-      __syncthreads();
-    }
-    if (ok) {
-      double g2 = 0.0;
-      for (int e = tid; e < rr; e += nt) g2 += s.work[e].re * s.work[e].re + s.work[e].im * s.work[e].im;
-      g2 = block_sum_d(g2, s.red);
-      if (isfinite(g2) && 8.0 * r * TCTF_EPS64 * fro * sqrt(g2) < 1.0) {
-        for (int e = tid; e < rr; e += nt) P[e] = cd_make(-s.work[e].re, -s.work[e].im);
-        __syncthreads();
-        return 1;
-      }
-    }
-  }
 
   // Jacobi eigen-decomposition of A into work (eigenvalues on the diagonal) and vec.
   jacobi_herm(A, r, fro, s);
@@ -299,9 +236,9 @@ __device__ inline int pinv_herm(const cd* A, cd* P, int r, int force_eigen, Pinv
   return kept == r ? 1 : 0;
 }
 
-// Bytes of LDS pinvy_block needs at rank r.
-__host__ __device__ inline size_t pinvy_lds_bytes(int r) {
-  return (size_t)(4 * r * r + 2 * r) * sizeof(cd) + 144 * sizeof(double);
+// Bytes of LDS of a Gram, its pseudo-inverse and the scratch at rank r.
+__host__ __device__ inline size_t pinv_lds_bytes(int r) {
+  return (size_t)(4 * r * r) * sizeof(cd) + 144 * sizeof(double);
 }
 
 // Inputs and outputs of pinvy_block ([nb][r][r] FP64 complex unless noted).
@@ -338,7 +275,7 @@ static inline PinvyArgs pinvy_args(const tctf::Plan& p) {
 // Per frequency b, by a whole block: G_Y as the sum of the column-block partials (fixed
 // order), the objective term c_b tr(D G_Y), G_Y^+ and, unless it is exactly 0,
 // q = I - eta G_Y G_Y^+ for the next X-update (first line of eq. (updataXYW1)); qy_zero[b] = 1
-// marks q = 0.  sm: pinvy_lds_bytes(r) bytes of LDS.
+// marks q = 0.  sm: pinv_lds_bytes(r) bytes of LDS.
 __device__ inline void pinvy_block(int b, const PinvyArgs& a, unsigned char* sm) {
   const int tid = threadIdx.x, nt = blockDim.x, r = a.r, rr = r * r;
   cd* gy = (cd*)sm;
@@ -346,20 +283,22 @@ __device__ inline void pinvy_block(int b, const PinvyArgs& a, unsigned char* sm)
   PinvScratch ps;
   ps.work = gp + rr;
   ps.vec = ps.work + rr;
-  ps.colk = ps.vec + rr;
-  ps.rowk = ps.colk + r;
-  ps.rot = (double*)(ps.rowk + r);
+  ps.rot = (double*)(ps.vec + rr);
   ps.red = ps.rot + 96;
-  double tr = 0.0;
   for (int e = tid; e < rr; e += nt) {
-    cd g = a.gyq[(size_t)b * a.ny * rr + e];
-    for (int k = 1; k < a.ny; ++k) g = cd_add(g, a.gyq[((size_t)b * a.ny + k) * rr + e]);
+    const cd* src = a.gyq + (size_t)b * a.ny * rr + e;
+    cd g = src[0];
+    for (int k0 = 1; k0 < a.ny; k0 += 8) {   // eight partials' loads in flight, added in order
+      cd v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = src[(size_t)min(k0 + k, a.ny - 1) * rr];
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (k0 + k < a.ny) g = cd_add(g, v[k]);
+    }
     gy[e] = g;
-    const cd d = a.dmat[(size_t)b * rr + (e % r) * r + e / r];   // D(t, s) for G_Y(s, t)
-    tr += d.re * g.re - d.im * g.im;
   }
-  tr = block_sum_d(tr, ps.red);   // also orders the G_Y stores before their reads
-  if (tid == 0) a.bin_obj[b] = bin_weight(b, a.n3) * tr;
+  __syncthreads();
   const int fully = pinv_herm(gy, gp, r, a.force_eigen, ps);
   const bool qyz = fully && a.eta == 1.0;
   for (int e = tid; e < rr; e += nt) {
@@ -374,4 +313,13 @@ __device__ inline void pinvy_block(int b, const PinvyArgs& a, unsigned char* sm)
     a.gyp[(size_t)b * rr + e] = gp[e];
   }
   if (tid == 0) a.qy_zero[b] = qyz ? 1 : 0;
+  if (tid < 64) {   // tr(D G_Y), by one wavefront
+    double tr = 0.0;
+    for (int e = tid; e < rr; e += 64) {
+      const cd d = a.dmat[(size_t)b * rr + (e % r) * r + e / r], g = gy[e];   // D(t, s) for G_Y(s, t)
+      tr += d.re * g.re - d.im * g.im;
+    }
+    for (int off = 32; off > 0; off >>= 1) tr += __shfl_xor(tr, off);
+    if (tid == 0) a.bin_obj[b] = bin_weight(b, a.n3) * tr;
+  }
 }

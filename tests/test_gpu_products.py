@@ -32,3 +32,26 @@ def test_x_update_edges(n1, n2, n3, r, rho1, eta, precision):
         # one iteration from BF16 W~ (relative rounding up to 2^-8 per entry): W is a smoothed
         # product of sums over it
         _compare(g, st, None, label=f"{n1}x{n2}x{n3} r{r} mixed", tol=2.0**-7, tol_max=2.0**-5, tol_row=2.0**-5)
+
+
+@pytest.mark.parametrize("n1,n2,n3,r", [
+    (1, 3, 4, 1),        # one row: no difference
+    (7, 9, 5, 2),        # inside one run of eight rows
+    (8, 17, 4, 8),       # exactly one run; a column past a 16-column group
+    (9, 33, 3, 7),       # one row in the second run, an odd rank: a last 1 x 1 pivot
+    (65, 16, 4, 15),     # nine runs over eight wavefronts
+    (130, 40, 6, 16),    # the largest rank of one tile
+    (66, 50, 4, 17),     # two tiles, one column in the second
+    (80, 64, 3, 32),     # two full tiles
+    (12, 12, 512, 8),    # two wavefronts per block (many frequencies of few rows)
+    (64, 20, 510, 9),    # its last row count and first frequency count
+    (65, 20, 510, 9),    # one row more: eight wavefronts
+])
+@pytest.mark.parametrize("pinv_mode", [0, 1])
+def test_gram_and_product_edges(n1, n2, n3, r, pinv_mode):
+    """X~^* W~ and G_X in one launch, with the pivot sweep (pinv_mode 0) and the eigen route (1)."""
+    d = make_inputs(n1, n2, n3, r, p=0.7, seed=n1 + n2 + n3 + r, sigma_od=1.0, noise=0.02)
+    print(f"{n1}x{n2}x{n3} r{r} pinv_mode {pinv_mode}", flush=True)
+    g = gpu_run(d, r, 4, pinv_mode=pinv_mode)
+    st, info = oracle_run(d, r, 4, history=True)
+    _compare(g, st, info, label=f"{n1}x{n2}x{n3} r{r}")
