@@ -259,7 +259,7 @@ static void fill_plan(tctf_ctx* c, hipStream_t stream) {
   q.zsp = (float*)(w + L.zsp);
   q.wsp = (float*)(w + L.wsp);
   q.csp = (float*)(w + L.csp);
-  q.twg = (double2*)(w + L.twg);
+  q.twg = L.split ? (double2*)(w + L.twg) : nullptr;
   q.rsig = (double*)(w + L.rsig);
   q.rtx = (cd*)(w + L.rtx);
   q.rty = (cd*)(w + L.rty);
@@ -352,15 +352,16 @@ static tctf_status ctx_init(tctf_ctx* c, const tctf_params* prm, const float* G,
   tctf::launch_zero(p, p.qy_zero, (size_t)p.nb * 4);
   tctf::launch_pack_g(p, G, omega);
   tctf::launch_tables(p);
-  if (c->lay.split) tctf::launch_gen_twiddles(p);   // the three-launch path's roots of unity
-  if (X0) tctf::launch_tube_dft_setup(p, X0, p.xt, p.n1, p.r, (long)p.r * p.n1, 1, p.n1);
+  if (p.twg) tctf::launch_roots(p);   // the three-launch path's roots of unity
+  const long n3 = p.n3;
+  if (X0) tctf::launch_tube_fwd(p, tctf::SPEC_F32, X0, p.xt, (long)p.r * p.n1, p.n1, 1, n3, p.r * n3, p.r, p.n1, 1.0);
   else tctf::launch_zero(p, p.xt, (size_t)p.nb * p.r * p.n1 * 8);
   const float* y0 = Y0;
   if (!y0) {
     tctf::launch_normal(p, (float*)p.zt, (size_t)p.r * p.n2 * p.n3, seed);
     y0 = (const float*)p.zt;
   }
-  tctf::launch_tube_dft_setup(p, y0, p.yt, p.r, p.n2, (long)p.r * p.n2, p.n2, 1);
+  tctf::launch_tube_fwd(p, tctf::SPEC_F32, y0, p.yt, (long)p.r * p.n2, p.n2, 1, p.n2 * n3, n3, p.r, p.n2, 1.0);
   tctf::launch_zgemm(p);
   tctf::launch_slice(p, tctf::SLICE_INIT, nullptr, nullptr, 1);
   tctf::launch_bgemm(p);
@@ -657,8 +658,12 @@ tctf_status tctf_get_result(tctf_ctx* c, float* W, float* Z, float* X, float* Y)
     tctf::launch_zgemm(p);
     tctf::launch_slice(p, tctf::SLICE_RESULT, W, Z, c->iters == 0 ? 1 : 0);
   }
-  if (X) tctf::launch_tube_idft_setup(p, p.xt, X, p.n1, p.r, (long)p.r * p.n1, 1, p.n1);
-  if (Y) tctf::launch_tube_idft_setup(p, p.yt, Y, p.r, p.n2, (long)p.r * p.n2, p.n2, 1);
+  const long n3 = p.n3;
+  const double scale = 1.0 / p.n3;
+  if (X)
+    tctf::launch_tube_inv(p, tctf::SPEC_F32, p.xt, (long)p.r * p.n1, p.n1, 1, X, nullptr, n3, p.r * n3, p.r, p.n1, scale);
+  if (Y)
+    tctf::launch_tube_inv(p, tctf::SPEC_F32, p.yt, (long)p.r * p.n2, p.n2, 1, Y, nullptr, p.n2 * n3, n3, p.r, p.n2, scale);
   tctf_status s = check_launch();
   if (s != TCTF_OK) return s;
   HIP_TRY(hipStreamSynchronize(p.stream));

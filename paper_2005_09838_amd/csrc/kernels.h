@@ -47,11 +47,11 @@ struct Plan {
   int* flag;        // non-finite detector
   uint32_t* ctr;    // iteration counter of the BF16 rounding bits (advanced by each X-step)
   // the three-launch slice path (tube lengths outside the generated set, or slices larger
-  // than the fused kernel's LDS): spatial Z, W and elimination factors, roots of unity
+  // than the fused kernel's LDS): spatial Z and W, partials of the objective, roots of unity
   float* zsp;       // [n1][n2][n3]
   float* wsp;       // [n1][n2][n3]
   float* csp;       // [n1][n2][n3]
-  double2* twg;     // [n3] (cos, sin)(2 pi m / n3)
+  double2* twg;     // [n3] (cos, sin)(2 pi m / n3); NULL without that path
   // step 5 (rank adjustment)
   double* rsig;     // [nb][r] singular values of Z~_b, descending
   cd* rtx;          // [nb][r][r] factor rotations of X~ and Y~
@@ -70,10 +70,19 @@ size_t wt_elem_bytes(const Plan& p);
 // setup
 void launch_pack_g(const Plan& p, const float* G, const uint8_t* omega);
 void launch_tables(const Plan& p);
-void launch_tube_dft_setup(const Plan& p, const float* src, float2* dst, int P, int Q,
-                           long sb, long sp, long sq);   // real [P][Q][n3] -> half spectrum
-void launch_tube_idft_setup(const Plan& p, const float2* src, float* dst, int P, int Q,
-                            long sb, long sp, long sq);  // half spectrum -> real [P][Q][n3]
+// FP64 tube transforms: P x Q tubes between a spectrum (bin b of tube (p, q) at b bs + p ps +
+// q qs) and spatial tubes (entry k at p sp + q sq + k), times s; the inverse sums over all n3
+// frequencies of the conjugate-symmetric spectrum.  out2 (or NULL): a second copy.
+enum SpecKind { SPEC_F32 = 0, SPEC_F64 = 1, SPEC_BF16 = 2 };   // float2, double2, packed bf16 pairs
+void launch_tube_inv(const Plan& p, int kind, const void* in, long bs, long ps, long qs, float* out, float* out2, long sp,
+                     long sq, int P, int Q, double s);
+void launch_tube_inv64(const Plan& p, int kind, const void* in, long bs, long ps, long qs, double* out, long sp, long sq,
+                       int P, int Q, double s);
+void launch_tube_fwd(const Plan& p, int kind, const float* in, void* out, long bs, long ps, long qs, long sp, long sq, int P,
+                     int Q, double s);
+void launch_tube_fwd64(const Plan& p, const double* in, double2* out, long bs, long ps, long qs, long sp, long sq, int P,
+                       int Q, double s);
+void launch_roots(const Plan& p);   // p.twg
 void launch_normal(const Plan& p, float* dst, size_t n, uint64_t seed);
 void launch_zero(const Plan& p, void* dst, size_t bytes);
 
@@ -87,7 +96,6 @@ int slice_default_path(int n2, int n3);
 bool slice_path_valid(int path, int n2, int n3);
 bool slice_supported(int n3);
 bool slice_fused(int n2, int n3);          // the fused LDS slice kernel applies
-void launch_gen_twiddles(const Plan& p);
 void launch_slice_generic(const Plan& p, int mode, float* w_out, float* z_out, int w_from_g);
 bool slice_hosts_pinvy(const Plan& p);   // the iteration's slice launch also forms G_Y^+
 size_t slice_launch_lds_bytes(const Plan& p);

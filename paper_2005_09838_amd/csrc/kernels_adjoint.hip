@@ -19,7 +19,7 @@
 //
 // Simple building blocks, chosen for clarity over speed (this is not the iteration's hot
 // path): a batched complex GEMM on 16 x 16 LDS tiles over strided views (FP32 forward
-// values or FP64 adjoints), tridiagonal H_rho1 applications and solves along n1, direct
+// values or FP64 adjoints), tridiagonal H_rho1 applications and solves along n1, the FP64
 // tube transforms, FP64 Gram inverses by the library's Hermitian pseudo-inverse, and
 // fixed-order reductions for the weights' adjoints.
 #include "kernels.h"
@@ -203,46 +203,6 @@ __global__ void __launch_bounds__(256) k_adj_inv(const double2* __restrict__ g, 
   if (threadIdx.x == 0 && !full) flag[0] = 1;
 }
 
-// ---------------------------------------------------------------- tube transforms
-// Spatial tubes -> stored frequencies: out(b, p, q) = s sum_l omega^{b l} in(p, q, l),
-// omega = exp(+2 pi i / n3) (eq. (bar BA-k)); one thread per (tube, b).
-__global__ void k_adj_tube_fwd(const double* __restrict__ in, long isp, long isq, double2* __restrict__ out,
-                               long obs, long ops, long oqs, int P, int Q, int n3, int nb, double s) {
-  const long g = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= (long)P * Q * nb) return;
-  const int b = (int)(g % nb);
-  const long t = g / nb, pp = t / Q, qq = t % Q;
-  const double* a = in + pp * isp + qq * isq;
-  double re = 0.0, im = 0.0;
-  for (int l = 0; l < n3; ++l) {
-    double sn, cs;
-    sincospi(2.0 * (double)((long)b * l % n3) / n3, &sn, &cs);
-    re += cs * a[l];
-    im += sn * a[l];
-  }
-  out[b * obs + pp * ops + qq * oqs] = make_double2(s * re, s * im);
-}
-
-// Stored frequencies -> spatial tubes: out(p, q, l) = s sum_b c_b Re(omega^{-b l} in(b, p, q))
-// (the sum over all n3 frequencies of a conjugate-symmetric spectrum); one thread per
-// (tube, l).  T: float2 (forward values) or double2 (adjoints).
-template <typename T>
-__global__ void k_adj_tube_inv(const T* __restrict__ in, long ibs, long ips, long iqs, double* __restrict__ out,
-                               long osp, long osq, int P, int Q, int n3, int nb, double s) {
-  const long g = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (g >= (long)P * Q * n3) return;
-  const int l = (int)(g % n3);
-  const long t = g / n3, pp = t / Q, qq = t % Q;
-  double acc = 0.0;
-  for (int b = 0; b < nb; ++b) {
-    const T v = in[b * ibs + pp * ips + qq * iqs];
-    double sn, cs;
-    sincospi(2.0 * (double)((long)b * l % n3) / n3, &sn, &cs);
-    acc += bin_weight(b, n3) * ((double)v.x * cs + (double)v.y * sn);   // Re(e^{-i th} v)
-  }
-  out[pp * osp + qq * osq + l] = s * acc;
-}
-
 // ---------------------------------------------------------------- W-step adjoint
 // For every row (i, :, k): lambda solves K_uu lambda_u = w_bar_u with lambda_o = 0
 // (K_{mu rho2} = (1 + mu) I + rho2 K^T K restricted to the unobserved entries), z_bar = lambda;
@@ -409,14 +369,6 @@ static void herm(const Plan& p, const double2* g, double2* s) {
   k_adj_herm<<<(unsigned)((n + 255) / 256), 256, 0, p.stream>>>(g, s, p.r, p.nb);
 }
 
-template <typename T>
-static void tube_inv(const Plan& p, const T* in, long ibs, long ips, long iqs, double* out, long osp, long osq, int P,
-                     int Q, double s) {
-  const long n = (long)P * Q * p.n3;
-  k_adj_tube_inv<T><<<(unsigned)((n + 255) / 256), 256, 0, p.stream>>>(in, ibs, ips, iqs, out, osp, osq, P, Q, p.n3,
-                                                                      p.nb, s);
-}
-
 void launch_adjoint_step(const Plan& p, const AdjWork& w, const AdjState& in, const AdjState& out, double2* xt_bar,
                          double2* yt_bar, double* w_bar, double* theta) {
   const int n1 = p.n1, n2 = p.n2, n3 = p.n3, r = p.r, nb = p.nb;
@@ -437,7 +389,7 @@ void launch_adjoint_step(const Plan& p, const AdjWork& w, const AdjState& in, co
   k_adj_flag_zero<<<1, 64, 0, p.stream>>>(w.flag);
   k_adj_htab<<<1, 64, 0, p.stream>>>(n1, p.rho1, w.htab);
   // W+ in the spatial domain, from its stored spectrum
-  tube_inv<float2>(p, out.wt, n2, (long)nb * n2, 1, w.w1s, (long)n2 * n3, n3, n1, n2, 1.0 / n3);
+  launch_tube_inv64(p, SPEC_F32, out.wt, n2, (long)nb * n2, 1, w.w1s, (long)n2 * n3, n3, n1, n2, 1.0 / n3);
   // step 4: W-step adjoint -> z_bar, and the mu, rho2 adjoints
   const int wblk = (int)(((long)n1 * n3 + 255) / 256);
   k_adj_wstep<<<wblk, 256, 0, p.stream>>>(w_bar, w.w1s, p.gp, w.zbar, w.cbuf, n1, n2, n3, p.mu, p.rho2, p.gseg,
@@ -445,12 +397,7 @@ void launch_adjoint_step(const Plan& p, const AdjWork& w, const AdjState& in, co
   k_adj_reduce2<<<1, 256, 0, p.stream>>>(w.part, wblk, theta, 0, 2);
   // step 3: Z~_bar = ifft(Z_bar) on the stored frequencies; X~+_bar += Z~_bar Y~+^*,
   // Y~+_bar += X~+^* Z~_bar
-  {
-    const long n = (long)n1 * n2 * nb;
-    k_adj_tube_fwd<<<(unsigned)((n + 255) / 256), 256, 0, p.stream>>>(w.zbar, (long)n2 * n3, n3, w.ztb,
-                                                                      (long)n1 * n2, n2, 1, n1, n2, n3, nb,
-                                                                      1.0 / n3);
-  }
+  launch_tube_fwd64(p, w.zbar, w.ztb, (long)n1 * n2, n2, 1, (long)n2 * n3, n3, n1, n2, 1.0 / n3);
   axpby(p, fx, 1.0, xt_bar, 0.0, nullptr, w.x1b);
   axpby(p, fy, 1.0, yt_bar, 0.0, nullptr, w.y1b);
   gemm(p, n1, r, n2, one, hv(w.ztb), ctr(Y1), one, w.x1b, (long)r * n1, 1, n1);
@@ -495,15 +442,15 @@ void launch_adjoint_step(const Plan& p, const AdjWork& w, const AdjState& in, co
   herm(p, w.gyb, w.S);
   gemm(p, r, n2, r, one, gv(w.S), Y, one, yt_bar, (long)r * n2, n2, 1);
   // step 7 of the previous iteration: W~ = dft(W), so W_bar = sum_b c_b Re(omega^{-b l} W~_bar_b)
-  tube_inv<double2>(p, w.wtb, (long)n1 * n2, n2, 1, w_bar, (long)n2 * n3, n3, n1, n2, 1.0);
+  launch_tube_inv64(p, SPEC_F64, w.wtb, (long)n1 * n2, n2, 1, w_bar, (long)n2 * n3, n3, n1, n2, 1.0);
 }
 
 void launch_adjoint_initial(const Plan& p, const double2* xt_bar, const double2* yt_bar, double* x0_bar,
                             double* y0_bar) {
   const int n1 = p.n1, n2 = p.n2, n3 = p.n3, r = p.r;
   // X~ [nb][r][n1] -> X0 [n1][r][n3];  Y~ [nb][r][n2] -> Y0 [r][n2][n3]
-  if (x0_bar) tube_inv<double2>(p, xt_bar, (long)r * n1, 1, n1, x0_bar, (long)r * n3, n3, n1, r, 1.0);
-  if (y0_bar) tube_inv<double2>(p, yt_bar, (long)r * n2, n2, 1, y0_bar, (long)n2 * n3, n3, r, n2, 1.0);
+  if (x0_bar) launch_tube_inv64(p, SPEC_F64, xt_bar, (long)r * n1, n1, 1, x0_bar, n3, (long)r * n3, r, n1, 1.0);
+  if (y0_bar) launch_tube_inv64(p, SPEC_F64, yt_bar, (long)r * n2, n2, 1, y0_bar, (long)n2 * n3, n3, r, n2, 1.0);
 }
 
 void launch_objective_gradient(const Plan& p, const AdjWork& w, double* x_grad, double* y_grad) {
@@ -522,8 +469,8 @@ void launch_objective_gradient(const Plan& p, const AdjWork& w, double* x_grad, 
   gemm(p, r, n2, n1, mone, ctr(X), Wt, zero, w.bm, (long)r * n2, n2, 1);
   gemm(p, r, n2, r, one, gv(w.gx), Y, one, w.bm, (long)r * n2, n2, 1);
   // d f0 / d X = Re idft(grad_X): the inverse transform with the 1 / n3 of eq. (barAAk)
-  tube_inv<double2>(p, w.a, (long)r * n1, 1, n1, x_grad, (long)r * n3, n3, n1, r, 1.0 / n3);
-  tube_inv<double2>(p, w.bm, (long)r * n2, n2, 1, y_grad, (long)n2 * n3, n3, r, n2, 1.0 / n3);
+  launch_tube_inv64(p, SPEC_F64, w.a, (long)r * n1, n1, 1, x_grad, n3, (long)r * n3, r, n1, 1.0 / n3);
+  launch_tube_inv64(p, SPEC_F64, w.bm, (long)r * n2, n2, 1, y_grad, (long)n2 * n3, n3, r, n2, 1.0 / n3);
 }
 
 }  // namespace tctf

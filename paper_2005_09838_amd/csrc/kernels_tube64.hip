@@ -1,0 +1,307 @@
+// FP64 tube transforms between spatial tubes and stored frequencies for any tube length and any
+// strides: the initial factors and the factor results, the three-launch slice path and the
+// adjoint.  Forward (eq. (bar BA-k)): X[b] = s sum_k x[k] exp(+2 pi i b k / n3), b = 0 .. n3 / 2;
+// inverse (eq. (barAAk)): x[k] = s sum_b c_b Re(exp(-2 pi i b k / n3) X[b]).
+#include "fft64.h"
+#include "kernels.h"
+
+namespace tctf {
+
+Fft64Plan fft64_plan(int n) {
+  Fft64Plan pl;
+  pl.n = n;
+  pl.passes = 0;
+  for (int r : {8, 7, 5, 4, 3, 2})
+    while (n % r == 0 && n > 1) {
+      pl.radix[pl.passes++] = r;
+      n /= r;
+    }
+  for (int r = 11; n > 1; r += 2)
+    while (n % r == 0) {
+      pl.radix[pl.passes++] = r;
+      n /= r;
+    }
+  return pl;
+}
+
+template <int KIND> struct SpecOf { typedef float2 type; };
+template <> struct SpecOf<SPEC_F64> { typedef double2 type; };
+
+template <int KIND>
+__device__ __forceinline__ cd spec_load(const void* in, size_t at) {
+  const typename SpecOf<KIND>::type v = ((const typename SpecOf<KIND>::type*)in)[at];
+  return cd_make(v.x, v.y);
+}
+// key: of the BF16 rounding bits (SPEC_BF16)
+template <int KIND>
+__device__ __forceinline__ void spec_store(void* out, size_t at, double re, double im, uint32_t key) {
+  if constexpr (KIND == SPEC_F64) ((double2*)out)[at] = make_double2(re, im);
+  else if constexpr (KIND == SPEC_F32) ((float2*)out)[at] = make_float2((float)re, (float)im);
+  else ((uint32_t*)out)[at] = pack_bf16x2_sr((float)re, (float)im, fmix32((uint32_t)at ^ key));
+}
+
+// Block (x, y): up to 2 PP tubes (y, q), q = 2 PP x ..., as PP complex sequences in LDS, then the
+// roots of unity unless the caller's table holds them.  A sequence carries two tubes: on the
+// inverse C[k] = A[k] + i B[k] over the conjugate-symmetric extension of both spectra, on the
+// forward A = (C[k] + conj C[N - k]) / 2, B = (C[k] - conj C[N - k]) / (2 i).  What bounds it:
+// LDS traffic and the barriers of the passes (12 x 12 x 8064: 29.6 us for 72 blocks of one pair,
+// 13.9 ms as direct sums; 288 x 28 x 144: 16.7 us, direct 115).
+struct Tube64 {
+  long bs, ps, qs;   // strides of the spectrum
+  long sp, sq;       // strides of the spatial tubes
+  int Q, PP;
+  double s;
+  const double2* tw;   // exp(2 pi i e / n3), or NULL: formed in LDS
+};
+__device__ __forceinline__ const cd* tube64_roots(const Tube64& t, cd* x, int N) {
+  if (t.tw) return (const cd*)t.tw;
+  cd* w = x + t.PP * N;
+  for (int e = threadIdx.x; e < N; e += blockDim.x) {
+    double sn, c;
+    sincospi(2.0 * e / N, &sn, &c);
+    w[e] = cd_make(c, sn);
+  }
+  return w;
+}
+
+template <int KIND, typename T>
+__global__ void __launch_bounds__(1024) k_tube64_inv(const void* __restrict__ in, T* __restrict__ out, T* __restrict__ out2,
+                                                     Tube64 t, Fft64Plan pl) {
+  extern __shared__ __align__(16) unsigned char sm[];
+  cd* x = (cd*)sm;
+  const int N = pl.n, nb = N / 2 + 1, q0 = 2 * t.PP * blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
+  const int nq = min(2 * t.PP, t.Q - q0), np = (nq + 1) >> 1;
+  const float rp = 1.0f / np, rn = 1.0f / N;
+  const cd* tw = tube64_roots(t, x, N);
+  for (int e = tid; e < nb * np; e += nt) {
+    const int b = fft64_div(e, rp), pp = e - b * np;
+    const size_t at = b * t.bs + blockIdx.y * t.ps + (q0 + 2 * pp) * t.qs;
+    const bool two = 2 * pp + 1 < nq;
+    cd a = spec_load<KIND>(in, at), c = spec_load<KIND>(in, at + (two ? t.qs : 0));
+    if (!two) c = cd_make(0.0, 0.0);
+    if (b == 0 || 2 * b == N) a.im = c.im = 0.0;
+    x[pp * N + b] = cd_make(a.re - c.im, a.im + c.re);
+    if (b > 0 && 2 * b != N) x[pp * N + N - b] = cd_make(a.re + c.im, c.re - a.im);
+  }
+  fft64(x, np, pl, tw, -1.0);
+  for (int e = tid; e < nq * N; e += nt) {
+    const int q = fft64_div(e, rn), k = e - q * N;
+    const cd v = x[(q >> 1) * N + k];
+    const T z = (T)(t.s * ((q & 1) ? v.im : v.re));
+    const size_t at = blockIdx.y * t.sp + (q0 + q) * t.sq + k;
+    out[at] = z;
+    if (out2) out2[at] = z;
+  }
+}
+
+template <int KIND, typename T>
+__global__ void __launch_bounds__(1024) k_tube64_fwd(const T* __restrict__ in, void* __restrict__ out, Tube64 t, Fft64Plan pl,
+                                                     const uint32_t* __restrict__ ctr) {
+  extern __shared__ __align__(16) unsigned char sm[];
+  cd* x = (cd*)sm;
+  const int N = pl.n, nb = N / 2 + 1, q0 = 2 * t.PP * blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
+  const int nq = min(2 * t.PP, t.Q - q0), np = (nq + 1) >> 1;
+  const float rp = 1.0f / np, rn = 1.0f / N;
+  const cd* tw = tube64_roots(t, x, N);
+  for (int e = tid; e < np * N; e += nt) {
+    const int pp = fft64_div(e, rn), k = e - pp * N;
+    const size_t at = blockIdx.y * t.sp + (q0 + 2 * pp) * t.sq + k;
+    const bool two = 2 * pp + 1 < nq;
+    const T a = in[at], c = in[at + (two ? t.sq : 0)];
+    x[pp * N + k] = cd_make((double)a, two ? (double)c : 0.0);
+  }
+  fft64(x, np, pl, tw, +1.0);
+  uint32_t key = 0;
+  if constexpr (KIND == SPEC_BF16) key = fmix32(ctr[0] * 0x9e3779b9u + 0x7f4a7c15u);
+  for (int e = tid; e < nb * np; e += nt) {
+    const int b = fft64_div(e, rp), pp = e - b * np;
+    const cd c = x[pp * N + b], d = x[pp * N + (b ? N - b : 0)];
+    const bool real = b == 0 || 2 * b == N;
+    const double h = 0.5 * t.s;
+    const size_t at = b * t.bs + blockIdx.y * t.ps + (q0 + 2 * pp) * t.qs;
+    spec_store<KIND>(out, at, h * (c.re + d.re), real ? 0.0 : h * (c.im - d.im), key);
+    if (2 * pp + 1 < nq) spec_store<KIND>(out, at + t.qs, h * (c.im + d.im), real ? 0.0 : h * (d.re - c.re), key);
+  }
+}
+
+// ---- direct sums, one thread per output: lengths with a large prime factor and few tubes
+template <int KIND, typename T>
+__global__ void __launch_bounds__(256) k_tube_direct_inv(const void* __restrict__ in, T* __restrict__ out, T* __restrict__ out2,
+                                                         Tube64 t, int P, int n3) {
+  const long g = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  if (g >= (long)P * t.Q * n3) return;
+  const int k = (int)(g % n3), nb = n3 / 2 + 1;
+  const long tube = g / n3, p = tube / t.Q, q = tube % t.Q;
+  double acc = 0.0;
+  int m = 0;   // (b k) mod n3
+  for (int b = 0; b < nb; ++b) {
+    const cd v = spec_load<KIND>(in, b * t.bs + p * t.ps + q * t.qs);
+    double sn, c;
+    if (t.tw) {
+      c = t.tw[m].x;
+      sn = t.tw[m].y;
+    } else {
+      sincospi(2.0 * m / n3, &sn, &c);
+    }
+    acc += bin_weight(b, n3) * (v.re * c + (bin_is_real(b, n3) ? 0.0 : v.im * sn));   // Re(e^{-i th} v)
+    m += k;
+    if (m >= n3) m -= n3;
+  }
+  const size_t at = p * t.sp + q * t.sq + k;
+  out[at] = (T)(t.s * acc);
+  if (out2) out2[at] = (T)(t.s * acc);
+}
+template <int KIND, typename T>
+__global__ void __launch_bounds__(256) k_tube_direct_fwd(const T* __restrict__ in, void* __restrict__ out, Tube64 t, int P,
+                                                         int n3, const uint32_t* __restrict__ ctr) {
+  const long g = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  const int nb = n3 / 2 + 1;
+  if (g >= (long)P * t.Q * nb) return;
+  const int b = (int)(g % nb);
+  const long tube = g / nb, p = tube / t.Q, q = tube % t.Q;
+  const T* src = in + p * t.sp + q * t.sq;
+  double re = 0.0, im = 0.0;
+  int m = 0;   // (b k) mod n3
+  for (int k = 0; k < n3; ++k) {
+    double sn, c;
+    if (t.tw) {
+      c = t.tw[m].x;
+      sn = t.tw[m].y;
+    } else {
+      sincospi(2.0 * m / n3, &sn, &c);
+    }
+    const double v = src[k];
+    re += c * v;
+    im += sn * v;
+    m += b;
+    if (m >= n3) m -= n3;
+  }
+  if (bin_is_real(b, n3)) im = 0.0;
+  uint32_t key = 0;
+  if constexpr (KIND == SPEC_BF16) key = fmix32(ctr[0] * 0x9e3779b9u + 0x7f4a7c15u);
+  spec_store<KIND>(out, b * t.bs + p * t.ps + q * t.qs, t.s * re, t.s * im, key);
+}
+
+// ---- host side
+static int largest_prime(int n) {
+  int best = 1;
+  for (int f = 2; f * f <= n; ++f)
+    while (n % f == 0) {
+      best = f;
+      n /= f;
+    }
+  return n > best ? n : best;
+}
+
+// Whether the passes beat the direct sums.  A large prime radix is itself a direct sum, run by one
+// block per few pairs and without the saving of real tubes, so it pays only beside a cofactor,
+// and below 40 entries (24 with radices up to 7) the passes' barriers cost as much as the sums.
+// Both transforms and the W-step in us, direct / passes, for 144 x 28 tubes: of 18 entries
+// 16.0 / 17.4, 22 17.0 / 20.4, 25 17.4 / 16.6, 33 20.3 / 23.2, 44 23.8 / 23.1, 60 31.9 / 19.5,
+// 62 32.0 / 38.5, 93 58.6 / 36.8, 122 88.4 / 63.8, 254 320 / 189, 257 335 / 447, 335 558 / 160;
+// for 100 tubes: 257 60 / 135, 335 74 / 48, 1018 220 / 358; 900 of 2003 5196 / 4490, 40 of 2003
+// 511 / 2282.
+static bool tube64_fast(const Plan& p, long pairs) {
+  const int n3 = p.n3, lp = largest_prime(n3);
+  if (n3 > 1024 && !p.twg) return false;   // the roots would not fit beside the sequence
+  if (lp <= 7) return n3 >= 24;
+  if (n3 / lp == 2) return n3 >= 64 && pairs >= 256;
+  return n3 / lp >= 3 && n3 >= 40;
+}
+
+static Tube64 tube64_args(const Plan& p, long bs, long ps, long qs, long sp, long sq, int Q, double s) {
+  Tube64 t;
+  t.bs = bs;
+  t.ps = ps;
+  t.qs = qs;
+  t.sp = sp;
+  t.sq = sq;
+  t.Q = Q;
+  t.PP = 1;
+  t.s = s;
+  t.tw = p.twg;
+  return t;
+}
+
+// Pairs per block (up to 2048 values, and at least two blocks per compute unit where there are
+// enough pairs), threads (about four values each) and LDS.
+static dim3 tube64_shape(Tube64* t, int n3, int P, int* threads, size_t* lds) {
+  const int per_p = (t->Q + 1) / 2;
+  const long pairs = (long)per_p * P;
+  int pp = n3 >= 2048 ? 1 : 2048 / n3;
+  if (pp > (pairs + 511) / 512) pp = (int)((pairs + 511) / 512);
+  if (pp > per_p) pp = per_p;
+  t->PP = pp;
+  int nt = ((pp * n3 + 3) / 4 + 63) / 64 * 64;
+  if (nt > 1024) nt = 1024;
+  *threads = nt;
+  *lds = ((size_t)pp * n3 + (t->tw ? 0 : n3)) * sizeof(cd);
+  return dim3((per_p + pp - 1) / pp, P);
+}
+
+template <int KIND, typename T>
+static void tube_inv(const Plan& p, const void* in, T* out, T* out2, Tube64 t, int P) {
+  const long pairs = (long)((t.Q + 1) / 2) * P;
+  if (!tube64_fast(p, pairs)) {
+    const long n = (long)P * t.Q * p.n3;
+    k_tube_direct_inv<KIND, T><<<(unsigned)((n + 255) / 256), 256, 0, p.stream>>>(in, out, out2, t, P, p.n3);
+    return;
+  }
+  int nt;
+  size_t lds;
+  const dim3 grid = tube64_shape(&t, p.n3, P, &nt, &lds);
+  if (lds > 65536)
+    (void)hipFuncSetAttribute((const void*)k_tube64_inv<KIND, T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  k_tube64_inv<KIND, T><<<grid, nt, lds, p.stream>>>(in, out, out2, t, fft64_plan(p.n3));
+}
+template <int KIND, typename T>
+static void tube_fwd(const Plan& p, const T* in, void* out, Tube64 t, int P) {
+  const long pairs = (long)((t.Q + 1) / 2) * P;
+  if (!tube64_fast(p, pairs)) {
+    const long n = (long)P * t.Q * (p.n3 / 2 + 1);
+    k_tube_direct_fwd<KIND, T><<<(unsigned)((n + 255) / 256), 256, 0, p.stream>>>(in, out, t, P, p.n3, p.ctr);
+    return;
+  }
+  int nt;
+  size_t lds;
+  const dim3 grid = tube64_shape(&t, p.n3, P, &nt, &lds);
+  if (lds > 65536)
+    (void)hipFuncSetAttribute((const void*)k_tube64_fwd<KIND, T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  k_tube64_fwd<KIND, T><<<grid, nt, lds, p.stream>>>(in, out, t, fft64_plan(p.n3), p.ctr);
+}
+
+// grid.y counts P (n1 <= 8192 or r <= 32)
+void launch_tube_inv(const Plan& p, int kind, const void* in, long bs, long ps, long qs, float* out, float* out2, long sp,
+                     long sq, int P, int Q, double s) {
+  const Tube64 t = tube64_args(p, bs, ps, qs, sp, sq, Q, s);
+  if (kind == SPEC_F64) tube_inv<SPEC_F64, float>(p, in, out, out2, t, P);
+  else tube_inv<SPEC_F32, float>(p, in, out, out2, t, P);
+}
+void launch_tube_inv64(const Plan& p, int kind, const void* in, long bs, long ps, long qs, double* out, long sp, long sq,
+                       int P, int Q, double s) {
+  const Tube64 t = tube64_args(p, bs, ps, qs, sp, sq, Q, s);
+  if (kind == SPEC_F64) tube_inv<SPEC_F64, double>(p, in, out, (double*)nullptr, t, P);
+  else tube_inv<SPEC_F32, double>(p, in, out, (double*)nullptr, t, P);
+}
+void launch_tube_fwd(const Plan& p, int kind, const float* in, void* out, long bs, long ps, long qs, long sp, long sq, int P,
+                     int Q, double s) {
+  const Tube64 t = tube64_args(p, bs, ps, qs, sp, sq, Q, s);
+  if (kind == SPEC_BF16) tube_fwd<SPEC_BF16, float>(p, in, out, t, P);
+  else tube_fwd<SPEC_F32, float>(p, in, out, t, P);
+}
+void launch_tube_fwd64(const Plan& p, const double* in, double2* out, long bs, long ps, long qs, long sp, long sq, int P,
+                       int Q, double s) {
+  tube_fwd<SPEC_F64, double>(p, in, out, tube64_args(p, bs, ps, qs, sp, sq, Q, s), P);
+}
+
+// twg[m] = (cos, sin)(2 pi m / n3), m = 0..n3-1
+__global__ void k_roots(double2* __restrict__ twg, int n3) {
+  const int m = blockIdx.x * blockDim.x + threadIdx.x;
+  if (m >= n3) return;
+  double s, c;
+  sincospi(2.0 * (double)m / n3, &s, &c);
+  twg[m] = make_double2(c, s);
+}
+void launch_roots(const Plan& p) { k_roots<<<(p.n3 + 255) / 256, 256, 0, p.stream>>>(p.twg, p.n3); }
+
+}  // namespace tctf
