@@ -70,6 +70,7 @@ size_t wt_elem_bytes(const Plan& p);
 // setup
 void launch_pack_g(const Plan& p, const float* G, const uint8_t* omega);
 void launch_tables(const Plan& p);
+void launch_tables64(const Plan& p, double* wtab, double* htab);   // the same tables in FP64
 // FP64 tube transforms: P x Q tubes between a spectrum (bin b of tube (p, q) at b bs + p ps +
 // q qs) and spatial tubes (entry k at p sp + q sq + k), times s; the inverse sums over all n3
 // frequencies of the conjugate-symmetric spectrum.  out2 (or NULL): a second copy.
@@ -140,13 +141,13 @@ struct AdjState {        // forward values of one iterate (inside a checkpoint b
   const float2* wt;      // W~ [n1][nb][n2]
 };
 struct AdjWork {         // adjoint scratch carved from the caller's adjoint workspace
-  double *w1s, *cbuf, *zbar;
+  double *w1s, *zbar;
   double2 *ztb, *wtb;
   double2 *x1b, *hx1, *a, *pp, *q, *pb, *qb, *ab, *dt;
   double2 *y1b, *bm, *bb, *rb;
   double2 *gy, *gyi, *gx, *gxi, *gyib, *gxib, *gyb, *gxb, *S, *T, *tmp;
-  double* htab;
-  double* part;
+  double *htab, *wtab;   // pivot tables in FP64
+  double *part, *wpart;
   int* flag;
 };
 size_t adjoint_work_bytes(const Plan& p);

@@ -146,40 +146,60 @@ __global__ void k_adj_happly(const T* __restrict__ x, double2* __restrict__ out,
   out[e] = make_double2(v.re, v.im);
 }
 
-// Thomas coefficients of H_rho1 = I + rho1 D^T D along n1 (one thread): tab[i] = 1 / pivot_i,
-// tab[n1 + i] = the superdiagonal factor c'_i.
-__global__ void k_adj_htab(int n1, double rho1, double* tab) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  double cp = 0.0;
-  for (int i = 0; i < n1; ++i) {
-    const double deg = (n1 == 1) ? 0.0 : ((i == 0 || i == n1 - 1) ? 1.0 : 2.0);
-    const double piv = 1.0 + rho1 * deg - (i > 0 ? -rho1 * cp : 0.0);
-    tab[i] = 1.0 / piv;
-    cp = (i + 1 < n1) ? -rho1 / piv : 0.0;
-    tab[n1 + i] = cp;
+// y = H_rho1^{-1} x for every column (b, s) of two X-shaped arrays (blockIdx.y), one wavefront per
+// column: d_i = (x_i + rho1 d_{i-1}) / alpha_i down the column, then y_i = d_i + (rho1 / alpha_i)
+// y_{i+1} up, as scans of affine maps over 64 entries at a time.  120 columns of 144 entries, both
+// arrays: 5.7 us (131 with a thread per column).
+__device__ __forceinline__ void hscan(double& a, double& br, double& bi, int dir) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int from = lane - dir * off;
+    const double ao = __shfl(a, from & 63), ro = __shfl(br, from & 63), io = __shfl(bi, from & 63);
+    if (from >= 0 && from < 64) {
+      br = fma(a, ro, br);
+      bi = fma(a, io, bi);
+      a *= ao;
+    }
   }
 }
-
-// y = H_rho1^{-1} x for every column (b, s) of X-shaped arrays (one thread per column).
-__global__ void k_adj_hsolve(const double2* __restrict__ x, double2* __restrict__ y, int n1, long ncol,
-                             double rho1, const double* __restrict__ tab) {
-  const long col = (long)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ void __launch_bounds__(256) k_adj_hsolve(const double2* __restrict__ x0, double2* __restrict__ y0,
+                                                    const double2* __restrict__ x1, double2* __restrict__ y1, int n1,
+                                                    long ncol, const double* __restrict__ htab) {
+  const long col = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (col >= ncol) return;
-  const double2* xc = x + col * n1;
-  double2* yc = y + col * n1;
-  double dr = 0.0, di = 0.0;
-  for (int i = 0; i < n1; ++i) {   // forward: d'_i = (x_i + rho1 d'_{i-1}) / pivot_i
-    const double2 v = xc[i];
-    dr = (v.x + rho1 * dr) * tab[i];
-    di = (v.y + rho1 * di) * tab[i];
-    yc[i] = make_double2(dr, di);
+  const int lane = threadIdx.x & 63, nch = (n1 + 63) / 64;
+  const double2* xc = (blockIdx.y ? x1 : x0) + col * n1;
+  double2* yc = (blockIdx.y ? y1 : y0) + col * n1;
+  double cr = 0.0, ci = 0.0;
+  for (int ch = 0; ch < nch; ++ch) {
+    const int i = 64 * ch + lane, at = min(i, n1 - 1);
+    const double2 v = xc[at];
+    const double inv = htab[n1 + at];
+    double a = at > 0 ? htab[2 * n1 + at] : 0.0, br = v.x * inv, bi = v.y * inv;
+    hscan(a, br, bi, 1);
+    br = fma(a, cr, br);
+    bi = fma(a, ci, bi);
+    if (i < n1) yc[i] = make_double2(br, bi);
+    cr = __shfl(br, 63);
+    ci = __shfl(bi, 63);
   }
-  double wr = 0.0, wi = 0.0;
-  for (int i = n1 - 1; i >= 0; --i) {   // backward: y_i = d'_i - c'_i y_{i+1}
-    const double2 d = yc[i];
-    wr = d.x - tab[n1 + i] * wr;
-    wi = d.y - tab[n1 + i] * wi;
-    yc[i] = make_double2(wr, wi);
+  cr = ci = 0.0;
+  for (int ch = nch - 1; ch >= 0; --ch) {
+    const int i = 64 * ch + lane;
+    double a = 0.0, br = 0.0, bi = 0.0;   // past the end: 0
+    if (i < n1) {
+      const double2 d = yc[i];
+      a = i + 1 < n1 ? htab[2 * n1 + i] : 0.0;
+      br = d.x;
+      bi = d.y;
+    }
+    hscan(a, br, bi, -1);
+    br = fma(a, cr, br);
+    bi = fma(a, ci, bi);
+    if (i < n1) yc[i] = make_double2(br, bi);
+    cr = __shfl(br, 0);
+    ci = __shfl(bi, 0);
   }
 }
 
@@ -206,59 +226,105 @@ __global__ void __launch_bounds__(256) k_adj_inv(const double2* __restrict__ g, 
 // ---------------------------------------------------------------- W-step adjoint
 // For every row (i, :, k): lambda solves K_uu lambda_u = w_bar_u with lambda_o = 0
 // (K_{mu rho2} = (1 + mu) I + rho2 K^T K restricted to the unobserved entries), z_bar = lambda;
-// partial sums of -<lambda, w> (mu) and -<lambda, K^T K w> (rho2) per block.  One thread per
-// row; cbuf holds the forward-elimination factors.
+// partial sums of -<lambda, w> (mu) and -<lambda, K^T K w> = -sum of products of differences
+// (rho2) per block.
+//
+// Block (x, i): S = 2^ls segments of at most L columns of the rows (i, :, k), k = x KB .. + KB,
+// KB = 256 / S, a thread per (segment, row).  With the tabulated pivots elimination and back
+// substitution are affine maps of the value that enters a segment, so each thread forms its
+// segment's map, takes the incoming value through the maps before it from LDS, and repeats its
+// columns.  What bounds it: the latency of the loads (all in flight at once) and of the chains of
+// L + S steps.  144 x 288 x 28: 18.4 us (516 with a thread per row and a division per entry).
+template <int L>
 __global__ void __launch_bounds__(256) k_adj_wstep(const double* __restrict__ wbar, const double* __restrict__ w,
                                                    const float* __restrict__ gp, double* __restrict__ zbar,
-                                                   double* __restrict__ cbuf, int n1, int n2, int n3, double mu,
-                                                   double rho2, int gseg, double* __restrict__ part) {
-  __shared__ double red[16];
-  const long row = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  double smu = 0.0, srho = 0.0;
-  if (row < (long)n1 * n3) {
-    const long i = row / n3, k = row % n3;
-    const long base = i * n2 * n3 + k;   // element (i, j, k) at base + j n3
-    auto deg = [&](int j) { return n2 == 1 ? 0.0 : ((j == 0 || j == n2 - 1) ? 1.0 : 2.0); };
-    auto unobs = [&](int j) { return is_unobserved(gp[packed_g_at(i, j, (int)k, n2, n3, gseg)]); };
-    double cprev = 0.0, dprev = 0.0;
-    bool uprev = false;
-    for (int j = 0; j < n2; ++j) {
-      const long e = base + (long)j * n3;
-      const bool u = unobs(j);
-      double cj = 0.0, dj = 0.0;
-      if (u) {
-        const double a = uprev ? -rho2 : 0.0;                              // coupling to j - 1
-        const double c = (j + 1 < n2 && unobs(j + 1)) ? -rho2 : 0.0;      // coupling to j + 1
-        const double piv = 1.0 + mu + rho2 * deg(j) - a * cprev;
-        cj = c / piv;
-        dj = (wbar[e] - a * dprev) / piv;
-      }
-      cbuf[e] = cj;
-      zbar[e] = dj;
-      cprev = cj;
-      dprev = dj;
-      uprev = u;
-    }
-    double lnext = 0.0;
-    for (int j = n2 - 1; j >= 0; --j) {
-      const long e = base + (long)j * n3;
-      const double lam = zbar[e] - cbuf[e] * lnext;   // 0 on observed entries (d = c = 0)
-      zbar[e] = lam;
-      lnext = lam;
-      const double wj = w[e];
-      double ktk = deg(j) * wj;
-      if (j > 0) ktk -= w[e - n3];
-      if (j + 1 < n2) ktk -= w[e + n3];
-      smu -= lam * wj;
-      srho -= lam * ktk;
+                                                   const double* __restrict__ wtab, int n2, int n3, double rho2,
+                                                   int gseg, int ls, double* __restrict__ part) {
+  __shared__ double red[48];
+  __shared__ double ma[256], mb[256], na[256], nb[256];
+  const int S = 1 << ls, KB = 256 >> ls, tid = threadIdx.x, s = tid >> (8 - ls), kk = tid & (KB - 1);
+  const int k = blockIdx.x * KB + kk, kc = min(k, n3 - 1), len = (n2 + S - 1) >> ls;
+  const int j0 = s * len, cnt = k < n3 ? min(len, n2 - j0) : 0;   // may be negative: no columns
+  const long i = blockIdx.y, base = i * n2 * n3 + kc;
+  double x[L], wj[L], inv[L];
+  float g[L];
+#pragma unroll
+  for (int u = 0; u < L; ++u) {
+    const int j = min(j0 + u, n2 - 1);
+    x[u] = wbar[base + (long)j * n3];
+    wj[u] = w[base + (long)j * n3];
+    g[u] = gp[packed_g_at(i, j, kc, n2, n3, gseg)];
+  }
+  const double wr = w[base + (long)min(j0 + max(cnt, 0), n2 - 1) * n3];   // right of the segment
+#pragma unroll
+  for (int u = 0; u < L; ++u) {
+    const bool un = u < cnt && is_unobserved(g[u]);
+    const double t = wtab[un ? unobs_index(g[u]) : 0];
+    inv[u] = un ? t : 0.0;   // 0: lambda = 0, and nothing passes
+    if (!un) x[u] = 0.0;
+  }
+  double a = 1.0, b = 0.0;
+#pragma unroll
+  for (int u = 0; u < L; ++u) {
+    if (u < cnt) {
+      b = inv[u] * fma(rho2, b, x[u]);
+      a *= rho2 * inv[u];
     }
   }
-  smu = block_sum_d(smu, red);
-  srho = block_sum_d(srho, red);
-  if (threadIdx.x == 0) {
-    part[2 * blockIdx.x] = smu;
-    part[2 * blockIdx.x + 1] = srho;
+  ma[tid] = a;
+  mb[tid] = b;
+  __syncthreads();
+  double d = 0.0;
+  for (int t = kk; t < s * KB; t += KB) d = fma(ma[t], d, mb[t]);
+#pragma unroll
+  for (int u = 0; u < L; ++u) {
+    if (u < cnt) d = inv[u] * fma(rho2, d, x[u]);
+    x[u] = d;
   }
+  a = cnt > 0 ? 1.0 : 0.0;
+  b = 0.0;
+#pragma unroll
+  for (int u = L - 1; u >= 0; --u) {
+    if (u < cnt) {
+      const double c = rho2 * inv[u];
+      b = fma(c, b, x[u]);
+      a *= c;
+    }
+  }
+  na[tid] = a;
+  nb[tid] = b;
+  __syncthreads();
+  double lam = 0.0, smu = 0.0, srho = 0.0;
+  for (int t = 256 - KB + kk; t > tid; t -= KB) lam = fma(na[t], lam, nb[t]);
+#pragma unroll
+  for (int u = L - 1; u >= 0; --u) {
+    if (u < cnt) {
+      const double right = lam, wn = u + 1 < cnt ? wj[u + 1 < L ? u + 1 : u] : wr;
+      lam = fma(rho2 * inv[u], lam, x[u]);
+      zbar[base + (long)(j0 + u) * n3] = lam;
+      smu -= lam * wj[u];
+      if (j0 + u + 1 < n2) srho -= (right - lam) * (wn - wj[u]);
+    }
+  }
+  double zero = 0.0;
+  block_sum3_d(smu, srho, zero, red);
+  if (tid == 0) {
+    const long blk = i * gridDim.x + blockIdx.x;
+    part[2 * blk] = smu;
+    part[2 * blk + 1] = srho;
+  }
+}
+
+// Segments of at most 16 columns; no more of them than that needs, so that as many lanes as
+// possible read consecutive words.  Returns the number of partials.
+static int wstep_adjoint(const Plan& p, const AdjWork& w, const double* w_bar) {
+  int ls = 0;
+  while (((p.n2 + (1 << ls) - 1) >> ls) > 16) ++ls;   // n2 <= 1024: ls <= 6
+  const int len = (p.n2 + (1 << ls) - 1) >> ls, KB = 256 >> ls;
+  const dim3 grid((p.n3 + KB - 1) / KB, p.n1);
+  const auto kernel = len <= 9 ? k_adj_wstep<9> : (len <= 12 ? k_adj_wstep<12> : k_adj_wstep<16>);
+  kernel<<<grid, 256, 0, p.stream>>>(w_bar, w.w1s, p.gp, w.zbar, w.wtab, p.n2, p.n3, p.rho2, p.gseg, ls, w.wpart);
+  return (int)(grid.x * grid.y);
 }
 
 // theta[k0] += sum of part[2 b], theta[k1] += sum of part[2 b + 1] (fixed order)
@@ -309,20 +375,17 @@ __global__ void k_adj_flag_zero(int* flag) {
 size_t adjoint_work_bytes(const Plan& p) {
   const size_t N = (size_t)p.n1 * p.n2 * p.n3, nh = (size_t)p.nb * p.n1 * p.n2;
   const size_t fx = (size_t)p.nb * p.r * p.n1, fy = (size_t)p.nb * p.r * p.n2, g = (size_t)p.nb * p.r * p.r;
-  const size_t wpart = ((N / p.n2 + 255) / 256) * 2 + ADJ_DOT_BLOCKS;
   auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
-  return 3 * al(N * 8) + 2 * al(nh * 16) + 9 * al(fx * 16) + 4 * al(fy * 16) + 11 * al(g * 16) +
-         al(2 * (size_t)p.n1 * 8) + al(wpart * 8) + al(64);
+  return 2 * al(N * 8) + 2 * al(nh * 16) + 9 * al(fx * 16) + 4 * al(fy * 16) + 11 * al(g * 16) +
+         al(3 * (size_t)p.n1 * 8) + al(4 * (size_t)p.n2 * 8) + al(ADJ_DOT_BLOCKS * 8) + al(64);
 }
 
 void adjoint_carve(const Plan& p, void* ws, AdjWork* w) {
   const size_t N = (size_t)p.n1 * p.n2 * p.n3, nh = (size_t)p.nb * p.n1 * p.n2;
   const size_t fx = (size_t)p.nb * p.r * p.n1, fy = (size_t)p.nb * p.r * p.n2, g = (size_t)p.nb * p.r * p.r;
-  const size_t wpart = ((N / p.n2 + 255) / 256) * 2 + ADJ_DOT_BLOCKS;
   unsigned char* o = (unsigned char*)ws;
   auto take = [&](size_t bytes) { unsigned char* at = o; o += (bytes + 255) & ~(size_t)255; return (void*)at; };
   w->w1s = (double*)take(N * 8);
-  w->cbuf = (double*)take(N * 8);
   w->zbar = (double*)take(N * 8);
   w->ztb = (double2*)take(nh * 16);
   w->wtb = (double2*)take(nh * 16);
@@ -332,8 +395,10 @@ void adjoint_carve(const Plan& p, void* ws, AdjWork* w) {
   for (auto q : ys) *q = (double2*)take(fy * 16);
   double2** gs[11] = {&w->gy, &w->gyi, &w->gx, &w->gxi, &w->gyib, &w->gxib, &w->gyb, &w->gxb, &w->S, &w->T, &w->tmp};
   for (auto q : gs) *q = (double2*)take(g * 16);
-  w->htab = (double*)take(2 * (size_t)p.n1 * 8);
-  w->part = (double*)take(wpart * 8);
+  w->htab = (double*)take(3 * (size_t)p.n1 * 8);
+  w->wtab = (double*)take(4 * (size_t)p.n2 * 8);
+  w->part = (double*)take(ADJ_DOT_BLOCKS * 8);
+  w->wpart = (double*)w->ztb;   // the W-step's partials, read before ztb is written
   w->flag = (int*)take(64);
 }
 
@@ -359,9 +424,9 @@ static void happly(const Plan& p, const T* x, double2* out, double a, double c) 
   k_adj_happly<T><<<(unsigned)((total + 255) / 256), 256, 0, p.stream>>>(x, out, p.n1, total, a, c);
 }
 
-static void hsolve(const Plan& p, const AdjWork& w, const double2* x, double2* y) {
+static void hsolve2(const Plan& p, const AdjWork& w, const double2* x0, double2* y0, const double2* x1, double2* y1) {
   const long ncol = (long)p.nb * p.r;
-  k_adj_hsolve<<<(unsigned)((ncol + 63) / 64), 64, 0, p.stream>>>(x, y, p.n1, ncol, p.rho1, w.htab);
+  k_adj_hsolve<<<dim3((unsigned)((ncol + 3) / 4), 2), 256, 0, p.stream>>>(x0, y0, x1, y1, p.n1, ncol, w.htab);
 }
 
 static void herm(const Plan& p, const double2* g, double2* s) {
@@ -387,14 +452,12 @@ void launch_adjoint_step(const Plan& p, const AdjWork& w, const AdjState& in, co
   auto hv = [&](const double2* a) { return view(a, (long)n1 * n2, n2, 1, 0); };     // n1 x n2, [nb][n1][n2]
 
   k_adj_flag_zero<<<1, 64, 0, p.stream>>>(w.flag);
-  k_adj_htab<<<1, 64, 0, p.stream>>>(n1, p.rho1, w.htab);
+  launch_tables64(p, w.wtab, w.htab);
   // W+ in the spatial domain, from its stored spectrum
   launch_tube_inv64(p, SPEC_F32, out.wt, n2, (long)nb * n2, 1, w.w1s, (long)n2 * n3, n3, n1, n2, 1.0 / n3);
   // step 4: W-step adjoint -> z_bar, and the mu, rho2 adjoints
-  const int wblk = (int)(((long)n1 * n3 + 255) / 256);
-  k_adj_wstep<<<wblk, 256, 0, p.stream>>>(w_bar, w.w1s, p.gp, w.zbar, w.cbuf, n1, n2, n3, p.mu, p.rho2, p.gseg,
-                                          w.part);
-  k_adj_reduce2<<<1, 256, 0, p.stream>>>(w.part, wblk, theta, 0, 2);
+  const int wblk = wstep_adjoint(p, w, w_bar);
+  k_adj_reduce2<<<1, 256, 0, p.stream>>>(w.wpart, wblk, theta, 0, 2);
   // step 3: Z~_bar = ifft(Z_bar) on the stored frequencies; X~+_bar += Z~_bar Y~+^*,
   // Y~+_bar += X~+^* Z~_bar
   launch_tube_fwd64(p, w.zbar, w.ztb, (long)n1 * n2, n2, 1, (long)n2 * n3, n3, n1, n2, 1.0 / n3);
@@ -429,8 +492,7 @@ void launch_adjoint_step(const Plan& p, const AdjWork& w, const AdjState& in, co
   inv(p, w, w.gy, w.gyi);
   gemm(p, n1, r, n2, one, Wt, ctr(Y), zero, w.a, (long)r * n1, 1, n1);
   gemm(p, n1, r, r, one, xv(w.a), gv(w.gyi), zero, w.pp, (long)r * n1, 1, n1);
-  hsolve(p, w, w.pp, w.q);
-  hsolve(p, w, w.qb, w.pb);
+  hsolve2(p, w, w.pp, w.q, w.qb, w.pb);
   happly<double2>(p, w.q, w.dt, 0.0, 1.0);
   wdot_add(p, w, w.pb, w.dt, (long)r * n1, -1.0, theta, 1);
   gemm(p, n1, r, r, one, xv(w.pb), ctr(gv(w.gyi)), zero, w.ab, (long)r * n1, 1, n1);
