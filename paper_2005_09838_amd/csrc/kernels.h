@@ -145,7 +145,7 @@ struct AdjWork {         // adjoint scratch carved from the caller's adjoint wor
   double2 *ztb, *wtb;
   double2 *x1b, *hx1, *a, *pp, *q, *pb, *qb, *ab, *dt;
   double2 *y1b, *bm, *bb, *rb;
-  double2 *gy, *gyi, *gx, *gxi, *gyib, *gxib, *gyb, *gxb, *S, *T, *tmp;
+  double2 *gy, *gyi, *gx, *gxi, *gyib, *gxib, *gyb, *gxb, *S, *T;
   double *htab, *wtab;   // pivot tables in FP64
   double *part, *wpart;
   int* flag;

@@ -17,8 +17,7 @@
 // the bin weights c_b.  The W-step's adjoint solves the same tridiagonal system restricted
 // to the unobserved entries of each row (i, :, k) (K_{mu rho2} is symmetric).
 //
-// Simple building blocks, chosen for clarity over speed (this is not the iteration's hot
-// path): a batched complex GEMM on 16 x 16 LDS tiles over strided views (FP32 forward
+// The parts: a batched complex GEMM on the FP64 matrix cores over strided views (FP32 forward
 // values or FP64 adjoints), tridiagonal H_rho1 applications and solves along n1, the FP64
 // tube transforms, FP64 Gram inverses by the library's Hermitian pseudo-inverse, and
 // fixed-order reductions for the weights' adjoints.
@@ -28,49 +27,128 @@
 namespace tctf {
 
 // ---------------------------------------------------------------- batched complex GEMM
-__device__ __forceinline__ cd ld_view(const CView& v, int b, long i, long j) {
-  const long e = (long)b * v.bs + i * v.rs + j * v.cs;
-  cd z;
-  if (v.f32) {
+template <bool F32>
+__device__ __forceinline__ cd ld_view(const CView& v, long e) {
+  if constexpr (F32) {
     const float2 f = ((const float2*)v.p)[e];
-    z = cd_make(f.x, f.y);
+    return cd_make(f.x, f.y);
   } else {
     const double2 d = ((const double2*)v.p)[e];
-    z = cd_make(d.x, d.y);
+    return cd_make(d.x, d.y);
   }
-  if (v.conj) z.im = -z.im;
-  return z;
 }
 
-// C = alpha A B + beta C for every batch b (blockIdx.z); A is M x K, B is K x N, C is M x N
-// FP64 complex at C + b cbs + i crs + j ccs.  beta = 0 does not read C.
-__global__ void __launch_bounds__(256) k_zgemm64(int M, int N, int K, cd alpha, CView A, CView B, cd beta,
-                                                 double2* __restrict__ C, long cbs, long crs, long ccs) {
-  __shared__ cd As[16][17];
-  __shared__ cd Bs[16][17];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4, b = blockIdx.z;
-  const int i = blockIdx.y * 16 + ty, j = blockIdx.x * 16 + tx;
-  cd acc = cd_make(0.0, 0.0);
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    As[ty][tx] = (i < M && k0 + tx < K) ? ld_view(A, b, i, k0 + tx) : cd_make(0.0, 0.0);
-    Bs[ty][tx] = (k0 + ty < K && j < N) ? ld_view(B, b, k0 + ty, j) : cd_make(0.0, 0.0);
-    __syncthreads();
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// C = alpha A B + beta D for every batch b (blockIdx.z); A is M x K, B is K x N, C and D are M x N
+// FP64 complex at b cbs + i crs + j ccs (D may be C; beta = 0 does not read it).
+//
+// A wavefront forms a 16 x 16 tile on the FP64 matrix cores, 16 of K (four steps of four products)
+// per turn with the turn's eight loads in flight at once and no LDS: lane (m, q) holds A(m, 4 s + q)
+// and B(4 s + q, m).  The products of this file are small (the tiles of M x N are fewer than the
+// compute units) and latency bounds them, so where K > 64 the NW = 8 wavefronts of a block share a
+// tile's K and their sums are added in LDS in a fixed order; else a block's four wavefronts take
+// four tiles along N.  The products of one step at 144 x 288 x 28, r 8: 3.6 to 7.9 us, 6.0 on
+// average (10.4 on 16 x 16 LDS tiles with two barriers per 16 of K).
+struct Gemm64 {
+  int M, N, K;
+  cd alpha, beta;
+  CView A, B;
+  const double2* D;
+  double2* C;
+  long cbs, crs, ccs;
+};
+__device__ __forceinline__ void gemm64_out(const Gemm64& g, int b, int i, int j, cd acc) {
+  if (i >= g.M || j >= g.N) return;
+  const long e = (long)b * g.cbs + (long)i * g.crs + (long)j * g.ccs;
+  cd v = cd_mul(g.alpha, acc);
+  if (g.beta.re != 0.0 || g.beta.im != 0.0) v = cd_add(v, cd_mul(g.beta, cd_make(g.D[e].x, g.D[e].y)));
+  g.C[e] = make_double2(v.re, v.im);
+}
+
+template <bool AF, bool BF, bool SPLIT>
+__global__ void __launch_bounds__(SPLIT ? 512 : 256) k_zgemm64(Gemm64 g) {
+  constexpr int NW = SPLIT ? 8 : 1;   // wavefronts on one tile's K
+  __shared__ double sums[SPLIT ? 8 * 256 * 2 : 1];
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, m = lane & 15, q = lane >> 4, b = blockIdx.z;
+  const int i0 = blockIdx.y * 16, j0 = (SPLIT ? blockIdx.x : blockIdx.x * 4 + wid) * 16;
+  const long ra = b * g.A.bs + min(i0 + m, g.M - 1) * g.A.rs, rb = b * g.B.bs + min(j0 + m, g.N - 1) * g.B.cs;
+  const double ca = g.A.conj ? -1.0 : 1.0, cb = g.B.conj ? -1.0 : 1.0;
+  v4d re = {0.0, 0.0, 0.0, 0.0}, im = re;
+  for (int k0 = 16 * (SPLIT ? wid : 0); k0 < g.K; k0 += 16 * NW) {
+    cd x[4], y[4];
 #pragma unroll
-    for (int kk = 0; kk < 16; ++kk) cd_fma(acc, As[ty][kk], Bs[kk][tx]);
-    __syncthreads();
+    for (int s = 0; s < 4; ++s) {
+      const int k = min(k0 + 4 * s + q, g.K - 1);
+      x[s] = ld_view<AF>(g.A, ra + k * g.A.cs);
+      y[s] = ld_view<BF>(g.B, rb + k * g.B.rs);
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      if (k0 + 4 * s < g.K) {
+        const bool in = k0 + 4 * s + q < g.K;
+        const double xr = in ? x[s].re : 0.0, xi = in ? ca * x[s].im : 0.0;
+        const double yr = in ? y[s].re : 0.0, yi = in ? cb * y[s].im : 0.0;
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(xr, yr, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(xr, yi, im, 0, 0, 0);
+        re = __builtin_amdgcn_mfma_f64_16x16x4f64(-xi, yi, re, 0, 0, 0);
+        im = __builtin_amdgcn_mfma_f64_16x16x4f64(xi, yr, im, 0, 0, 0);
+      }
+    }
   }
-  if (i < M && j < N) {
-    double2* c = C + (long)b * cbs + (long)i * crs + (long)j * ccs;
-    cd v = cd_mul(alpha, acc);
-    if (beta.re != 0.0 || beta.im != 0.0) v = cd_add(v, cd_mul(beta, cd_make(c->x, c->y)));
-    *c = make_double2(v.re, v.im);
+  if constexpr (SPLIT) {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {   // row q + 4 t, column m
+      const int e = (q + 4 * t) * 16 + m;
+      sums[2 * (wid * 256 + e)] = re[t];
+      sums[2 * (wid * 256 + e) + 1] = im[t];
+    }
+    __syncthreads();
+    if (threadIdx.x < 256) {
+      const int f = threadIdx.x, i = g.crs == 1 ? f & 15 : f >> 4, j = g.crs == 1 ? f >> 4 : f & 15;
+      cd acc = cd_make(0.0, 0.0);
+#pragma unroll
+      for (int w = 0; w < 8; ++w) {
+        const int e = 2 * (w * 256 + i * 16 + j);
+        acc = cd_add(acc, cd_make(sums[e], sums[e + 1]));
+      }
+      gemm64_out(g, b, i0 + i, j0 + j, acc);
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < 4; ++t) gemm64_out(g, b, i0 + q + 4 * t, j0 + m, cd_make(re[t], im[t]));
   }
 }
 
-static void gemm(const Plan& p, int M, int N, int K, cd alpha, CView A, CView B, cd beta, double2* C, long cbs,
-                 long crs, long ccs) {
-  dim3 grid((N + 15) / 16, (M + 15) / 16, p.nb);
-  k_zgemm64<<<grid, 256, 0, p.stream>>>(M, N, K, alpha, A, B, beta, C, cbs, crs, ccs);
+template <bool AF, bool BF>
+static void gemm64(const Plan& p, const Gemm64& g) {
+  const unsigned tm = (g.M + 15) / 16, tn = (g.N + 15) / 16;
+  if (g.K > 64) k_zgemm64<AF, BF, true><<<dim3(tn, tm, p.nb), 512, 0, p.stream>>>(g);
+  else k_zgemm64<AF, BF, false><<<dim3((tn + 3) / 4, tm, p.nb), 256, 0, p.stream>>>(g);
+}
+static void gemm_add(const Plan& p, int M, int N, int K, cd alpha, CView A, CView B, cd beta, const double2* D, double2* C,
+                     long cbs, long crs, long ccs) {
+  Gemm64 g;
+  g.M = M;
+  g.N = N;
+  g.K = K;
+  g.alpha = alpha;
+  g.beta = beta;
+  g.A = A;
+  g.B = B;
+  g.D = D;
+  g.C = C;
+  g.cbs = cbs;
+  g.crs = crs;
+  g.ccs = ccs;
+  if (A.f32 && B.f32) gemm64<true, true>(p, g);
+  else if (A.f32) gemm64<true, false>(p, g);
+  else if (B.f32) gemm64<false, true>(p, g);
+  else gemm64<false, false>(p, g);
+}
+static void gemm(const Plan& p, int M, int N, int K, cd alpha, CView A, CView B, cd beta, double2* C, long cbs, long crs,
+                 long ccs) {
+  gemm_add(p, M, N, K, alpha, A, B, beta, C, C, cbs, crs, ccs);
 }
 
 static CView view(const void* ptr, long bs, long rs, long cs, int f32) {
@@ -92,42 +170,59 @@ static CView ctr(CView v) {   // conjugate transpose of a view
 }
 
 // ---------------------------------------------------------------- elementwise helpers
-__global__ void k_adj_axpby(long n, double a, const double2* __restrict__ x, double b, double2* y, double2* out) {
+// The step length's share of an adjoint: u <- (1 - eta) a, v <- eta a for a: [nb][per] complex, after
+// the imaginary parts of the real frequencies (b = 0 and the Nyquist bin) are set to 0 (the forward
+// update does this to its results, and the map is its own adjoint).
+__global__ void k_adj_split(const double2* __restrict__ a, long per, int nb, int n3, double eta, double2* __restrict__ u,
+                            double2* __restrict__ v) {
   const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n) return;
-  const double2 xv = x[e];
-  double2 v = make_double2(a * xv.x, a * xv.y);
-  if (b != 0.0) {
-    const double2 yv = y[e];
-    v.x += b * yv.x;
-    v.y += b * yv.y;
+  if (e >= per * nb) return;
+  double2 x = a[e];
+  if (bin_is_real((int)(e / per), n3)) x.y = 0.0;
+  u[e] = make_double2((1.0 - eta) * x.x, (1.0 - eta) * x.y);
+  v[e] = make_double2(eta * x.x, eta * x.y);
+}
+static void split(const Plan& p, const double2* a, long per, double2* u, double2* v) {
+  k_adj_split<<<(unsigned)((per * p.nb + 255) / 256), 256, 0, p.stream>>>(a, per, p.nb, p.n3, p.eta, u, v);
+}
+
+// The inverse's rule on the r x r adjoints, one block per frequency: G_bar = -C^* C_bar C^* and
+// S = G_bar + G_bar^*, C = G^{-1}.
+__global__ void __launch_bounds__(256) k_adj_gram(const double2* __restrict__ gi, const double2* __restrict__ gib,
+                                                  double2* __restrict__ gb, double2* __restrict__ s, int r) {
+  extern __shared__ __align__(16) unsigned char sm[];
+  const int rr = r * r;
+  cd* c = (cd*)sm;
+  cd* x = c + rr;
+  cd* y = x + rr;
+  const long o = (long)blockIdx.x * rr;
+  for (int e = threadIdx.x; e < rr; e += blockDim.x) {
+    c[e] = cd_make(gi[o + e].x, gi[o + e].y);
+    x[e] = cd_make(gib[o + e].x, gib[o + e].y);
   }
-  out[e] = v;
+  __syncthreads();
+  for (int e = threadIdx.x; e < rr; e += blockDim.x) {   // C^* C_bar
+    const int i = e / r, j = e % r;
+    cd acc = cd_make(0.0, 0.0);
+    for (int k = 0; k < r; ++k) cd_fma(acc, cd_make(c[k * r + i].re, -c[k * r + i].im), x[k * r + j]);
+    y[e] = acc;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < rr; e += blockDim.x) {   // times -C^*
+    const int i = e / r, j = e % r;
+    cd acc = cd_make(0.0, 0.0);
+    for (int k = 0; k < r; ++k) cd_fma(acc, y[i * r + k], cd_make(-c[j * r + k].re, c[j * r + k].im));
+    x[e] = acc;
+    gb[o + e] = make_double2(acc.re, acc.im);
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < rr; e += blockDim.x) {
+    const cd u = x[e], v = x[(e % r) * r + e / r];
+    s[o + e] = make_double2(u.re + v.re, u.im - v.im);
+  }
 }
-static void axpby(const Plan& p, long n, double a, const double2* x, double b, double2* y, double2* out) {
-  k_adj_axpby<<<(unsigned)((n + 255) / 256), 256, 0, p.stream>>>(n, a, x, b, y, out);
-}
-
-// Imaginary parts of the real frequencies (b = 0 and the Nyquist bin) set to 0: the forward
-// update does this to its results, and the map is its own adjoint.  a: [nb][per] complex.
-__global__ void k_adj_realbins(double2* a, long per, int nb, int n3) {
-  const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= per) return;
-  a[e].y = 0.0;
-  if (n3 % 2 == 0 && nb - 1 == n3 / 2 && nb > 1) a[(long)(nb - 1) * per + e].y = 0.0;
-}
-static void realbins(const Plan& p, double2* a, long per) {
-  k_adj_realbins<<<(unsigned)((per + 255) / 256), 256, 0, p.stream>>>(a, per, p.nb, p.n3);
-}
-
-// S = G + G^* per frequency (r x r)
-__global__ void k_adj_herm(const double2* __restrict__ g, double2* __restrict__ s, int r, int nb) {
-  const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const long rr = (long)r * r;
-  if (e >= rr * nb) return;
-  const long b = e / rr, k = e % rr, i = k / r, j = k % r;
-  const double2 u = g[e], v = g[b * rr + j * r + i];
-  s[e] = make_double2(u.x + v.x, u.y - v.y);
+static void gram_adjoint(const Plan& p, const double2* gi, const double2* gib, double2* gb, double2* s) {
+  k_adj_gram<<<p.nb, 256, 3 * (size_t)p.r * p.r * sizeof(cd), p.stream>>>(gi, gib, gb, s, p.r);
 }
 
 // out(b, s, i) = (a + c deg_i) x_i - c (x_{i-1} + x_{i+1}) along n1 for X-shaped arrays
@@ -376,7 +471,7 @@ size_t adjoint_work_bytes(const Plan& p) {
   const size_t N = (size_t)p.n1 * p.n2 * p.n3, nh = (size_t)p.nb * p.n1 * p.n2;
   const size_t fx = (size_t)p.nb * p.r * p.n1, fy = (size_t)p.nb * p.r * p.n2, g = (size_t)p.nb * p.r * p.r;
   auto al = [](size_t b) { return (b + 255) & ~(size_t)255; };
-  return 2 * al(N * 8) + 2 * al(nh * 16) + 9 * al(fx * 16) + 4 * al(fy * 16) + 11 * al(g * 16) +
+  return 2 * al(N * 8) + 2 * al(nh * 16) + 9 * al(fx * 16) + 4 * al(fy * 16) + 10 * al(g * 16) +
          al(3 * (size_t)p.n1 * 8) + al(4 * (size_t)p.n2 * 8) + al(ADJ_DOT_BLOCKS * 8) + al(64);
 }
 
@@ -393,7 +488,7 @@ void adjoint_carve(const Plan& p, void* ws, AdjWork* w) {
   for (auto q : xs) *q = (double2*)take(fx * 16);
   double2** ys[4] = {&w->y1b, &w->bm, &w->bb, &w->rb};
   for (auto q : ys) *q = (double2*)take(fy * 16);
-  double2** gs[11] = {&w->gy, &w->gyi, &w->gx, &w->gxi, &w->gyib, &w->gxib, &w->gyb, &w->gxb, &w->S, &w->T, &w->tmp};
+  double2** gs[10] = {&w->gy, &w->gyi, &w->gx, &w->gxi, &w->gyib, &w->gxib, &w->gyb, &w->gxb, &w->S, &w->T};
   for (auto q : gs) *q = (double2*)take(g * 16);
   w->htab = (double*)take(3 * (size_t)p.n1 * 8);
   w->wtab = (double*)take(4 * (size_t)p.n2 * 8);
@@ -429,17 +524,10 @@ static void hsolve2(const Plan& p, const AdjWork& w, const double2* x0, double2*
   k_adj_hsolve<<<dim3((unsigned)((ncol + 3) / 4), 2), 256, 0, p.stream>>>(x0, y0, x1, y1, p.n1, ncol, w.htab);
 }
 
-static void herm(const Plan& p, const double2* g, double2* s) {
-  const long n = (long)p.nb * p.r * p.r;
-  k_adj_herm<<<(unsigned)((n + 255) / 256), 256, 0, p.stream>>>(g, s, p.r, p.nb);
-}
-
 void launch_adjoint_step(const Plan& p, const AdjWork& w, const AdjState& in, const AdjState& out, double2* xt_bar,
                          double2* yt_bar, double* w_bar, double* theta) {
   const int n1 = p.n1, n2 = p.n2, n3 = p.n3, r = p.r, nb = p.nb;
-  const long fx = (long)nb * r * n1, fy = (long)nb * r * n2;
-  const cd one = cd_make(1.0, 0.0), zero = cd_make(0.0, 0.0), mone = cd_make(-1.0, 0.0);
-  const double eta = p.eta;
+  const cd one = cd_make(1.0, 0.0), zero = cd_make(0.0, 0.0);
   // matrix views of the forward values (FP32): X [nb][r][n1] as n1 x r, Y [nb][r][n2] as
   // r x n2, W~ [n1][nb][n2] as n1 x n2
   const CView X = view(in.xt, (long)r * n1, 1, n1, 1), Y = view(in.yt, (long)r * n2, n2, 1, 1);
@@ -461,33 +549,25 @@ void launch_adjoint_step(const Plan& p, const AdjWork& w, const AdjState& in, co
   // step 3: Z~_bar = ifft(Z_bar) on the stored frequencies; X~+_bar += Z~_bar Y~+^*,
   // Y~+_bar += X~+^* Z~_bar
   launch_tube_fwd64(p, w.zbar, w.ztb, (long)n1 * n2, n2, 1, (long)n2 * n3, n3, n1, n2, 1.0 / n3);
-  axpby(p, fx, 1.0, xt_bar, 0.0, nullptr, w.x1b);
-  axpby(p, fy, 1.0, yt_bar, 0.0, nullptr, w.y1b);
-  gemm(p, n1, r, n2, one, hv(w.ztb), ctr(Y1), one, w.x1b, (long)r * n1, 1, n1);
-  gemm(p, r, n2, n1, one, ctr(X1), hv(w.ztb), one, w.y1b, (long)r * n2, n2, 1);
+  gemm_add(p, n1, r, n2, one, hv(w.ztb), ctr(Y1), one, xt_bar, w.x1b, (long)r * n1, 1, n1);
+  gemm_add(p, r, n2, n1, one, ctr(X1), hv(w.ztb), one, yt_bar, w.y1b, (long)r * n2, n2, 1);
   // step 2: Y~+ = (1 - eta) Y~ + eta G_X^{-1} B,  B = X~+^* W~,  G_X = X~+^* H_rho1 X~+
-  realbins(p, w.y1b, (long)r * n2);
-  axpby(p, fy, 1.0 - eta, w.y1b, 0.0, nullptr, yt_bar);
-  axpby(p, fy, eta, w.y1b, 0.0, nullptr, w.rb);
+  split(p, w.y1b, (long)r * n2, yt_bar, w.rb);
   happly<float2>(p, (const float2*)out.xt, w.hx1, 1.0, p.rho1);
   gemm(p, r, r, n1, one, ctr(X1), xv(w.hx1), zero, w.gx, (long)r * r, r, 1);
   inv(p, w, w.gx, w.gxi);
   gemm(p, r, n2, n1, one, ctr(X1), Wt, zero, w.bm, (long)r * n2, n2, 1);
   gemm(p, r, r, n2, one, yv(w.rb), ctr(yv(w.bm)), zero, w.gxib, (long)r * r, r, 1);
   gemm(p, r, n2, r, one, ctr(gv(w.gxi)), yv(w.rb), zero, w.bb, (long)r * n2, n2, 1);
-  gemm(p, r, r, r, one, ctr(gv(w.gxi)), gv(w.gxib), zero, w.tmp, (long)r * r, r, 1);
-  gemm(p, r, r, r, mone, gv(w.tmp), ctr(gv(w.gxi)), zero, w.gxb, (long)r * r, r, 1);
+  gram_adjoint(p, w.gxi, w.gxib, w.gxb, w.S);
   gemm(p, n1, r, n2, one, Wt, ctr(yv(w.bb)), one, w.x1b, (long)r * n1, 1, n1);
   gemm(p, n1, n2, r, one, X1, yv(w.bb), zero, w.wtb, (long)n1 * n2, n2, 1);
-  herm(p, w.gxb, w.S);
   gemm(p, n1, r, r, one, xv(w.hx1), gv(w.S), one, w.x1b, (long)r * n1, 1, n1);
   happly<float2>(p, (const float2*)out.xt, w.dt, 0.0, 1.0);
   gemm(p, r, r, n1, one, ctr(X1), xv(w.dt), zero, w.T, (long)r * r, r, 1);
   wdot_add(p, w, w.gxb, w.T, (long)r * r, 1.0, theta, 1);
   // step 1: X~+ = (1 - eta) X~ + eta Q,  Q = H_rho1^{-1} P,  P = A G_Y^{-1},  A = W~ Y~^*
-  realbins(p, w.x1b, (long)r * n1);
-  axpby(p, fx, 1.0 - eta, w.x1b, 0.0, nullptr, xt_bar);
-  axpby(p, fx, eta, w.x1b, 0.0, nullptr, w.qb);
+  split(p, w.x1b, (long)r * n1, xt_bar, w.qb);
   gemm(p, r, r, n2, one, Y, ctr(Y), zero, w.gy, (long)r * r, r, 1);
   inv(p, w, w.gy, w.gyi);
   gemm(p, n1, r, n2, one, Wt, ctr(Y), zero, w.a, (long)r * n1, 1, n1);
@@ -497,11 +577,9 @@ void launch_adjoint_step(const Plan& p, const AdjWork& w, const AdjState& in, co
   wdot_add(p, w, w.pb, w.dt, (long)r * n1, -1.0, theta, 1);
   gemm(p, n1, r, r, one, xv(w.pb), ctr(gv(w.gyi)), zero, w.ab, (long)r * n1, 1, n1);
   gemm(p, r, r, n1, one, ctr(xv(w.a)), xv(w.pb), zero, w.gyib, (long)r * r, r, 1);
-  gemm(p, r, r, r, one, ctr(gv(w.gyi)), gv(w.gyib), zero, w.tmp, (long)r * r, r, 1);
-  gemm(p, r, r, r, mone, gv(w.tmp), ctr(gv(w.gyi)), zero, w.gyb, (long)r * r, r, 1);
+  gram_adjoint(p, w.gyi, w.gyib, w.gyb, w.S);
   gemm(p, n1, n2, r, one, xv(w.ab), Y, one, w.wtb, (long)n1 * n2, n2, 1);
   gemm(p, r, n2, n1, one, ctr(xv(w.ab)), Wt, one, yt_bar, (long)r * n2, n2, 1);
-  herm(p, w.gyb, w.S);
   gemm(p, r, n2, r, one, gv(w.S), Y, one, yt_bar, (long)r * n2, n2, 1);
   // step 7 of the previous iteration: W~ = dft(W), so W_bar = sum_b c_b Re(omega^{-b l} W~_bar_b)
   launch_tube_inv64(p, SPEC_F64, w.wtb, (long)n1 * n2, n2, 1, w_bar, (long)n2 * n3, n3, n1, n2, 1.0);
