@@ -10,42 +10,69 @@ size_t wt_elem_bytes(const Plan& p) { return p.mixed ? 4 : 8; }
 // be finite); unobserved ones become NaNs carrying their index into the pivot table
 // (section 3.3: the equality constraints of the W-step are eliminated row by row, leaving
 // one tridiagonal system per run of unobserved entries).  seg: the order (packed_g_at).
-__global__ void k_pack_g(const float* __restrict__ g, const uint8_t* __restrict__ om,
-                         float* __restrict__ gp, int n1, int n2, int n3, int seg, int* flag) {
-  const long row = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (row >= (long)n1 * n3) return;
-  const long i = row / n3, k = row % n3;
-  int run_start = -1;          // index of the first unobserved entry of the current run
-  bool seen_obs = false;
-  // packed_g_at without its divisions: column j is column u of segment s
-  const int lf = seg ? n2 / seg : 0, rem = seg ? n2 % seg : 0;
-  float* row_out = gp + (size_t)i * n2 * n3;
-  int s = 0, u = 0;
-  for (int j = 0; j < n2; ++j) {
-    const long idx = (i * n2 + j) * n3 + k;
-    const size_t at = seg == 0 ? (size_t)j * n3 + k : (u < lf ? (size_t)(u * n3 + k) * seg + s : (size_t)lf * n3 * seg + (size_t)k * rem + s);
-    if (++u == lf + (s < rem ? 1 : 0)) {
-      u = 0;
-      ++s;
-    }
-    if (om[idx]) {
-      const float v = g[idx];
-      if (!isfinite(v)) atomicOr(flag, 1);
-      row_out[at] = v;
-      seen_obs = true;
-      run_start = -1;
-    } else {
-      if (run_start < 0) run_start = j;
-      const uint32_t table = (j == n2 - 1 ? 2u : 0u) + (seen_obs ? 1u : 0u);
-      row_out[at] = __uint_as_float(pack_unobserved(table * (uint32_t)n2 + (uint32_t)(j - run_start)));
+//
+// Block (x, i): S = 2^ls segments of at most 16 columns of the rows (i, :, k), k = x KB .. + KB,
+// KB = 256 / S, a thread per (segment, row): its entries are in flight at once, and the last
+// observed column before the segment comes from the other segments' through LDS.
+// 144 x 288 x 28: 11.4 us (186 with a thread per row).
+__global__ void __launch_bounds__(256) k_pack_g(const float* __restrict__ g, const uint8_t* __restrict__ om,
+                                                float* __restrict__ gp, int n2, int n3, int seg, int ls, int* flag) {
+  constexpr int L = 16;
+  __shared__ int last[256];
+  const int KB = 256 >> ls, tid = threadIdx.x, s = tid >> (8 - ls), kk = tid & (KB - 1), k = blockIdx.x * KB + kk;
+  const int kc = min(k, n3 - 1), len = (n2 + (1 << ls) - 1) >> ls, j0 = s * len, cnt = k < n3 ? min(len, n2 - j0) : 0;
+  const size_t row = (size_t)blockIdx.y * n2 * n3;
+  float v[L];
+  uint8_t o[L];
+#pragma unroll
+  for (int u = 0; u < L; ++u) {
+    const size_t at = row + (size_t)min(j0 + u, n2 - 1) * n3 + kc;
+    v[u] = g[at];
+    o[u] = om[at];
+  }
+  int prev = -1;   // the last observed column so far
+#pragma unroll
+  for (int u = 0; u < L; ++u)
+    if (u < cnt && o[u]) prev = j0 + u;
+  last[tid] = prev;
+  __syncthreads();
+  prev = -1;
+  for (int t = kk; t < s * KB; t += KB) prev = max(prev, last[t]);
+  // packed_g_at with one division: column j is column c of the slice kernel's segment q
+  const int lf = seg ? n2 / seg : 0, rem = seg ? n2 % seg : 0, cut = rem * (lf + 1);
+  const int jf = min(j0, n2 - 1);
+  int q = 0, c = 0;
+  if (seg) {
+    q = jf < cut ? jf / (lf + 1) : rem + (jf - cut) / lf;
+    c = jf < cut ? jf - q * (lf + 1) : jf - cut - (q - rem) * lf;
+  }
+#pragma unroll
+  for (int u = 0; u < L; ++u) {
+    if (u < cnt) {
+      const int j = j0 + u;
+      const size_t at = seg == 0 ? (size_t)j * n3 + k
+                                 : (c < lf ? (size_t)(c * n3 + k) * seg + q : (size_t)lf * n3 * seg + (size_t)k * rem + q);
+      if (++c == lf + (q < rem ? 1 : 0)) {
+        c = 0;
+        ++q;
+      }
+      if (o[u]) {
+        if (!isfinite(v[u])) atomicOr(flag, 1);
+        gp[row + at] = v[u];
+        prev = j;
+      } else {
+        const uint32_t table = (j == n2 - 1 ? 2u : 0u) + (prev >= 0 ? 1u : 0u);
+        gp[row + at] = __uint_as_float(pack_unobserved(table * (uint32_t)n2 + (uint32_t)(j - prev - 1)));
+      }
     }
   }
 }
 
 void launch_pack_g(const Plan& p, const float* G, const uint8_t* omega) {
-  const long rows = (long)p.n1 * p.n3;
-  k_pack_g<<<(unsigned)((rows + 255) / 256), 256, 0, p.stream>>>(G, omega, p.gp, p.n1, p.n2, p.n3, p.gseg,
-                                                                  p.flag);
+  int ls = 0;
+  while (((p.n2 + (1 << ls) - 1) >> ls) > 16) ++ls;   // n2 <= 1024: ls <= 6
+  const int KB = 256 >> ls;
+  k_pack_g<<<dim3((p.n3 + KB - 1) / KB, p.n1), 256, 0, p.stream>>>(G, omega, p.gp, p.n2, p.n3, p.gseg, ls, p.flag);
 }
 
 // Reciprocal pivots of the W-step row systems (eq. (subquKKT)), in FP64 then rounded.
