@@ -7,6 +7,7 @@
 #include <cstdarg>
 #include <cstdio>
 #include <array>
+#include <cstddef>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -691,6 +692,55 @@ static int state_regions(tctf_ctx* c, Region* r) {
   return n;
 }
 
+static StateHeader state_header(tctf_ctx* c) {
+  const Plan& p = c->plan;
+  StateHeader h;
+  std::memset(&h, 0, sizeof(h));
+  h.magic = kStateMagic;
+  h.n1 = p.n1; h.n2 = p.n2; h.n3 = p.n3; h.r = p.r; h.precision = c->prm.precision;
+  h.iters = c->iters;
+  return h;
+}
+
+// The regions of a blob to copy by one launch: memory of the context's device, the whole blob in one
+// allocation and its words aligned.  Any other address goes by copy calls, which report what is wrong.
+static bool state_in_one_launch(tctf_ctx* c, const unsigned char* blob) {
+  hipPointerAttribute_t at;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  hipError_t e = hipPointerGetAttributes(&at, blob);
+  if (e == hipSuccess) e = hipMemGetAddressRange(&base, &size, (hipDeviceptr_t)blob);
+  if (e != hipSuccess) (void)hipGetLastError();
+  return e == hipSuccess && at.type == hipMemoryTypeDevice && at.device == c->device && ((uintptr_t)blob & 3u) == 0 &&
+         blob + c->lay.state_bytes <= (const unsigned char*)base + size;
+}
+
+// to_blob: the state and its header to the blob; else the state from the blob, but in one launch only
+// if the blob's header names this problem.
+static tctf_status copy_state(tctf_ctx* c, unsigned char* blob, bool one_launch, bool to_blob) {
+  const hipStream_t stream = c->plan.stream;
+  const StateHeader h = state_header(c);
+  Region reg[COPY_REGIONS];
+  tctf::CopyRegion cr[COPY_REGIONS];
+  const int n = state_regions(c, reg);
+  size_t off = sizeof(StateHeader);
+  for (int k = 0; k < n; ++k) {
+    unsigned char* w = c->ws + reg[k].off;
+    cr[k] = {to_blob ? w : blob + off, to_blob ? blob + off : w, reg[k].bytes};
+    off += reg[k].bytes;
+  }
+  if (one_launch) {
+    static_assert(sizeof(StateHeader) == 4 * COPY_HEADER_WORDS && offsetof(StateHeader, pad) == 4 * COPY_HEADER_CHECKED,
+                  "the header's words");
+    tctf::launch_copy_regions(c->plan, cr, n, &h, blob, to_blob);
+    return check_launch();
+  }
+  if (to_blob) HIP_TRY(hipMemcpyAsync(blob, &h, sizeof(h), hipMemcpyHostToDevice, stream));
+  for (int k = 0; k < n; ++k) HIP_TRY(hipMemcpyAsync(cr[k].dst, cr[k].src, cr[k].bytes, hipMemcpyDeviceToDevice, stream));
+  HIP_TRY(hipStreamSynchronize(stream));   // h is on this stack
+  return TCTF_OK;
+}
+
 tctf_status tctf_state_bytes(tctf_ctx* c, size_t* bytes) {
   if (!c || !bytes) return fail(TCTF_E_ARG, "NULL argument");
   *bytes = c->lay.state_bytes;
@@ -700,22 +750,10 @@ tctf_status tctf_state_bytes(tctf_ctx* c, size_t* bytes) {
 tctf_status tctf_get_state(tctf_ctx* c, void* dst, size_t bytes) {
   if (!c || !dst) return fail(TCTF_E_ARG, "NULL argument");
   if (bytes < c->lay.state_bytes) return fail(TCTF_E_STATE, "state buffer has %zu bytes, %zu needed", bytes, c->lay.state_bytes);
-  const Plan& p = c->plan;
-  StateHeader h;
-  std::memset(&h, 0, sizeof(h));
-  h.magic = kStateMagic;
-  h.n1 = p.n1; h.n2 = p.n2; h.n3 = p.n3; h.r = p.r; h.precision = c->prm.precision;
-  h.iters = c->iters;
   unsigned char* d = (unsigned char*)dst;
-  HIP_TRY(hipMemcpyAsync(d, &h, sizeof(h), hipMemcpyHostToDevice, p.stream));
-  size_t off = sizeof(h);
-  Region reg[16];
-  const int n = state_regions(c, reg);
-  for (int k = 0; k < n; ++k) {
-    HIP_TRY(hipMemcpyAsync(d + off, c->ws + reg[k].off, reg[k].bytes, hipMemcpyDeviceToDevice, p.stream));
-    off += reg[k].bytes;
-  }
-  HIP_TRY(hipStreamSynchronize(p.stream));
+  const tctf_status s = copy_state(c, d, state_in_one_launch(c, d), true);
+  if (s != TCTF_OK) return s;
+  HIP_TRY(hipStreamSynchronize(c->plan.stream));
   return TCTF_OK;
 }
 
@@ -724,20 +762,16 @@ tctf_status tctf_set_state(tctf_ctx* c, const void* src, size_t bytes) {
   if (bytes < c->lay.state_bytes) return fail(TCTF_E_STATE, "state blob has %zu bytes, %zu needed", bytes, c->lay.state_bytes);
   const Plan& p = c->plan;
   StateHeader h;
-  const unsigned char* s = (const unsigned char*)src;
+  unsigned char* s = (unsigned char*)src;
+  const bool one = state_in_one_launch(c, s);
+  tctf_status st;
+  if (one && (st = copy_state(c, s, true, false)) != TCTF_OK) return st;   // the kernel reads the header too
   HIP_TRY(hipMemcpyAsync(&h, s, sizeof(h), hipMemcpyDeviceToHost, p.stream));
   HIP_TRY(hipStreamSynchronize(p.stream));
   if (h.magic != kStateMagic || h.n1 != p.n1 || h.n2 != p.n2 || h.n3 != p.n3 || h.r != p.r ||
       h.precision != c->prm.precision)
     return fail(TCTF_E_STATE, "state blob belongs to another problem");
-  size_t off = sizeof(h);
-  Region reg[16];
-  const int n = state_regions(c, reg);
-  for (int k = 0; k < n; ++k) {
-    HIP_TRY(hipMemcpyAsync(c->ws + reg[k].off, s + off, reg[k].bytes, hipMemcpyDeviceToDevice, p.stream));
-    off += reg[k].bytes;
-  }
-  HIP_TRY(hipStreamSynchronize(p.stream));
+  if (!one && (st = copy_state(c, s, false, false)) != TCTF_OK) return st;
   c->iters = h.iters;
   c->term_valid = false;
   return TCTF_OK;

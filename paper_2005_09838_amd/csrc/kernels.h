@@ -86,6 +86,18 @@ void launch_tube_fwd64(const Plan& p, const double* in, double2* out, long bs, l
 void launch_roots(const Plan& p);   // p.twg
 void launch_normal(const Plan& p, float* dst, size_t n, uint64_t seed);
 void launch_zero(const Plan& p, void* dst, size_t bytes);
+// n <= COPY_REGIONS copies between the context and a checkpoint blob in one launch; addresses and
+// sizes are multiples of 4 bytes, on the context's device.  to_blob: the header goes to the blob;
+// else nothing is copied unless the first COPY_HEADER_CHECKED words of the blob's are the same.
+#define COPY_REGIONS 16
+#define COPY_HEADER_WORDS 18
+#define COPY_HEADER_CHECKED 7
+struct CopyRegion {
+  const unsigned char* src;
+  unsigned char* dst;
+  size_t bytes;
+};
+void launch_copy_regions(const Plan& p, const CopyRegion* r, int n, const void* header, void* blob, bool to_blob);
 
 // iteration
 enum SliceMode { SLICE_INIT = 0, SLICE_ITER = 1, SLICE_RESULT = 2, SLICE_KKT = 3 };

@@ -1,4 +1,5 @@
-"""Packing of G at the edges of its segments (needs an MI355X)."""
+"""Packing of G and the checkpoint copies at the edges of their segments and alignments (needs an
+MI355X)."""
 import numpy as np
 import pytest
 
@@ -35,3 +36,26 @@ def test_pack_edges(n1, n2, n3, p):
         with pytest.raises(B.TctfError) as e:
             Completion(to_dev(g), to_dev(om), 2, Y0=to_dev(d["Y0"]))
         assert e.value.status == B.TCTF_E_NONFINITE
+
+
+@pytest.mark.parametrize("shift", [0, 8, 4, 2])
+def test_state_copies_at_any_alignment(shift):
+    """Bytes equal to those of an aligned blob, and a bitwise equal continuation from them."""
+    import torch
+    from paper_2005_09838_amd import Completion, binding as B
+    d = make_inputs(7, 9, 5, 2, p=0.4, seed=3, weekly=True, sigma_od=1.0, noise=0.02)   # nb = 3: odd words
+    c = Completion(to_dev(d["G"]), to_dev(d["omega"]), 2, X0=to_dev(d["X0"]), Y0=to_dev(d["Y0"]))
+    c.step(3)
+    ref = c.get_state()
+    n = ref.numel()
+    buf = torch.full((n + 64,), 0x5a, dtype=torch.uint8, device="cuda:0")
+    B.tctf_get_state(c.ctx, buf.data_ptr() + shift, n)
+    used = shift + int(B.tctf_state_bytes(c.ctx))
+    assert torch.equal(buf[shift:used], ref)
+    assert bool((buf[:shift] == 0x5a).all()) and bool((buf[used:] == 0x5a).all())
+    c.step(2)
+    w = c.result(W=True)["W"]
+    B.tctf_set_state(c.ctx, buf.data_ptr() + shift, n)
+    c.step(2)
+    assert torch.equal(c.result(W=True)["W"], w)
+    c.close()
