@@ -34,14 +34,18 @@ __device__ __forceinline__ v4d mfma4d(double a, double b, v4d c) {
 // Real form: Z'[i][2j + c] = sum_kk X'[i][kk] Y'[kk][2j + c] with kk = 2s + d,
 // X'[i][2s + d] = (re, im)_d X~(i, s) and Y' carrying the signs of the complex product:
 // Y'[2s][2j] = Yr, Y'[2s+1][2j] = -Yi, Y'[2s][2j+1] = Yi, Y'[2s+1][2j+1] = Yr.
-// Block: 64 rows x one frequency, 4 wavefronts of 16 rows; Y~ staged in LDS by column
-// chunks of ZG_COLS; each wavefront sweeps its rows across the chunk in groups of 4
-// 16-column tiles.  Output tiles go straight to the interleaved Z~ rows.
+// Block: 64 rows x 32 columns of one frequency, 4 wavefronts of 16 rows; Y~ staged in LDS, each
+// wavefront forms four 16-column tiles, and output tiles go straight to the interleaved Z~ rows.
+// The product writes Z~ and reads little, so it is bound by the stores once enough blocks are
+// there; a block is short enough that its loads, LDS stage and stores are one latency each.  us
+// with 128 / 64 / 32 columns per block: 144 x 288 x 28, r 8 6.7 / 4.8 / 4.0 (12.3 with the 288
+// columns of a row tile in one block); 300 x 120 x 24, r 24 16.7 / 10.3 / 7.0; 529 x 96 x 112, r 16
+// 12.0 / 11.4 / 11.6; 36 x 48 x 7, r 3 4.2 / 4.1 / 3.1.
 // PINV: the first npinv blocks instead form G_Y^+ and I - eta P_Y of frequency blockIdx.x for
 // the next X-step (pinvy_block): independent work that runs beside the product (an instance of
 // its own, since its registers would halve the product's wavefronts).
 #define ZG_ROWS 64
-#define ZG_COLS 128
+#define ZG_COLS 32
 template <int RM, bool PINV>   // r <= RM: every loop below has a compile-time trip count
 __global__ void __launch_bounds__(256) k_zgemm(const float2* __restrict__ xt, const float2* __restrict__ yt,
                                                float2* __restrict__ zt, int n1, int n2, int r, int nb,
@@ -54,21 +58,17 @@ __global__ void __launch_bounds__(256) k_zgemm(const float2* __restrict__ xt, co
     }
   }
   float2* ysh = (float2*)zsm;   // [s][j] of the column chunk
-  const int bid = blockIdx.x - npinv, ntile = (n1 + ZG_ROWS - 1) / ZG_ROWS;
-  const int i0 = (bid % ntile) * ZG_ROWS, b = bid / ntile, tid = threadIdx.x;
+  const int bid = blockIdx.x - npinv, ntile = (n1 + ZG_ROWS - 1) / ZG_ROWS, tb = bid / ntile;
+  const int i0 = (bid % ntile) * ZG_ROWS, b = tb % nb, j0 = tb / nb * ZG_COLS, nc = min(ZG_COLS, n2 - j0), tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6, m = lane & 15, q = lane >> 4;
   constexpr int KS = RM / 2;   // K steps of 4 over 2r <= 2 RM
   constexpr int YPER = RM * ZG_COLS / 256;
-  float2 yv[YPER];   // this thread's share of a Y~ column chunk, loaded ahead of its LDS store
-  auto load_y = [&](int j0) {
-    const int nc = min(ZG_COLS, n2 - j0);
+  float2 yv[YPER];   // this thread's share of the block's Y~ columns, loaded ahead of its LDS store
 #pragma unroll
-    for (int u = 0; u < YPER; ++u) {
-      const int e = tid + 256 * u, s = e / ZG_COLS, jj = e % ZG_COLS;
-      yv[u] = ld_or(yt, ((size_t)b * r + s) * n2 + j0 + jj, s < r && jj < nc, make_float2(0.f, 0.f));
-    }
-  };
-  load_y(0);
+  for (int u = 0; u < YPER; ++u) {
+    const int e = tid + 256 * u, s = e / ZG_COLS, jj = e % ZG_COLS;
+    yv[u] = ld_or(yt, ((size_t)b * r + s) * n2 + j0 + jj, s < r && jj < nc, make_float2(0.f, 0.f));
+  }
   // A operands for every K step: X'[row][4 ks + q] (0 past the ends; loads clamped in range)
   const int row = i0 + 16 * w + m;
   float a[KS];
@@ -84,50 +84,40 @@ __global__ void __launch_bounds__(256) k_zgemm(const float2* __restrict__ xt, co
   const int d = q & 1;
   float* zf = (float*)zt;
   const bool vec4 = (n2 & 1) == 0;   // rows start 16-byte aligned
-  for (int j0 = 0; j0 < n2; j0 += ZG_COLS) {
-    const int nc = min(ZG_COLS, n2 - j0);
-    if (j0 > 0) {
-      __syncthreads();   // every wavefront is done with the previous chunk
-      load_y(j0);
+#pragma unroll
+  for (int u = 0; u < YPER; ++u) ysh[tid + 256 * u] = yv[u];
+  __syncthreads();
+  v4f acc[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) acc[u] = v4f{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    const int s = min((4 * ks + q) >> 1, r - 1);   // rows past 2r meet a zero A operand
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int cpar = u & 1;
+      const int jj = 2 * m + (u >> 1);
+      const float2 y = ysh[s * ZG_COLS + jj];
+      const float bv = (d == 1 && cpar == 0) ? -y.y : (d != cpar ? y.y : y.x);
+      acc[u] = mfma4(a[ks], bv, acc[u]);
     }
+  }
+  const int col = 4 * m;   // first of this lane's four floats of the block's 2 nc
+  if (col < 2 * nc) {
 #pragma unroll
-    for (int u = 0; u < YPER; ++u) ysh[tid + 256 * u] = yv[u];
-    __syncthreads();
-    const int ntiles = (2 * nc + 15) / 16;
-    for (int nt0 = 0; nt0 < ntiles; nt0 += 4) {
-      v4f acc[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) acc[u] = v4f{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        const int s = min((4 * ks + q) >> 1, r - 1);   // rows past 2r meet a zero A operand
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int cpar = u & 1;
-          const int jj = min(8 * nt0 + 2 * m + (u >> 1), ZG_COLS - 1);
-          const float2 y = ysh[s * ZG_COLS + jj];
-          const float bv = (d == 1 && cpar == 0) ? -y.y : (d != cpar ? y.y : y.x);
-          acc[u] = mfma4(a[ks], bv, acc[u]);
-        }
-      }
-      const int col = 16 * nt0 + 4 * m;   // first of this lane's four floats in the chunk's 2 nc
-      if (col < 2 * nc) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int i = i0 + 16 * w + 4 * q + t;
-          if (i < n1) {
-            float* dst = zf + (((size_t)i * nb + b) * n2 + j0) * 2 + col;
-            if (col + 4 <= 2 * nc) {
-              if (vec4) {
-                *(float4*)dst = make_float4(acc[0][t], acc[1][t], acc[2][t], acc[3][t]);
-              } else {
-                ((float2*)dst)[0] = make_float2(acc[0][t], acc[1][t]);
-                ((float2*)dst)[1] = make_float2(acc[2][t], acc[3][t]);
-              }
-            } else {   // 2 nc is even: the last two floats of the row
-              *(float2*)dst = make_float2(acc[0][t], acc[1][t]);
-            }
+    for (int t = 0; t < 4; ++t) {
+      const int i = i0 + 16 * w + 4 * q + t;
+      if (i < n1) {
+        float* dst = zf + (((size_t)i * nb + b) * n2 + j0) * 2 + col;
+        if (col + 4 <= 2 * nc) {
+          if (vec4) {
+            *(float4*)dst = make_float4(acc[0][t], acc[1][t], acc[2][t], acc[3][t]);
+          } else {
+            ((float2*)dst)[0] = make_float2(acc[0][t], acc[1][t]);
+            ((float2*)dst)[1] = make_float2(acc[2][t], acc[3][t]);
           }
+        } else {   // 2 nc is even: the last two floats of the row
+          *(float2*)dst = make_float2(acc[0][t], acc[1][t]);
         }
       }
     }
@@ -167,21 +157,17 @@ __global__ void __launch_bounds__(256) k_zgemm_bf(const float2* __restrict__ xt,
     }
   }
   uint2* ysh = (uint2*)zsm;   // [s][j] of the column chunk: (re, im) split words
-  const int bid = blockIdx.x - npinv, ntile = (n1 + ZG_ROWS - 1) / ZG_ROWS;
-  const int i0 = (bid % ntile) * ZG_ROWS, b = bid / ntile, tid = threadIdx.x;
+  const int bid = blockIdx.x - npinv, ntile = (n1 + ZG_ROWS - 1) / ZG_ROWS, tb = bid / ntile;
+  const int i0 = (bid % ntile) * ZG_ROWS, b = tb % nb, j0 = tb / nb * ZG_COLS, nc = min(ZG_COLS, n2 - j0), tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6, m = lane & 15, q = lane >> 4;
   constexpr int KC = RM / 8;   // 16-deep K chunks over 2 RM
   constexpr int YPER = RM * ZG_COLS / 256;
   float2 yv[YPER];
-  auto load_y = [&](int j0) {
-    const int nc = min(ZG_COLS, n2 - j0);
 #pragma unroll
-    for (int u = 0; u < YPER; ++u) {
-      const int e = tid + 256 * u, s = e / ZG_COLS, jj = e % ZG_COLS;
-      yv[u] = ld_or(yt, ((size_t)b * r + s) * n2 + j0 + jj, s < r && jj < nc, make_float2(0.f, 0.f));
-    }
-  };
-  load_y(0);
+  for (int u = 0; u < YPER; ++u) {
+    const int e = tid + 256 * u, s = e / ZG_COLS, jj = e % ZG_COLS;
+    yv[u] = ld_or(yt, ((size_t)b * r + s) * n2 + j0 + jj, s < r && jj < nc, make_float2(0.f, 0.f));
+  }
   // A operands: X~(row, s0), X~(row, s0 + 1) of each chunk, split
   const int row = i0 + 16 * w + m;
   v4s ahi[KC], alo[KC];
@@ -201,60 +187,50 @@ __global__ void __launch_bounds__(256) k_zgemm_bf(const float2* __restrict__ xt,
   }
   float* zf = (float*)zt;
   const bool vec4 = (n2 & 1) == 0;   // rows start 16-byte aligned
-  for (int j0 = 0; j0 < n2; j0 += ZG_COLS) {
-    const int nc = min(ZG_COLS, n2 - j0);
-    if (j0 > 0) {
-      __syncthreads();   // every wavefront is done with the previous chunk
-      load_y(j0);
-    }
 #pragma unroll
-    for (int u = 0; u < YPER; ++u) ysh[tid + 256 * u] = make_uint2(bf16_split(yv[u].x), bf16_split(yv[u].y));
-    __syncthreads();
-    const int ntiles = (2 * nc + 15) / 16;
-    for (int nt0 = 0; nt0 < ntiles; nt0 += 4) {
-      v4f acc[4];
+  for (int u = 0; u < YPER; ++u) ysh[tid + 256 * u] = make_uint2(bf16_split(yv[u].x), bf16_split(yv[u].y));
+  __syncthreads();
+  v4f acc[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) acc[u] = v4f{0.f, 0.f, 0.f, 0.f};
+  for (int u = 0; u < 4; ++u) acc[u] = v4f{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int c = 0; c < KC; ++c) {
-        const int s0 = 8 * c + 2 * q;   // rows past r are zero in the chunk
+  for (int c = 0; c < KC; ++c) {
+    const int s0 = 8 * c + 2 * q;   // rows past r are zero in the chunk
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int jj = min(8 * nt0 + 2 * m + (u >> 1), ZG_COLS - 1);
-          const uint2 y0 = ysh[s0 * ZG_COLS + jj], y1 = ysh[(s0 + 1) * ZG_COLS + jj];   // (re, im) split words
-          v4s bh, bl;
-          if (u & 1) {   // column 2 j + 1: (Yi, Yr, Yi', Yr')
-            bh = v4s{(short)(y0.y & 0xffffu), (short)(y0.x & 0xffffu), (short)(y1.y & 0xffffu), (short)(y1.x & 0xffffu)};
-            bl = v4s{(short)(y0.y >> 16), (short)(y0.x >> 16), (short)(y1.y >> 16), (short)(y1.x >> 16)};
-          } else {       // column 2 j: (Yr, -Yi, Yr', -Yi')
-            bh = v4s{(short)(y0.x & 0xffffu), (short)((y0.y & 0xffffu) ^ 0x8000u), (short)(y1.x & 0xffffu),
-                     (short)((y1.y & 0xffffu) ^ 0x8000u)};
-            bl = v4s{(short)(y0.x >> 16), (short)((y0.y >> 16) ^ 0x8000u), (short)(y1.x >> 16),
-                     (short)((y1.y >> 16) ^ 0x8000u)};
-          }
-          acc[u] = mfma16bf(alo[c], bh, acc[u]);
-          acc[u] = mfma16bf(ahi[c], bl, acc[u]);
-          acc[u] = mfma16bf(ahi[c], bh, acc[u]);
-        }
+    for (int u = 0; u < 4; ++u) {
+      const int jj = 2 * m + (u >> 1);
+      const uint2 y0 = ysh[s0 * ZG_COLS + jj], y1 = ysh[(s0 + 1) * ZG_COLS + jj];   // (re, im) split words
+      v4s bh, bl;
+      if (u & 1) {   // column 2 j + 1: (Yi, Yr, Yi', Yr')
+        bh = v4s{(short)(y0.y & 0xffffu), (short)(y0.x & 0xffffu), (short)(y1.y & 0xffffu), (short)(y1.x & 0xffffu)};
+        bl = v4s{(short)(y0.y >> 16), (short)(y0.x >> 16), (short)(y1.y >> 16), (short)(y1.x >> 16)};
+      } else {       // column 2 j: (Yr, -Yi, Yr', -Yi')
+        bh = v4s{(short)(y0.x & 0xffffu), (short)((y0.y & 0xffffu) ^ 0x8000u), (short)(y1.x & 0xffffu),
+                 (short)((y1.y & 0xffffu) ^ 0x8000u)};
+        bl = v4s{(short)(y0.x >> 16), (short)((y0.y >> 16) ^ 0x8000u), (short)(y1.x >> 16),
+                 (short)((y1.y >> 16) ^ 0x8000u)};
       }
-      const int col = 16 * nt0 + 4 * m;   // first of this lane's four floats in the chunk's 2 nc
-      if (col < 2 * nc) {
+      acc[u] = mfma16bf(alo[c], bh, acc[u]);
+      acc[u] = mfma16bf(ahi[c], bl, acc[u]);
+      acc[u] = mfma16bf(ahi[c], bh, acc[u]);
+    }
+  }
+  const int col = 4 * m;   // first of this lane's four floats of the block's 2 nc
+  if (col < 2 * nc) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          const int i = i0 + 16 * w + 4 * q + t;
-          if (i < n1) {
-            float* dst = zf + (((size_t)i * nb + b) * n2 + j0) * 2 + col;
-            if (col + 4 <= 2 * nc) {
-              if (vec4) {
-                *(float4*)dst = make_float4(acc[0][t], acc[1][t], acc[2][t], acc[3][t]);
-              } else {
-                ((float2*)dst)[0] = make_float2(acc[0][t], acc[1][t]);
-                ((float2*)dst)[1] = make_float2(acc[2][t], acc[3][t]);
-              }
-            } else {
-              *(float2*)dst = make_float2(acc[0][t], acc[1][t]);
-            }
+    for (int t = 0; t < 4; ++t) {
+      const int i = i0 + 16 * w + 4 * q + t;
+      if (i < n1) {
+        float* dst = zf + (((size_t)i * nb + b) * n2 + j0) * 2 + col;
+        if (col + 4 <= 2 * nc) {
+          if (vec4) {
+            *(float4*)dst = make_float4(acc[0][t], acc[1][t], acc[2][t], acc[3][t]);
+          } else {
+            ((float2*)dst)[0] = make_float2(acc[0][t], acc[1][t]);
+            ((float2*)dst)[1] = make_float2(acc[2][t], acc[3][t]);
           }
+        } else {
+          *(float2*)dst = make_float2(acc[0][t], acc[1][t]);
         }
       }
     }
@@ -270,28 +246,27 @@ void zgemm_set_attr(int r) {
   }
 }
 
+template <int RM>
+static void zgemm(const Plan& p, int npinv) {
+  const int grid = npinv + (p.n1 + ZG_ROWS - 1) / ZG_ROWS * p.nb * ((p.n2 + ZG_COLS - 1) / ZG_COLS);
+  size_t lds = (size_t)RM * ZG_COLS * sizeof(float2);
+  if (npinv && pinv_lds_bytes(p.r) > lds) lds = pinv_lds_bytes(p.r);
+  const auto k = p.mixed ? (npinv ? k_zgemm_bf<RM, true> : k_zgemm_bf<RM, false>)
+                         : (npinv ? k_zgemm<RM, true> : k_zgemm<RM, false>);
+  k<<<grid, 256, lds, p.stream>>>(p.xt, p.yt, p.zt, p.n1, p.n2, p.r, p.nb, npinv, pinvy_args(p));
+}
+
+// with_pinv: G_Y^+ too, in the product's launch while its blocks are two per compute unit or
+// fewer, in a launch before it beyond: there the product's blocks wait behind rounds of inverses
+// and run at their occupancy.  One iteration in us, together / apart: 288 x 28 x 144 78.1 / 82.0,
+// 12 x 12 x 1008 56.4 / 57.4, 12 x 12 x 2016 74.6 / 70.1, 12 x 12 x 8064 201.5 / 171.4.
 void launch_zgemm(const Plan& p, int with_pinv) {
-  const int npinv = with_pinv ? p.nb : 0;
-  const int grid = npinv + (p.n1 + ZG_ROWS - 1) / ZG_ROWS * p.nb;
-  const int rm = p.r <= 8 ? 8 : (p.r <= 16 ? 16 : 32);
-  size_t lds = (size_t)rm * ZG_COLS * sizeof(float2);
-  if (with_pinv && pinv_lds_bytes(p.r) > lds) lds = pinv_lds_bytes(p.r);
-  const PinvyArgs pa = pinvy_args(p);
-#define TCTF_ZGEMM_P(K, RM)                                                                                   \
-  do {                                                                                                        \
-    if (npinv) K<RM, true><<<grid, 256, lds, p.stream>>>(p.xt, p.yt, p.zt, p.n1, p.n2, p.r, p.nb, npinv, pa); \
-    else K<RM, false><<<grid, 256, lds, p.stream>>>(p.xt, p.yt, p.zt, p.n1, p.n2, p.r, p.nb, npinv, pa);      \
-  } while (0)
-#define TCTF_ZGEMM(RM)                      \
-  do {                                      \
-    if (p.mixed) TCTF_ZGEMM_P(k_zgemm_bf, RM); \
-    else TCTF_ZGEMM_P(k_zgemm, RM);         \
-  } while (0)
-  if (p.r <= 8) TCTF_ZGEMM(8);
-  else if (p.r <= 16) TCTF_ZGEMM(16);
-  else TCTF_ZGEMM(32);
-#undef TCTF_ZGEMM
-#undef TCTF_ZGEMM_P
+  const bool apart = with_pinv && p.nb > 512;
+  if (apart) launch_pinvy(p, p.stream);
+  const int npinv = with_pinv && !apart ? p.nb : 0;
+  if (p.r <= 8) zgemm<8>(p, npinv);
+  else if (p.r <= 16) zgemm<16>(p, npinv);
+  else zgemm<32>(p, npinv);
 }
 
 // ---------------------------------------------------------------- A = W~ Y~^* and the X-update

@@ -1,8 +1,9 @@
 """The products of the iteration at the edges of their tiles (needs an MI355X), each run against
 the FP64 oracle with the tolerances of the parity tests."""
+import numpy as np
 import pytest
 
-from tests.gpu_helpers import gpu_run, make_inputs, oracle_run
+from tests.gpu_helpers import gpu_run, make_inputs, oracle_run, rel
 from tests.test_gpu_parity import _compare
 
 pytestmark = pytest.mark.gpu
@@ -55,3 +56,26 @@ def test_gram_and_product_edges(n1, n2, n3, r, pinv_mode):
     g = gpu_run(d, r, 4, pinv_mode=pinv_mode)
     st, info = oracle_run(d, r, 4, history=True)
     _compare(g, st, info, label=f"{n1}x{n2}x{n3} r{r}")
+
+
+@pytest.mark.parametrize("n1,n2,n3,r", [
+    (63, 31, 5, 3),      # one block per frequency, its last column missing; odd rows
+    (64, 32, 6, 8),      # one full block
+    (65, 33, 7, 9),      # a row and a column over; odd rows
+    (1, 1, 4, 1),
+    (130, 66, 3, 17),    # even rows whose last block holds two columns
+    (40, 96, 1, 32),     # the largest rank
+])
+@pytest.mark.parametrize("precision", ["fp32", "mixed"])
+def test_factor_product_edges(n1, n2, n3, r, precision):
+    """Z = X * Y of the initial factors.  A term of the product is rounded by 2^-24 in FP32 and
+    by 2^-16 where the factors are split into BF16 parts; the sums and the two transforms of
+    either add less than 8 such roundings in norm."""
+    rng = np.random.default_rng(n1 + n2 + n3 + r)
+    d = make_inputs(n1, n2, n3, r, p=0.5, seed=n1 + n2, weekly=True, sigma_od=1.0, noise=0.02)
+    d["X0"] = rng.normal(size=(n1, r, n3)).astype(np.float32)
+    print(f"{n1}x{n2}x{n3} r{r} {precision}", flush=True)
+    g = gpu_run(d, r, 0, precision=precision, want=("Z",))
+    ref = np.einsum("irk,rjk->ijk", np.fft.fft(d["X0"].astype(float)), np.fft.fft(d["Y0"].astype(float)))
+    assert rel(g["Z"], np.fft.ifft(ref).real) <= 8 * (2.0**-24 if precision == "fp32" else 2.0**-16)
+    g["ctx"].close()
