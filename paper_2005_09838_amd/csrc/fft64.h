@@ -48,6 +48,44 @@ __device__ __forceinline__ void dft_small(cd (&v)[R], double sg) {
       v[k] = cd_add(e[k], o[k]);
       v[k + 4] = cd_sub(e[k], o[k]);
     }
+  } else if constexpr (R == 9) {   // 3 x 3 with twiddles: n = 3 n1 + n2, k = k1 + 3 k2
+    constexpr double C9[5] = {1.0, 0.766044443118978, 0.17364817766693041, 0.0, -0.9396926207859083}, S9[5] = {0.0, 0.6427876096865393, 0.984807753012208, 0.0, 0.3420201433256689};   // exp(2 pi i e / 9), e = n2 k1
+    cd t[3][3];
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+#pragma unroll
+      for (int a = 0; a < 3; ++a) t[b][a] = v[3 * a + b];
+      dft_small<3>(t[b], sg);
+#pragma unroll
+      for (int k = 1; k < 3; ++k)
+        if (b > 0) t[b][k] = cmul2(t[b][k], cd_make(C9[b * k], sg * S9[b * k]));
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      cd u[3] = {t[0][k], t[1][k], t[2][k]};
+      dft_small<3>(u, sg);
+#pragma unroll
+      for (int l = 0; l < 3; ++l) v[k + 3 * l] = u[l];
+    }
+  } else if constexpr (R == 6 || R == 10 || R == 12) {   // coprime factors need no twiddles
+    constexpr int A = R == 6 ? 3 : (R == 10 ? 5 : 3), B = R / A;
+    constexpr int EA = R == 6 ? 4 : (R == 10 ? 6 : 4), EB = R == 6 ? 3 : (R == 10 ? 5 : 9);   // 1 mod A, 0 mod B and the reverse
+    cd t[B][A];
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+#pragma unroll
+      for (int a = 0; a < A; ++a) t[b][a] = v[(B * a + A * b) % R];
+      dft_small<A>(t[b], sg);
+    }
+#pragma unroll
+    for (int k = 0; k < A; ++k) {
+      cd u[B];
+#pragma unroll
+      for (int b = 0; b < B; ++b) u[b] = t[b][k];
+      dft_small<B>(u, sg);
+#pragma unroll
+      for (int l = 0; l < B; ++l) v[(EA * k + EB * l) % R] = u[l];
+    }
   } else {   // odd R through the sums and differences of the pairs (q, R - q)
     constexpr int H = (R - 1) / 2;
     // cos and sin of 2 pi k / R, k = 1..H
@@ -98,16 +136,21 @@ __device__ __forceinline__ void fft64_pass(cd* x, int N, int P, int Ns, const cd
     if (f < tot) {
       const int pr = fft64_div(f, rnr), j = f - pr * nr, jd = fft64_div(j, rns), jm = j - jd * Ns;
       const cd* src = x + pr * N + j;
-      cd w = tw[jm * step];
-      w.im *= sg;
       at[h] = pr * N + jd * Ns * R + jm;
 #pragma unroll
       for (int r = 0; r < R; ++r) v[h][r] = src[r * nr];
-      cd p = w;
+      if (Ns > 1) {   // powers of the twiddle as an even and an odd chain
+        cd w = tw[jm * step];
+        w.im *= sg;
+        const cd w2 = cmul2(w, w);
+        cd po = w, pe = w2;
 #pragma unroll
-      for (int r = 1; r < R; ++r) {
-        v[h][r] = cmul2(v[h][r], p);
-        if (r + 1 < R) p = cmul2(p, w);
+        for (int r = 1; r < R; r += 2) {
+          v[h][r] = cmul2(v[h][r], po);
+          if (r + 1 < R) v[h][r + 1] = cmul2(v[h][r + 1], pe);
+          if (r + 2 < R) po = cmul2(po, w2);
+          if (r + 3 < R) pe = cmul2(pe, w2);
+        }
       }
       dft_small<R>(v[h], sg);
     }
@@ -163,15 +206,19 @@ __device__ inline void fft64(cd* x, int P, const Fft64Plan& pl, const cd* tw, do
   int Ns = 1;
   __syncthreads();
   for (int k = 0; k < pl.passes; ++k) {
-    const int R = pl.radix[k];
+    const int R = pl.radix[k], N = pl.n;
     switch (R) {
-      case 2: fft64_pass<2>(x, pl.n, P, Ns, tw, sg); break;
-      case 3: fft64_pass<3>(x, pl.n, P, Ns, tw, sg); break;
-      case 4: fft64_pass<4>(x, pl.n, P, Ns, tw, sg); break;
-      case 5: fft64_pass<5>(x, pl.n, P, Ns, tw, sg); break;
-      case 7: fft64_pass<7>(x, pl.n, P, Ns, tw, sg); break;
-      case 8: fft64_pass<8>(x, pl.n, P, Ns, tw, sg); break;
-      default: fft64_pass_any(x, pl.n, P, R, Ns, tw, sg); break;
+      case 2: fft64_pass<2>(x, N, P, Ns, tw, sg); break;
+      case 3: fft64_pass<3>(x, N, P, Ns, tw, sg); break;
+      case 4: fft64_pass<4>(x, N, P, Ns, tw, sg); break;
+      case 5: fft64_pass<5>(x, N, P, Ns, tw, sg); break;
+      case 6: fft64_pass<6>(x, N, P, Ns, tw, sg); break;
+      case 7: fft64_pass<7>(x, N, P, Ns, tw, sg); break;
+      case 8: fft64_pass<8>(x, N, P, Ns, tw, sg); break;
+      case 9: fft64_pass<9>(x, N, P, Ns, tw, sg); break;
+      case 10: fft64_pass<10>(x, N, P, Ns, tw, sg); break;
+      case 12: fft64_pass<12>(x, N, P, Ns, tw, sg); break;
+      default: fft64_pass_any(x, N, P, R, Ns, tw, sg); break;
     }
     Ns *= R;
   }

@@ -7,20 +7,36 @@
 
 namespace tctf {
 
+// The fewest passes over the radices of dft_small (of two such plans the one with the smaller
+// largest radix), prime factors past 7 as passes of their own.  Odd radices first: the first pass
+// writes its outputs R apart, which an even R would put into few LDS banks.
+static void fft64_factor(int n, int cap, int* cur, int depth, int* best, int* passes) {
+  if (depth >= *passes) return;
+  if (n == 1) {
+    *passes = depth;
+    for (int k = 0; k < depth; ++k) best[k] = cur[k];
+    return;
+  }
+  for (int r : {12, 10, 9, 8, 7, 6, 5, 4, 3, 2})
+    if (r <= cap && n % r == 0) {
+      cur[depth] = r;
+      fft64_factor(n / r, r, cur, depth + 1, best, passes);
+    }
+}
 Fft64Plan fft64_plan(int n) {
   Fft64Plan pl;
   pl.n = n;
   pl.passes = 0;
-  for (int r : {8, 7, 5, 4, 3, 2})
-    while (n % r == 0 && n > 1) {
+  for (int r = 11; r <= n; r += 2)
+    while (n % r == 0 && r % 3 && r % 5 && r % 7) {   // what is left of r's smaller factors is gone: r is prime
       pl.radix[pl.passes++] = r;
       n /= r;
     }
-  for (int r = 11; n > 1; r += 2)
-    while (n % r == 0) {
-      pl.radix[pl.passes++] = r;
-      n /= r;
-    }
+  int cur[FFT64_MAX_PASSES], best[FFT64_MAX_PASSES], passes = FFT64_MAX_PASSES;
+  fft64_factor(n, 12, cur, 0, best, &passes);
+  for (int odd = 1; odd >= 0; --odd)
+    for (int k = 0; k < passes; ++k)
+      if ((best[k] & 1) == odd) pl.radix[pl.passes++] = best[k];
   return pl;
 }
 
@@ -44,35 +60,44 @@ __device__ __forceinline__ void spec_store(void* out, size_t at, double re, doub
 // roots of unity unless the caller's table holds them.  A sequence carries two tubes: on the
 // inverse C[k] = A[k] + i B[k] over the conjugate-symmetric extension of both spectra, on the
 // forward A = (C[k] + conj C[N - k]) / 2, B = (C[k] - conj C[N - k]) / (2 i).  What bounds it:
-// LDS traffic and the barriers of the passes (12 x 12 x 8064: 29.6 us for 72 blocks of one pair,
-// 13.9 ms as direct sums; 288 x 28 x 144: 16.7 us, direct 115).
+// LDS traffic and the barriers of the passes (12 x 12 x 8064: 25.3 us for 72 blocks of one pair and
+// four passes, 29.6 with six of radices up to 8, 13.9 ms as direct sums; 288 x 28 x 144: 10.9 us
+// with two passes, 16.7 with four and twice the values per block, direct 115).  NT: at most 256
+// threads hold a butterfly of 12 in registers, 1024 would not at the others' expense.
 struct Tube64 {
   long bs, ps, qs;   // strides of the spectrum
   long sp, sq;       // strides of the spatial tubes
   int Q, PP;
+  int lds_tw;          // the roots are in LDS
   double s;
-  const double2* tw;   // exp(2 pi i e / n3), or NULL: formed in LDS
+  const double2* tw;   // exp(2 pi i e / n3), or NULL
 };
-__device__ __forceinline__ const cd* tube64_roots(const Tube64& t, cd* x, int N) {
-  if (t.tw) return (const cd*)t.tw;
-  cd* w = x + t.PP * N;
+// The roots of unity: in LDS behind the sequences (from the caller's table, or formed), or the table
+// itself where a sequence leaves no room.
+__device__ __forceinline__ const cd* tube64_roots(const Tube64& t, cd* w, int N) {
+  if (!t.lds_tw) return (const cd*)t.tw;
   for (int e = threadIdx.x; e < N; e += blockDim.x) {
     double sn, c;
-    sincospi(2.0 * e / N, &sn, &c);
+    if (t.tw) {
+      c = t.tw[e].x;
+      sn = t.tw[e].y;
+    } else {
+      sincospi(2.0 * e / N, &sn, &c);
+    }
     w[e] = cd_make(c, sn);
   }
   return w;
 }
 
-template <int KIND, typename T>
-__global__ void __launch_bounds__(1024) k_tube64_inv(const void* __restrict__ in, T* __restrict__ out, T* __restrict__ out2,
+template <int KIND, typename T, int NT>
+__global__ void __launch_bounds__(NT) k_tube64_inv(const void* __restrict__ in, T* __restrict__ out, T* __restrict__ out2,
                                                      Tube64 t, Fft64Plan pl) {
   extern __shared__ __align__(16) unsigned char sm[];
   cd* x = (cd*)sm;
   const int N = pl.n, nb = N / 2 + 1, q0 = 2 * t.PP * blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
   const int nq = min(2 * t.PP, t.Q - q0), np = (nq + 1) >> 1;
   const float rp = 1.0f / np, rn = 1.0f / N;
-  const cd* tw = tube64_roots(t, x, N);
+  const cd* tw = tube64_roots(t, x + t.PP * N, N);
   for (int e = tid; e < nb * np; e += nt) {
     const int b = fft64_div(e, rp), pp = e - b * np;
     const size_t at = b * t.bs + blockIdx.y * t.ps + (q0 + 2 * pp) * t.qs;
@@ -94,15 +119,15 @@ __global__ void __launch_bounds__(1024) k_tube64_inv(const void* __restrict__ in
   }
 }
 
-template <int KIND, typename T>
-__global__ void __launch_bounds__(1024) k_tube64_fwd(const T* __restrict__ in, void* __restrict__ out, Tube64 t, Fft64Plan pl,
+template <int KIND, typename T, int NT>
+__global__ void __launch_bounds__(NT) k_tube64_fwd(const T* __restrict__ in, void* __restrict__ out, Tube64 t, Fft64Plan pl,
                                                      const uint32_t* __restrict__ ctr) {
   extern __shared__ __align__(16) unsigned char sm[];
   cd* x = (cd*)sm;
   const int N = pl.n, nb = N / 2 + 1, q0 = 2 * t.PP * blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
   const int nq = min(2 * t.PP, t.Q - q0), np = (nq + 1) >> 1;
   const float rp = 1.0f / np, rn = 1.0f / N;
-  const cd* tw = tube64_roots(t, x, N);
+  const cd* tw = tube64_roots(t, x + t.PP * N, N);
   for (int e = tid; e < np * N; e += nt) {
     const int pp = fft64_div(e, rn), k = e - pp * N;
     const size_t at = blockIdx.y * t.sp + (q0 + 2 * pp) * t.sq + k;
@@ -194,19 +219,19 @@ static int largest_prime(int n) {
 }
 
 // Whether the passes beat the direct sums.  A large prime radix is itself a direct sum, run by one
-// block per few pairs and without the saving of real tubes, so it pays only beside a cofactor,
-// and below 40 entries (24 with radices up to 7) the passes' barriers cost as much as the sums.
-// Both transforms and the W-step in us, direct / passes, for 144 x 28 tubes: of 18 entries
-// 16.0 / 17.4, 22 17.0 / 20.4, 25 17.4 / 16.6, 33 20.3 / 23.2, 44 23.8 / 23.1, 60 31.9 / 19.5,
-// 62 32.0 / 38.5, 93 58.6 / 36.8, 122 88.4 / 63.8, 254 320 / 189, 257 335 / 447, 335 558 / 160;
-// for 100 tubes: 257 60 / 135, 335 74 / 48, 1018 220 / 358; 900 of 2003 5196 / 4490, 40 of 2003
-// 511 / 2282.
+// block per few pairs and without the saving of real tubes, so with no cofactor, or 2, it pays only
+// where the pairs fill the device; and below 40 entries (32 with radices up to 7; 24 where the sums
+// have no table of roots) the passes' barriers cost as much as the sums.  Both transforms and the
+// W-step in us, direct / passes, for 144 x 28 tubes: of 18 entries 13.6 / 15.8, 25 15.2 / 15.8, 30
+// 16.3 / 16.2, 33 19.0 / 21.2, 36 19.3 / 18.4, 44 22.2 / 21.4, 60 30.7 / 19.4, 62 30.6 / 30.6, 67
+// 39.0 / 38.0, 93 56 / 30, 122 86 / 49, 257 331 / 180; for 100 tubes: 257 59 / 76, 335 76 / 33,
+// 1018 221 / 258; for 900: 2003 5206 / 4514, 4093 31876 / 32724; for 40: 2003 512 / 2283.
 static bool tube64_fast(const Plan& p, long pairs) {
   const int n3 = p.n3, lp = largest_prime(n3);
   if (n3 > 1024 && !p.twg) return false;   // the roots would not fit beside the sequence
-  if (lp <= 7) return n3 >= 24;
-  if (n3 / lp == 2) return n3 >= 64 && pairs >= 256;
-  return n3 / lp >= 3 && n3 >= 40;
+  if (lp <= 7) return n3 >= (p.twg ? 32 : 24);
+  if (n3 / lp <= 2) return n3 >= 64 && lp <= 2048 && pairs >= 256;
+  return n3 >= 40;
 }
 
 static Tube64 tube64_args(const Plan& p, long bs, long ps, long qs, long sp, long sq, int Q, double s) {
@@ -223,19 +248,23 @@ static Tube64 tube64_args(const Plan& p, long bs, long ps, long qs, long sp, lon
   return t;
 }
 
-// Pairs per block (up to 2048 values, and at least two blocks per compute unit where there are
-// enough pairs), threads (about four values each) and LDS.
+// Pairs per block (up to 1024 values, and at least two blocks per compute unit where there are
+// enough pairs), threads (four values each) and LDS.  Both transforms and the W-step in us with up
+// to 512 / 1024 / 2048 values: 288 x 28 x 144 34.3 / 31.7 / 39.5, 144 x 28 x 288 42.2 / 35.9 / 45.4,
+// 144 x 288 x 25 104.0 / 104.9 / 110.8; with 2 / 4 / 8 values per thread, of 1024: 12 x 12 x 2016
+// 28.3 / 28.2 / 31.9, 288 x 28 x 144 - / 31.7 / 33.6.
 static dim3 tube64_shape(Tube64* t, int n3, int P, int* threads, size_t* lds) {
   const int per_p = (t->Q + 1) / 2;
   const long pairs = (long)per_p * P;
-  int pp = n3 >= 2048 ? 1 : 2048 / n3;
+  int pp = n3 >= 1024 ? 1 : 1024 / n3;
   if (pp > (pairs + 511) / 512) pp = (int)((pairs + 511) / 512);
   if (pp > per_p) pp = per_p;
   t->PP = pp;
   int nt = ((pp * n3 + 3) / 4 + 63) / 64 * 64;
   if (nt > 1024) nt = 1024;
   *threads = nt;
-  *lds = ((size_t)pp * n3 + (t->tw ? 0 : n3)) * sizeof(cd);
+  t->lds_tw = n3 <= 1024;
+  *lds = ((size_t)pp * n3 + (t->lds_tw ? n3 : 0)) * sizeof(cd);
   return dim3((per_p + pp - 1) / pp, P);
 }
 
@@ -250,9 +279,9 @@ static void tube_inv(const Plan& p, const void* in, T* out, T* out2, Tube64 t, i
   int nt;
   size_t lds;
   const dim3 grid = tube64_shape(&t, p.n3, P, &nt, &lds);
-  if (lds > 65536)
-    (void)hipFuncSetAttribute((const void*)k_tube64_inv<KIND, T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  k_tube64_inv<KIND, T><<<grid, nt, lds, p.stream>>>(in, out, out2, t, fft64_plan(p.n3));
+  const auto k = nt <= 256 ? k_tube64_inv<KIND, T, 256> : k_tube64_inv<KIND, T, 1024>;
+  if (lds > 65536) (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  k<<<grid, nt, lds, p.stream>>>(in, out, out2, t, fft64_plan(p.n3));
 }
 template <int KIND, typename T>
 static void tube_fwd(const Plan& p, const T* in, void* out, Tube64 t, int P) {
@@ -265,9 +294,9 @@ static void tube_fwd(const Plan& p, const T* in, void* out, Tube64 t, int P) {
   int nt;
   size_t lds;
   const dim3 grid = tube64_shape(&t, p.n3, P, &nt, &lds);
-  if (lds > 65536)
-    (void)hipFuncSetAttribute((const void*)k_tube64_fwd<KIND, T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  k_tube64_fwd<KIND, T><<<grid, nt, lds, p.stream>>>(in, out, t, fft64_plan(p.n3), p.ctr);
+  const auto k = nt <= 256 ? k_tube64_fwd<KIND, T, 256> : k_tube64_fwd<KIND, T, 1024>;
+  if (lds > 65536) (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  k<<<grid, nt, lds, p.stream>>>(in, out, t, fft64_plan(p.n3), p.ctr);
 }
 
 // grid.y counts P (n1 <= 8192 or r <= 32)
