@@ -79,8 +79,15 @@ void launch_tube_inv(const Plan& p, int kind, const void* in, long bs, long ps, 
                      long sq, int P, int Q, double s);
 void launch_tube_inv64(const Plan& p, int kind, const void* in, long bs, long ps, long qs, double* out, long sp, long sq,
                        int P, int Q, double s);
-void launch_tube_fwd(const Plan& p, int kind, const float* in, void* out, long bs, long ps, long qs, long sp, long sq, int P,
-                     int Q, double s);
+// rows (part NULL: none): out[p][3] = sums over c of part[p][c][3], for each of the P rows in the
+// same launch; returns whether it did (direct sums have no block per row).
+struct RowSums {
+  const double* part;
+  double* out;
+  int nchunk;
+};
+bool launch_tube_fwd(const Plan& p, int kind, const float* in, void* out, long bs, long ps, long qs, long sp, long sq, int P,
+                     int Q, double s, RowSums rows = RowSums{nullptr, nullptr, 0});
 void launch_tube_fwd64(const Plan& p, const double* in, double2* out, long bs, long ps, long qs, long sp, long sq, int P,
                        int Q, double s);
 void launch_roots(const Plan& p);   // p.twg

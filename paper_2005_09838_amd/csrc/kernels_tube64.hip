@@ -71,6 +71,7 @@ struct Tube64 {
   int lds_tw;          // the roots are in LDS
   double s;
   const double2* tw;   // exp(2 pi i e / n3), or NULL
+  RowSums rows;        // of the rows y, summed by the first block of each (k_tube64_fwd)
 };
 // The roots of unity: in LDS behind the sequences (from the caller's table, or formed), or the table
 // itself where a sequence leaves no room.
@@ -127,6 +128,12 @@ __global__ void __launch_bounds__(NT) k_tube64_fwd(const T* __restrict__ in, voi
   const int N = pl.n, nb = N / 2 + 1, q0 = 2 * t.PP * blockIdx.x, tid = threadIdx.x, nt = blockDim.x;
   const int nq = min(2 * t.PP, t.Q - q0), np = (nq + 1) >> 1;
   const float rp = 1.0f / np, rn = 1.0f / N;
+  if (t.rows.part && blockIdx.x == 0 && tid < 3) {
+    const double* part = t.rows.part + 3 * (size_t)blockIdx.y * t.rows.nchunk + tid;
+    double v = 0.0;
+    for (int c = 0; c < t.rows.nchunk; ++c) v += part[3 * c];
+    t.rows.out[3 * blockIdx.y + tid] = v;
+  }
   const cd* tw = tube64_roots(t, x + t.PP * N, N);
   for (int e = tid; e < np * N; e += nt) {
     const int pp = fft64_div(e, rn), k = e - pp * N;
@@ -245,6 +252,7 @@ static Tube64 tube64_args(const Plan& p, long bs, long ps, long qs, long sp, lon
   t.PP = 1;
   t.s = s;
   t.tw = p.twg;
+  t.rows = {nullptr, nullptr, 0};
   return t;
 }
 
@@ -284,12 +292,12 @@ static void tube_inv(const Plan& p, const void* in, T* out, T* out2, Tube64 t, i
   k<<<grid, nt, lds, p.stream>>>(in, out, out2, t, fft64_plan(p.n3));
 }
 template <int KIND, typename T>
-static void tube_fwd(const Plan& p, const T* in, void* out, Tube64 t, int P) {
+static bool tube_fwd(const Plan& p, const T* in, void* out, Tube64 t, int P) {
   const long pairs = (long)((t.Q + 1) / 2) * P;
   if (!tube64_fast(p, pairs)) {
     const long n = (long)P * t.Q * (p.n3 / 2 + 1);
     k_tube_direct_fwd<KIND, T><<<(unsigned)((n + 255) / 256), 256, 0, p.stream>>>(in, out, t, P, p.n3, p.ctr);
-    return;
+    return false;
   }
   int nt;
   size_t lds;
@@ -297,6 +305,7 @@ static void tube_fwd(const Plan& p, const T* in, void* out, Tube64 t, int P) {
   const auto k = nt <= 256 ? k_tube64_fwd<KIND, T, 256> : k_tube64_fwd<KIND, T, 1024>;
   if (lds > 65536) (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   k<<<grid, nt, lds, p.stream>>>(in, out, t, fft64_plan(p.n3), p.ctr);
+  return true;
 }
 
 // grid.y counts P (n1 <= 8192 or r <= 32)
@@ -312,11 +321,11 @@ void launch_tube_inv64(const Plan& p, int kind, const void* in, long bs, long ps
   if (kind == SPEC_F64) tube_inv<SPEC_F64, double>(p, in, out, (double*)nullptr, t, P);
   else tube_inv<SPEC_F32, double>(p, in, out, (double*)nullptr, t, P);
 }
-void launch_tube_fwd(const Plan& p, int kind, const float* in, void* out, long bs, long ps, long qs, long sp, long sq, int P,
-                     int Q, double s) {
-  const Tube64 t = tube64_args(p, bs, ps, qs, sp, sq, Q, s);
-  if (kind == SPEC_BF16) tube_fwd<SPEC_BF16, float>(p, in, out, t, P);
-  else tube_fwd<SPEC_F32, float>(p, in, out, t, P);
+bool launch_tube_fwd(const Plan& p, int kind, const float* in, void* out, long bs, long ps, long qs, long sp, long sq, int P,
+                     int Q, double s, RowSums rows) {
+  Tube64 t = tube64_args(p, bs, ps, qs, sp, sq, Q, s);
+  t.rows = rows;
+  return kind == SPEC_BF16 ? tube_fwd<SPEC_BF16, float>(p, in, out, t, P) : tube_fwd<SPEC_F32, float>(p, in, out, t, P);
 }
 void launch_tube_fwd64(const Plan& p, const double* in, double2* out, long bs, long ps, long qs, long sp, long sq, int P,
                        int Q, double s) {

@@ -1,7 +1,7 @@
 """The FP64 tube transforms and the W-step of the three-launch slice path (needs an MI355X).
 
 Tubes go through mixed-radix passes in LDS, two real tubes per complex sequence, or through
-direct sums where n3 is short, prime, or twice a prime with few tubes.  Every size runs against
+direct sums where n3 is short, or a prime or twice one with few tubes.  Every size runs against
 the FP64 oracle with the tolerances of the parity tests, through the factor transforms, the
 iteration, the results and the stationarity measures.
 """
@@ -16,16 +16,16 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n1,n2,n3,r,rho2", [
     (2, 1, 98, 1, 1e-2),     # one tube per OD row: its partner is empty
     (3, 5, 22, 2, 0.7),      # direct sums: short
-    (3, 6, 30, 2, 1e-2),     # three short passes
+    (3, 6, 30, 2, 1e-2),     # direct sums with the table, passes for the factors
     (3, 5, 67, 2, 1e-2),     # direct sums: prime
-    (5, 103, 67, 2, 0.7),
+    (5, 103, 67, 2, 0.7),    # the same length as a pass: 260 pairs; W-step segments with a short last one
     (3, 5, 183, 2, 0.7),     # a pass of radix 61
     (3, 5, 134, 2, 1e-2),    # direct sums: twice a prime, few tubes
     (21, 27, 134, 2, 1e-2),  # the same length in passes: 294 pairs
-    (3, 16, 90, 2, 0.7),     # W-step rows of 16 in registers, several pairs per block
+    (3, 16, 90, 2, 0.7),     # a full W-step segment of 16, several pairs per block
     (4, 17, 125, 2, 1e-2),
     (2, 32, 121, 2, 0.7),
-    (3, 33, 256, 2, 0.7),    # chunked W-step rows, a full block of tubes
+    (3, 33, 256, 2, 0.7),    # three W-step segments of 11 in four; a full block of tubes
     (2, 7, 257, 2, 1e-2),    # prime; two W-step blocks per OD row, the second with one row
     (2, 3, 1000, 2, 0.7),    # roots beside the sequence in the factor transforms
     (2, 3, 1331, 2, 1e-2),   # three passes of radix 11
