@@ -77,7 +77,7 @@ def stage_bytes(stage, n1, n2, n3, r, mixed):
 
 STAGE_NAMES = ("slice", "zgemm", "agemm", "hsolve", "bgemm", "ystep", "pinvy")
 # kernel symbol of each stage at this workload (what rocprofv3 lists)
-STAGE_KERNELS = {"slice": "k_slice_coop", "zgemm": "k_zgemm", "agemm": "k_agemm", "hsolve": "k_hsolve_reg",
+STAGE_KERNELS = {"slice": "k_slice", "zgemm": "k_zgemm", "agemm": "k_agemm", "hsolve": "k_hsolve_reg",
                  "bgemm": "k_bgemm", "ystep": "k_ystep", "pinvy": "k_pinvy"}
 
 

@@ -12,18 +12,18 @@ bool slice_supported(int n3) {
   }
 }
 
-static int tube_ld(int n3) {
+static int tube_ld(int n3, bool iter) {
   switch (n3) {
-#define TCTF_CASE(n) case n: return slice_ld<n>();
+#define TCTF_CASE(n) case n: return iter ? slice_ld<n, true>() : slice_ld<n, false>();
     TUBE_DFT_SIZES(TCTF_CASE)
 #undef TCTF_CASE
     default: return 1;
   }
 }
 
-static int tube_threads(int n3) {
+static int tube_threads(int n3, bool iter) {
   switch (n3) {
-#define TCTF_CASE(n) case n: return slice_tube_threads<n>();
+#define TCTF_CASE(n) case n: return iter ? slice_tube_threads<n, true>() : slice_tube_threads<n, false>();
     TUBE_DFT_SIZES(TCTF_CASE)
 #undef TCTF_CASE
     default: return 1;
@@ -41,15 +41,15 @@ bool slice_fused(int n2, int n3) {
   return floats * sizeof(float) + 48 * sizeof(double) + 16 <= TCTF_SLICE_LDS_MAX;
 }
 
-static size_t slice_lds_bytes(int n2, int n3) {
-  size_t floats = (size_t)n2 * (tube_ld(n3) + 4) + 1;
-  if (tube_threads(n3) > 1) floats += 2 * (size_t)(n3 + 1);   // twiddles of the LDS transforms
+static size_t slice_lds_bytes(int n2, int n3, bool iter) {
+  size_t floats = (size_t)n2 * (tube_ld(n3, iter) + 4) + 1;
+  if (tube_threads(n3, iter) > 1) floats += 2 * (size_t)(n3 + 1);   // twiddles of the LDS transforms
   return floats * sizeof(float) + 48 * sizeof(double) + 16;
 }
 
 int slice_default_path(int n2, int n3) {
   if (!slice_fused(n2, n3)) return SPATH_SPLIT;
-  return tube_threads(n3) > 1 ? SPATH_COOP : SPATH_THREAD;
+  return tube_threads(n3, true) > 1 ? SPATH_COOP : SPATH_THREAD;
 }
 
 bool slice_path_valid(int path, int n2, int n3) { return path == SPATH_SPLIT || path == slice_default_path(n2, n3); }
@@ -72,16 +72,20 @@ int slice_segments(int n2, int n3) {
 // 256 / 448 / 640 / 1024 threads: 144 x 288 x 28 13.7 / 9.9 / 9.5 / 10.5, 144 x 96 x 112
 // 18.4 / 15.7 / 15.2 / 16.4; 529 x 96 x 112 28.7 / 33.8 / 41.8 / 45.4, 529 x 288 x 28
 // 20.8 / 21.9 / 27.4 / 29.7.
-static int slice_threads(const Plan& p) {
-  const int tubes = p.n2 * tube_threads(p.n3), items = p.n3 * p.gseg;
+static int slice_threads(const Plan& p, bool iter) {
+  const int tubes = p.n2 * tube_threads(p.n3, iter), items = p.n3 * p.gseg;
   const int need = ((tubes > items ? tubes : items) + 63) / 64 * 64, most = p.n1 <= 256 ? 640 : 256;
   return need < most ? need : most;
 }
 
 size_t slice_launch_lds_bytes(const Plan& p) {
   if (p.spath == SPATH_SPLIT) return 0;
-  const size_t a = slice_lds_bytes(p.n2, p.n3), b = pinv_lds_bytes(p.r);
-  return a > b ? a : b;
+  size_t lds = pinv_lds_bytes(p.r);
+  for (int iter = 0; iter < 2; ++iter) {
+    const size_t a = slice_lds_bytes(p.n2, p.n3, iter != 0);
+    if (a > lds) lds = a;
+  }
+  return lds;
 }
 
 // The kernel of a tube length, segment length (at most 6, 9, 12 or 16 columns) and use.
@@ -138,7 +142,8 @@ void launch_slice(const Plan& p, int mode, float* w_out, float* z_out, int w_fro
   a.mixed = p.mixed;
   a.w_from_g = w_from_g;
   a.nseg = p.gseg;
-  slice_kernel(p.n2, p.n3, mode == SLICE_ITER)<<<p.n1 + a.npinv, slice_threads(p), slice_launch_lds_bytes(p), p.stream>>>(a);
+  slice_kernel(p.n2, p.n3, mode == SLICE_ITER)<<<p.n1 + a.npinv, slice_threads(p, mode == SLICE_ITER), slice_launch_lds_bytes(p),
+                                                        p.stream>>>(a);
 }
 
 }  // namespace tctf

@@ -224,23 +224,28 @@ __device__ __forceinline__ void wstep_rows(float* zs, int LD, const float* tab, 
 
 // Threads per tube: short tubes are transformed by one thread in registers; longer ones by
 // four or eight neighbouring lanes of one wavefront through the tube's LDS row (at most two
-// groups of each four-step stage per lane), so that no stage needs a block barrier.
-template <int N>
+// groups of each four-step stage per lane), so that no stage needs a block barrier.  Outside the
+// iteration (ITER false) short even tubes take the four-step form as well: the rounding of the
+// first W~ to BF16 turns a last FP32 bit of the transform into 2^-8 of an entry, and with this
+// form the first W~ of a mixed-precision run, and a checkpoint of it, keep the bits that they
+// had before the iteration's transforms moved to registers.
+template <int N, bool ITER>
 __host__ __device__ constexpr int slice_tube_threads() {
   constexpr int m1 = TubePlan<N>::M1, m2 = TubePlan<N>::M2;
-  return m1 == 0 || N <= 32 ? 1 : (m1 > 5 && m2 > 5 ? 8 : 4);
+  return m1 == 0 || (ITER && N <= 32) ? 1 : (m1 > 5 && m2 > 5 ? 8 : 4);
 }
 
 // LDS row stride of one tube: odd where one thread owns a tube, so that a run of tubes does not
 // meet in one bank; where lanes share a tube, rows of (re, im) pairs whose stride spreads the
-// tubes of 16 lanes over the 32 banks.
-template <int N>
+// tubes of 16 lanes over the 32 banks (short tubes: the least, within the LDS of the rule on
+// slice sizes).
+template <int N, bool ITER>
 __host__ __device__ constexpr int slice_ld() {
-  constexpr int T = slice_tube_threads<N>();
+  constexpr int T = slice_tube_threads<N, ITER>();
   int ld = (N % 2 == 0) ? N + 3 : N + 2;
   if (T > 1) {
     ld = N + 2;
-    while (T == 8 ? (ld % 32 < 14 || ld % 32 > 22) : ((ld + 2) % 16 < 8)) ld += 2;
+    while (N > 32 && (T == 8 ? (ld % 32 < 14 || ld % 32 > 22) : ((ld + 2) % 16 < 8))) ld += 2;
   }
   return ld;
 }
@@ -275,7 +280,7 @@ __device__ __forceinline__ void load_inverse_tube(const float2* __restrict__ src
 // W-step), 9.5 now; 36 x 48 x 7: 19.2 before, 5.7 now.
 template <int N, int L, bool ITER>
 __global__ void __launch_bounds__(640) k_slice(SliceArgs a) {
-  constexpr int T = slice_tube_threads<N>(), LD = slice_ld<N>(), NB = N / 2 + 1, M = N / 2, PN = (M / 2 + T) / T;
+  constexpr int T = slice_tube_threads<N, ITER>(), LD = slice_ld<N, ITER>(), NB = N / 2 + 1, M = N / 2, PN = (M / 2 + T) / T;
   extern __shared__ __align__(16) float smem[];
   if constexpr (ITER) {
     if ((int)blockIdx.x < a.npinv) {

@@ -16,7 +16,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n1,n2,n3,r,rho2", [
     (2, 1, 98, 1, 1e-2),     # one tube per OD row: its partner is empty
     (3, 5, 22, 2, 0.7),      # direct sums: short
-    (3, 6, 30, 2, 1e-2),     # direct sums with the table, passes for the factors
+    (3, 6, 30, 2, 1e-2),     # direct sums: below the line of small radices
     (3, 5, 67, 2, 1e-2),     # direct sums: prime
     (5, 103, 67, 2, 0.7),    # the same length as a pass: 260 pairs; W-step segments with a short last one
     (3, 5, 183, 2, 0.7),     # a pass of radix 61
