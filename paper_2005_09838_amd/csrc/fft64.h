@@ -123,7 +123,7 @@ __device__ __forceinline__ void dft_small(cd (&v)[R], double sg) {
 // exp(sg 2 pi i r (j mod Ns) / (Ns R)) and writes (j / Ns) Ns R + j mod Ns + r Ns.  Every thread
 // reads all of its butterflies before any thread writes.
 template <int R>
-__device__ __forceinline__ void fft64_pass(cd* x, int N, int P, int Ns, const cd* tw, double sg) {
+__device__ __forceinline__ void fft64_pass(cd* x, int N, int P, int Ns, const cd* tw, int ts, double sg) {
   constexpr int B = (FFT64_PER + R - 1) / R;
   const int tid = threadIdx.x, nt = blockDim.x, nr = N / R, tot = P * nr, step = nr / Ns;   // N / (Ns R)
   const float rnr = 1.0f / nr, rns = 1.0f / Ns;
@@ -140,7 +140,7 @@ __device__ __forceinline__ void fft64_pass(cd* x, int N, int P, int Ns, const cd
 #pragma unroll
       for (int r = 0; r < R; ++r) v[h][r] = src[r * nr];
       if (Ns > 1) {   // powers of the twiddle as an even and an odd chain
-        cd w = tw[jm * step];
+        cd w = tw[jm * step * ts];
         w.im *= sg;
         const cd w2 = cmul2(w, w);
         cd po = w, pe = w2;
@@ -167,7 +167,7 @@ __device__ __forceinline__ void fft64_pass(cd* x, int N, int P, int Ns, const cd
 }
 
 // The same for any radix: output by output, sum_u x_u exp(sg 2 pi i u (jm + t Ns) / (Ns R)).
-__device__ __forceinline__ void fft64_pass_any(cd* x, int N, int P, int R, int Ns, const cd* tw, double sg) {
+__device__ __forceinline__ void fft64_pass_any(cd* x, int N, int P, int R, int Ns, const cd* tw, int ts, double sg) {
   const int tid = threadIdx.x, nt = blockDim.x, nr = N / R, tot = P * N, step = nr / Ns;
   const float rn = 1.0f / N, rnsr = 1.0f / (Ns * R), rns = 1.0f / Ns;
   cd v[FFT64_PER];
@@ -182,7 +182,7 @@ __device__ __forceinline__ void fft64_pass_any(cd* x, int N, int P, int R, int N
       int e = 0;   // u e1 mod N
       cd acc = cd_make(0.0, 0.0);
       for (int u = 0; u < R; ++u) {
-        cd w = tw[e];
+        cd w = tw[e * ts];
         w.im *= sg;
         cd_fma(acc, src[u * nr], w);
         e += e1;
@@ -200,25 +200,25 @@ __device__ __forceinline__ void fft64_pass_any(cd* x, int N, int P, int R, int N
   __syncthreads();
 }
 
-// All passes; x holds the sequences in natural order before and after.  tw[e] = exp(2 pi i e / N).
+// All passes; x holds the sequences in natural order before and after.  tw[ts e] = exp(2 pi i e / N).
 // Begins and ends with a block barrier.
-__device__ inline void fft64(cd* x, int P, const Fft64Plan& pl, const cd* tw, double sg) {
+__device__ inline void fft64(cd* x, int P, const Fft64Plan& pl, const cd* tw, int ts, double sg) {
   int Ns = 1;
   __syncthreads();
   for (int k = 0; k < pl.passes; ++k) {
     const int R = pl.radix[k], N = pl.n;
     switch (R) {
-      case 2: fft64_pass<2>(x, N, P, Ns, tw, sg); break;
-      case 3: fft64_pass<3>(x, N, P, Ns, tw, sg); break;
-      case 4: fft64_pass<4>(x, N, P, Ns, tw, sg); break;
-      case 5: fft64_pass<5>(x, N, P, Ns, tw, sg); break;
-      case 6: fft64_pass<6>(x, N, P, Ns, tw, sg); break;
-      case 7: fft64_pass<7>(x, N, P, Ns, tw, sg); break;
-      case 8: fft64_pass<8>(x, N, P, Ns, tw, sg); break;
-      case 9: fft64_pass<9>(x, N, P, Ns, tw, sg); break;
-      case 10: fft64_pass<10>(x, N, P, Ns, tw, sg); break;
-      case 12: fft64_pass<12>(x, N, P, Ns, tw, sg); break;
-      default: fft64_pass_any(x, N, P, R, Ns, tw, sg); break;
+      case 2: fft64_pass<2>(x, N, P, Ns, tw, ts, sg); break;
+      case 3: fft64_pass<3>(x, N, P, Ns, tw, ts, sg); break;
+      case 4: fft64_pass<4>(x, N, P, Ns, tw, ts, sg); break;
+      case 5: fft64_pass<5>(x, N, P, Ns, tw, ts, sg); break;
+      case 6: fft64_pass<6>(x, N, P, Ns, tw, ts, sg); break;
+      case 7: fft64_pass<7>(x, N, P, Ns, tw, ts, sg); break;
+      case 8: fft64_pass<8>(x, N, P, Ns, tw, ts, sg); break;
+      case 9: fft64_pass<9>(x, N, P, Ns, tw, ts, sg); break;
+      case 10: fft64_pass<10>(x, N, P, Ns, tw, ts, sg); break;
+      case 12: fft64_pass<12>(x, N, P, Ns, tw, ts, sg); break;
+      default: fft64_pass_any(x, N, P, R, Ns, tw, ts, sg); break;
     }
     Ns *= R;
   }

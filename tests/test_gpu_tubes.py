@@ -30,6 +30,10 @@ pytestmark = pytest.mark.gpu
     (2, 3, 1000, 2, 0.7),    # roots beside the sequence in the factor transforms
     (2, 3, 1331, 2, 1e-2),   # three passes of radix 11
     (3, 4, 2187, 2, 0.7),    # seven passes of radix 3
+    (2, 3, 2046, 2, 0.7),    # the longest pairs of few even tubes
+    (2, 3, 2048, 2, 1e-2),   # sequences of half the length
+    (20, 27, 2048, 2, 0.7),  # pairs again: 280
+    (3, 5, 4094, 2, 0.7),    # passes of radix 23 and 89
     (2, 2, 8064, 2, 1e-2),
     (2, 3, 8191, 2, 1e-2),   # the largest prime: direct sums
     (2, 3, 8192, 2, 0.7),    # the longest tube
