@@ -82,7 +82,7 @@ STAGE_KERNELS = {"slice": "k_slice", "zgemm": "k_zgemm", "agemm": "k_agemm", "hs
 
 
 def run_precision(prec, d, w, steps, warmup, dev, torch):
-    """Warm up (the first step call captures the iteration graph, so capture stays outside
+    """Warm up (ten steps or more also capture the iteration graph, which then stays outside
     every timed region); time `steps` iterations as the library runs them (graph replays) on
     the wall clock between two synchronisations; time five more blocks of `steps` iterations
     with HIP events on the library's stream (torch's current stream) and keep their median;
