@@ -11,7 +11,9 @@ size_t wt_elem_bytes(const Plan& p) { return p.mixed ? 4 : 8; }
 // One thread per row (i, k) along mode 2.  Observed entries keep their value (they must
 // be finite); unobserved ones become NaNs carrying their index into the pivot table
 // (section 3.3: the equality constraints of the W-step are eliminated row by row, leaving
-// one tridiagonal system per run of unobserved entries).  seg: the order (packed_g_at).
+// one tridiagonal system per run of unobserved entries).  An observed value that is not finite is
+// flagged and stored as index 0: the kernels that create launches before it reads the flag take the
+// payload of any NaN as an index.  seg: the order (packed_g_at).
 //
 // Block (x, i): S = 2^ls segments of at most 16 columns of the rows (i, :, k), k = x KB .. + KB,
 // KB = 256 / S, a thread per (segment, row): its entries are in flight at once, and the last
@@ -59,8 +61,9 @@ __global__ void __launch_bounds__(256) k_pack_g(const float* __restrict__ g, con
         ++q;
       }
       if (o[u]) {
-        if (!isfinite(v[u])) atomicOr(flag, 1);
-        gp[row + at] = v[u];
+        const bool fin = isfinite(v[u]);
+        if (!fin) atomicOr(flag, 1);
+        gp[row + at] = fin ? v[u] : __uint_as_float(pack_unobserved(0));
         prev = j;
       } else {
         const uint32_t table = (j == n2 - 1 ? 2u : 0u) + (prev >= 0 ? 1u : 0u);
