@@ -136,9 +136,12 @@ tctf_status tctf_create(const tctf_params* p, const float* G, const uint8_t* ome
 
 /* Enqueue `iters` iterations (steps 1-4 and 7 of the algorithm box; step 5 keeps r,
  * step 6 is tctf_termination).  Asynchronous and stream-ordered.  Whole blocks of 10
- * iterations are replayed from a HIP graph that the first call with such a block captures on
- * a private stream of the context, after it has launched its first block (the results are the
- * same as eager launches); the rest run as eager launches.  Nothing but the iteration runs unless step 6 is tracked. */
+ * iterations are replayed from a HIP graph, the rest run as eager launches (the results are the
+ * same).  The graph is captured on a private stream of the context by the first call with two whole
+ * blocks, or the second with one, after it has launched its first block eagerly.  Where a graph
+ * cannot be captured every iteration runs as eager launches, which is no error.  On an error the
+ * iterations enqueued before it have run: tctf_iterations tells how many.  Nothing but the iteration
+ * runs unless step 6 is tracked. */
 tctf_status tctf_step(tctf_ctx* c, int32_t iters);
 
 /* Step 6 tracking (algorithm box, step 6).  With on != 0, every later tctf_step call keeps a

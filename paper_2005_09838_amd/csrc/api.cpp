@@ -161,6 +161,8 @@ struct tctf_ctx {
   size_t prof_used = 0;
   // GRAPH_ITERS iterations captured once as a HIP graph (on a private stream) and replayed
   // on the context's stream
+  bool ran_block = false;      // a tctf_step call has had a whole block of iterations
+  bool graph_failed = false;   // the capture failed: eager launches only
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t graph_exec = nullptr;
@@ -508,9 +510,9 @@ tctf_status tctf_create(const tctf_params* prm, const float* G, const uint8_t* o
   return TCTF_OK;
 }
 
-// Capture GRAPH_ITERS iterations into a graph (once per context, by the first tctf_step call that
-// has a whole block of them).  The kernels take the same buffers every iteration, so one graph
-// serves every later call.  A failed capture leaves no graph.
+// Capture GRAPH_ITERS iterations into a graph (once per context).  The kernels take the same buffers
+// every iteration, so one graph serves every later call.  A failed capture leaves no graph; the
+// context runs eagerly from then on.
 static tctf_status ensure_graph(tctf_ctx* c) {
   if (c->graph_exec) return TCTF_OK;
   if (!c->cap_stream) HIP_TRY(hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
@@ -552,20 +554,24 @@ tctf_status tctf_step(tctf_ctx* c, int32_t iters) {
   const int32_t body = c->track ? iters - 1 : iters;
   int32_t it = 0;
   if (c->prof_mask == 0 && !c->eager && c->prm.rank_every == 0 && body >= GRAPH_ITERS) {
-    // The first block runs eagerly, and the graph is captured while the device works on it: a
-    // 50-iteration completion of 144 x 288 x 28 from scratch 2508 us, with the capture first 2606
-    // (and calls of less than a block, which captured a graph that they did not use, pay for none:
-    // unrolled 144 x 288 x 28 2964, 3412 before).
-    if (!c->graph_exec) {
+    // The first block of a context without a graph runs eagerly, and the graph is captured while
+    // the device works on it, if a replay is to come: more blocks in this call, or calls of a block
+    // before this one.  A 50-iteration completion of 144 x 288 x 28 from scratch 2508 us, with the
+    // capture first 2606; calls of less than a block (unrolled 144 x 288 x 28) 2964, with a capture
+    // that they do not use 3412.
+    if (!c->graph_exec && !c->graph_failed) {
       for (; it < GRAPH_ITERS; ++it) {
         const tctf_status s = enqueue_iteration(c);
         if (s != TCTF_OK) return s;
         c->iters++;
       }
-      const tctf_status s = ensure_graph(c);
-      if (s != TCTF_OK) return s;
+      if ((c->ran_block || body - it >= GRAPH_ITERS) && ensure_graph(c) != TCTF_OK) {
+        c->graph_failed = true;
+        (void)hipGetLastError();   // the eager launches below report what is still wrong
+      }
+      c->ran_block = true;
     }
-    for (; body - it >= GRAPH_ITERS; it += GRAPH_ITERS) {
+    for (; c->graph_exec && body - it >= GRAPH_ITERS; it += GRAPH_ITERS) {
       HIP_TRY(hipGraphLaunch(c->graph_exec, p.stream));
       c->iters += GRAPH_ITERS;
     }
