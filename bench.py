@@ -81,10 +81,17 @@ STAGE_KERNELS = {"slice": "k_slice", "zgemm": "k_zgemm", "agemm": "k_agemm", "hs
                  "bgemm": "k_bgemm", "ystep": "k_ystep", "pinvy": "k_pinvy"}
 
 
+def capture_graph(c):
+    """Have a context capture its iteration graph (tctf_step does so in the first call of two
+    blocks of ten) before its warm-up, whatever its length, and go back to the iterate it had."""
+    state = c.get_state()
+    c.step(20)
+    c.set_state(state)
+
+
 def run_precision(prec, d, w, steps, warmup, dev, torch):
-    """Warm up (ten steps or more also capture the iteration graph, which then stays outside
-    every timed region); time `steps` iterations as the library runs them (graph replays) on
-    the wall clock between two synchronisations; time five more blocks of `steps` iterations
+    """Capture the iteration graph and warm up; time `steps` iterations as the library runs them
+    (graph replays) on the wall clock between two synchronisations; time five more blocks of `steps` iterations
     with HIP events on the library's stream (torch's current stream) and keep their median;
     then time every stage over 20 iterations (to pick the dominant one) and `steps` more
     iterations with only the dominant stage's launches bracketed by HIP events (event
@@ -94,6 +101,7 @@ def run_precision(prec, d, w, steps, warmup, dev, torch):
     t = lambda a: torch.from_numpy(a).to(dev)
     c = Completion(t(d["G"]), t(d["omega"]), w.r, mu=w.mu, rho1=w.rho1, rho2=w.rho2, precision=prec,
                    X0=t(d["X0"]), Y0=t(d["Y0"]))
+    capture_graph(c)
     c.step(max(warmup, 1))
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -166,6 +174,7 @@ def batch_bench(count, steps, warmup, autotune=False):
     t_tune = time.perf_counter() - t_tune
     tunings = [c.tuning() for c in singles]
     for c in singles:
+        capture_graph(c)
         c.step(warmup)
     torch.cuda.synchronize()
     t0 = time.perf_counter()
@@ -224,7 +233,8 @@ def layout_bench(iters, rates):
             t = lambda a: torch.from_numpy(a).to(dev)
             c = Completion(t(e["G"]), t(e["omega"]), w.r, mu=w.mu, rho1=w.rho1, rho2=w.rho2, X0=t(e["X0"]),
                            Y0=t(e["Y0"]))
-            c.step(1)   # graph capture outside the timed run
+            capture_graph(c)
+            c.step(1)
             torch.cuda.synchronize()
             t0 = time.perf_counter()
             c.step(iters - 1)
