@@ -217,8 +217,17 @@ __global__ void __launch_bounds__(512) k_tube64_half_fwd(const T* __restrict__ i
   }
 }
 
-// ---- direct sums, one thread per output: lengths with a large prime factor and few tubes
-template <int KIND, typename T>
+// ---- direct sums, one thread per output: lengths with a large prime factor and few tubes.  TAB: the
+// roots come from the caller's table (an instance of its own: with the choice inside the loop its
+// loads wait for each other; both transforms of 4 tubes of 3347 and the W-step 464 us, 801 so).
+template <bool TAB>
+__device__ __forceinline__ double2 direct_root(const Tube64& t, int m, int n3) {
+  if constexpr (TAB) return t.tw[m];
+  double2 w;
+  sincospi(2.0 * m / n3, &w.y, &w.x);
+  return w;
+}
+template <int KIND, typename T, bool TAB>
 __global__ void __launch_bounds__(256) k_tube_direct_inv(const void* __restrict__ in, T* __restrict__ out, T* __restrict__ out2,
                                                          Tube64 t, int P, int n3) {
   const long g = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -227,16 +236,11 @@ __global__ void __launch_bounds__(256) k_tube_direct_inv(const void* __restrict_
   const long tube = g / n3, p = tube / t.Q, q = tube % t.Q;
   double acc = 0.0;
   int m = 0;   // (b k) mod n3
+#pragma unroll 4
   for (int b = 0; b < nb; ++b) {
     const cd v = spec_load<KIND>(in, b * t.bs + p * t.ps + q * t.qs);
-    double sn, c;
-    if (t.tw) {
-      c = t.tw[m].x;
-      sn = t.tw[m].y;
-    } else {
-      sincospi(2.0 * m / n3, &sn, &c);
-    }
-    acc += bin_weight(b, n3) * (v.re * c + (bin_is_real(b, n3) ? 0.0 : v.im * sn));   // Re(e^{-i th} v)
+    const double2 w = direct_root<TAB>(t, m, n3);
+    acc += bin_weight(b, n3) * (v.re * w.x + (bin_is_real(b, n3) ? 0.0 : v.im * w.y));   // Re(e^{-i th} v)
     m += k;
     if (m >= n3) m -= n3;
   }
@@ -244,7 +248,7 @@ __global__ void __launch_bounds__(256) k_tube_direct_inv(const void* __restrict_
   out[at] = (T)(t.s * acc);
   if (out2) out2[at] = (T)(t.s * acc);
 }
-template <int KIND, typename T>
+template <int KIND, typename T, bool TAB>
 __global__ void __launch_bounds__(256) k_tube_direct_fwd(const T* __restrict__ in, void* __restrict__ out, Tube64 t, int P,
                                                          int n3, const uint32_t* __restrict__ ctr) {
   const long g = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -255,17 +259,12 @@ __global__ void __launch_bounds__(256) k_tube_direct_fwd(const T* __restrict__ i
   const T* src = in + p * t.sp + q * t.sq;
   double re = 0.0, im = 0.0;
   int m = 0;   // (b k) mod n3
+#pragma unroll 4
   for (int k = 0; k < n3; ++k) {
-    double sn, c;
-    if (t.tw) {
-      c = t.tw[m].x;
-      sn = t.tw[m].y;
-    } else {
-      sincospi(2.0 * m / n3, &sn, &c);
-    }
+    const double2 w = direct_root<TAB>(t, m, n3);
     const double v = src[k];
-    re += c * v;
-    im += sn * v;
+    re += w.x * v;
+    im += w.y * v;
     m += b;
     if (m >= n3) m -= n3;
   }
@@ -276,37 +275,14 @@ __global__ void __launch_bounds__(256) k_tube_direct_fwd(const T* __restrict__ i
 }
 
 // ---- host side
-static int largest_prime(int n) {
-  int best = 1;
-  for (int f = 2; f * f <= n; ++f)
-    while (n % f == 0) {
-      best = f;
-      n /= f;
-    }
-  return n > best ? n : best;
-}
-
-// Whether the passes beat the direct sums.  A large prime radix is itself a direct sum, run by one
-// block per few pairs and without the saving of real tubes, so with no cofactor, or 2, it pays only
-// where the pairs fill the device; and below 40 entries (32 with radices up to 7; 24 where the sums
-// have no table of roots) the passes' barriers cost as much as the sums.  Both transforms and the
-// W-step in us, direct / passes, for 144 x 28 tubes: of 18 entries 13.6 / 15.8, 25 15.2 / 15.8, 30
-// 16.3 / 16.2, 33 19.0 / 21.2, 36 19.3 / 18.4, 44 22.2 / 21.4, 60 30.7 / 19.4, 62 30.6 / 30.6, 67
-// 39.0 / 38.0, 93 56 / 30, 122 86 / 49, 257 331 / 180; for 100 tubes: 257 59 / 76, 335 76 / 33,
-// 1018 221 / 258; for 900: 2003 5206 / 4514, 4093 31876 / 32724; for 40: 2003 512 / 2283.
-static bool tube64_fast(const Plan& p, long pairs) {
-  const int n3 = p.n3, lp = largest_prime(n3);
-  if (n3 > 1024 && !p.twg) return false;   // the roots would not fit beside the sequence
-  if (lp <= 7) return n3 >= (p.twg ? 32 : 24);
-  if (n3 / lp <= 2) return n3 >= 64 && lp <= 2048 && pairs >= 256;
-  return n3 >= 40;
-}
-
 // Whether tubes go through sequences of half their length, a block each: long even ones (with the
 // table of roots) of which a compute unit holds one.  Both transforms and the W-step in us, pairs /
 // halves: 12 x 12 x 8064 58.3 / 50.2, 10 x 10 x 4032 36.8 / 30.7, 12 x 12 x 2688 31.5 / 28.2,
 // 12 x 12 x 2048 26.9 / 25.8; 22 x 22 x 2048 (242 pairs) 35.2 / 39.2.
 static bool tube64_half(const Plan& p, long pairs) { return p.n3 % 2 == 0 && p.n3 >= 2048 && pairs <= 128; }
+
+// Threads of a block on a sequence of half the length, of M values.
+static int tube64_half_threads(int M) { return M >= 2048 ? 512 : (M / 4 + 63) / 64 * 64; }
 
 static Tube64 tube64_args(const Plan& p, long bs, long ps, long qs, long sp, long sq, int Q, double s) {
   Tube64 t;
@@ -343,16 +319,76 @@ static dim3 tube64_shape(Tube64* t, int n3, int P, int* threads, size_t* lds) {
   return dim3((per_p + pp - 1) / pp, P);
 }
 
+// Sum of the radices that are passes of direct sums (fft64_pass_any).
+static int sum_radices(int n) {
+  int sum = 0;
+  for (int f = 2; f * f <= n; ++f)
+    while (n % f == 0) {
+      if (f > 7) sum += f;
+      n /= f;
+    }
+  return n > 7 ? sum + n : sum;
+}
+
+// Whether the passes beat the direct sums.  With radices up to 7 they do from 32 entries on (24 where
+// the sums have no table of roots): below, their barriers cost as much as the sums.  Both transforms
+// and the W-step in us, direct / passes, for 144 x 28 tubes: of 18 entries 13.6 / 15.8, 25 15.2 /
+// 15.8, 30 16.3 / 16.2, 36 19.3 / 18.4, 60 30.7 / 19.4.
+// A prime radix past 7 is itself a direct sum of N radix terms by the one block that holds the
+// sequence, while the direct sums spread over the device, so few tubes of such lengths are better off
+// with them.  The two times in us, fitted to 471 shapes (1 to 8192 tubes; lengths up to 8192 with a prime
+// factor past 7), in 11 of which the choice costs a tenth and 10 us more than the better side:
+// * a direct sum's thread waits 0.13 us for each term of both transforms, however few tubes there
+//   are, once per round of one 256-thread block per compute unit (0.7 of that from the second on;
+//   more where the table of roots leaves the caches);
+// * a pass costs 0.072 us per radix term and value of a thread (four, or eight past 4096; 0.3 of
+//   that more for each further block of a compute unit), or where the blocks fill the device 0.45 ns
+//   per term, 0.6 with the roots in memory.
+// Direct / passes: 1 x 1021 129 / 425, 128 x 1021 136 / 434, 1024 x 1021 1369 / 539; 4 x 1527 201 /
+// 440, 256 x 1527 803 / 449; 64 x 5105 4153 / 3059; 455 x 1481 1340 / 2400; 6 x 7115 1270 / 6110.
+static bool tube64_fast(const Plan& p, int P, int Q) {
+  const int n3 = p.n3;
+  if (n3 > 1024 && !p.twg) return false;   // the roots would not fit beside the sequence
+  const int terms = sum_radices(n3);
+  if (terms == 0) return n3 >= (p.twg ? 32 : 24);
+  const long tubes = (long)P * Q, pairs = (long)((Q + 1) / 2) * P;
+  int threads;
+  long blocks, values;
+  if (tube64_half(p, pairs)) {
+    threads = tube64_half_threads(n3 / 2);
+    blocks = tubes;
+    values = n3 / 2;
+  } else {
+    Tube64 t;
+    t.Q = Q;
+    size_t lds;
+    const dim3 grid = tube64_shape(&t, n3, P, &threads, &lds);
+    blocks = (long)grid.x * grid.y;
+    values = (long)t.PP * n3;
+  }
+  if (terms > 4096) return false;   // one pass over nearly the whole length
+  const long rounds = (tubes * n3 + 65535) / 65536;
+  double per_round = 2.5e-4 * n3;
+  per_round = per_round < 0.7 ? 0.7 : (per_round > 1.35 ? 1.35 : per_round);
+  const double direct = 6.0 + 0.13 * n3 * (per_round * rounds > 1.0 ? per_round * rounds : 1.0);
+  const double shared = n3 > 1024 ? 1.0 : 1.0 + 0.3 * ((blocks + 255) / 256 - 1);
+  const double chain = 0.072 * ((values + threads - 1) / threads) * terms * shared;
+  const double full = n3 > 1024 ? 6e-4 * ((blocks + 255) / 256) : 4.5e-4 * (blocks > 512 ? blocks / 512.0 : 1.0);
+  const double passes = 14.0 + (chain > full * values * terms ? chain : full * values * terms);
+  return passes < direct;
+}
+
 template <int KIND, typename T>
 static void tube_inv(const Plan& p, const void* in, T* out, T* out2, Tube64 t, int P) {
   const long pairs = (long)((t.Q + 1) / 2) * P;
-  if (!tube64_fast(p, pairs)) {
+  if (!tube64_fast(p, P, t.Q)) {
     const long n = (long)P * t.Q * p.n3;
-    k_tube_direct_inv<KIND, T><<<(unsigned)((n + 255) / 256), 256, 0, p.stream>>>(in, out, out2, t, P, p.n3);
+    const auto k = t.tw ? k_tube_direct_inv<KIND, T, true> : k_tube_direct_inv<KIND, T, false>;
+    k<<<(unsigned)((n + 255) / 256), 256, 0, p.stream>>>(in, out, out2, t, P, p.n3);
     return;
   }
   if (tube64_half(p, pairs)) {
-    const int M = p.n3 / 2, threads = M >= 2048 ? 512 : (M / 4 + 63) / 64 * 64;
+    const int M = p.n3 / 2, threads = tube64_half_threads(M);
     k_tube64_half_inv<KIND, T><<<dim3(t.Q, P), threads, M * sizeof(cd), p.stream>>>(in, out, out2, t, fft64_plan(p.n3 / 2));
     return;
   }
@@ -366,13 +402,14 @@ static void tube_inv(const Plan& p, const void* in, T* out, T* out2, Tube64 t, i
 template <int KIND, typename T>
 static bool tube_fwd(const Plan& p, const T* in, void* out, Tube64 t, int P) {
   const long pairs = (long)((t.Q + 1) / 2) * P;
-  if (!tube64_fast(p, pairs)) {
+  if (!tube64_fast(p, P, t.Q)) {
     const long n = (long)P * t.Q * (p.n3 / 2 + 1);
-    k_tube_direct_fwd<KIND, T><<<(unsigned)((n + 255) / 256), 256, 0, p.stream>>>(in, out, t, P, p.n3, p.ctr);
+    const auto k = t.tw ? k_tube_direct_fwd<KIND, T, true> : k_tube_direct_fwd<KIND, T, false>;
+    k<<<(unsigned)((n + 255) / 256), 256, 0, p.stream>>>(in, out, t, P, p.n3, p.ctr);
     return false;
   }
   if (tube64_half(p, pairs)) {
-    const int M = p.n3 / 2, threads = M >= 2048 ? 512 : (M / 4 + 63) / 64 * 64;
+    const int M = p.n3 / 2, threads = tube64_half_threads(M);
     k_tube64_half_fwd<KIND, T><<<dim3(t.Q, P), threads, M * sizeof(cd), p.stream>>>(in, out, t, fft64_plan(p.n3 / 2), p.ctr);
     return true;
   }
