@@ -9,6 +9,10 @@
 // eigenvalue and A^+ = A^-1.  Otherwise (or when forced) a cyclic Jacobi
 // eigen-decomposition with parallel (round-robin) pair ordering is used by the whole block
 // and the rule is applied to its eigenvalues.
+//
+// The routines are forced inline: called out of line they take their LDS through generic
+// addresses and give every kernel that hosts them 152 registers (r = 30 by the eigen route: 761 us
+// beside the Z~ product and 824 in the X~^* W~ launch, 535 and 491 inline).
 #pragma once
 #include "common.h"
 #include "kernels.h"
@@ -96,7 +100,7 @@ __device__ __forceinline__ int pinv_sweep(const cd* A, cd* w0, cd* w1, int r, co
 // parallel (round-robin) pair ordering: on return s.work holds the rotated matrix (the
 // eigenvalues on its diagonal, unsorted) and s.vec the eigenvectors as columns.  fro is
 // ||A||_F (the sweeps stop when the off-diagonal part falls below 1e-14 fro).
-__device__ inline void jacobi_herm(const cd* A, int r, double fro, PinvScratch s) {
+__device__ __forceinline__ void jacobi_herm(const cd* A, int r, double fro, PinvScratch s) {
   const int tid = threadIdx.x, nt = blockDim.x, rr = r * r;
   for (int e = tid; e < rr; e += nt) {
     s.work[e] = A[e];
@@ -169,7 +173,7 @@ __device__ inline void jacobi_herm(const cd* A, int r, double fro, PinvScratch s
 }
 
 // Returns 1 (to every thread) if all eigenvalues were kept, 0 otherwise.
-__device__ inline int pinv_herm(const cd* A, cd* P, int r, int force_eigen, PinvScratch s) {
+__device__ __forceinline__ int pinv_herm(const cd* A, cd* P, int r, int force_eigen, PinvScratch s) {
   const int tid = threadIdx.x, nt = blockDim.x, rr = r * r;
   if (!force_eigen) {
     const cd* swept;
@@ -276,7 +280,7 @@ static inline PinvyArgs pinvy_args(const tctf::Plan& p) {
 // order), the objective term c_b tr(D G_Y), G_Y^+ and, unless it is exactly 0,
 // q = I - eta G_Y G_Y^+ for the next X-update (first line of eq. (updataXYW1)); qy_zero[b] = 1
 // marks q = 0.  sm: pinv_lds_bytes(r) bytes of LDS.
-__device__ inline void pinvy_block(int b, const PinvyArgs& a, unsigned char* sm) {
+__device__ __forceinline__ void pinvy_block(int b, const PinvyArgs& a, unsigned char* sm) {
   const int tid = threadIdx.x, nt = blockDim.x, r = a.r, rr = r * r;
   cd* gy = (cd*)sm;
   cd* gp = gy + rr;
