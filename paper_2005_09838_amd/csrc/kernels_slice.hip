@@ -72,10 +72,19 @@ int slice_segments(int n2, int n3) {
 // 256 / 448 / 640 / 1024 threads: 144 x 288 x 28 13.7 / 9.9 / 9.5 / 10.5, 144 x 96 x 112
 // 18.4 / 15.7 / 15.2 / 16.4; 529 x 96 x 112 28.7 / 33.8 / 41.8 / 45.4, 529 x 288 x 28
 // 20.8 / 21.9 / 27.4 / 29.7.
+//
+// In an iteration the blocks of the inverses have the same size and are the launch's longest, so
+// past r = 8 (one entry per lane of a wavefront) short rows get 256 threads too, but 128, and those
+// past r = 12 only, where thousands of rows would carry the idle wavefronts.  One iteration in us
+// with 64 / 128 / 256 threads: 40 x 33 x 7, r = 32 140.8 / 115.3 / 102.8; 20 x 17 x 9, r = 12 36.2 /
+// 34.2 / 32.9; 26 x 18 x 8, r = 16 by the eigen route 464 / 416 / 415; 4000 x 17 x 7, r = 16 104.1 /
+// 101.8 / 106.4; 8192 x 12 x 4, r = 12 153.8 / 156.0 / 165.8; 20 x 17 x 9, r = 8 25.8 / 25.7 / 25.9.
 static int slice_threads(const Plan& p, bool iter) {
   const int tubes = p.n2 * tube_threads(p.n3, iter), items = p.n3 * p.gseg;
   const int need = ((tubes > items ? tubes : items) + 63) / 64 * 64, most = p.n1 <= 256 ? 640 : 256;
-  return need < most ? need : most;
+  const int threads = need < most ? need : most;
+  const int host = !iter || p.r <= 8 ? 64 : (p.n1 <= 2048 ? 256 : (p.r > 12 ? 128 : 64));
+  return threads < host ? host : threads;
 }
 
 size_t slice_launch_lds_bytes(const Plan& p) {
