@@ -603,15 +603,20 @@ int hinv_stencil(double rho1, int n1, int r, double* tap) {
 // (12 x 12 x 8064 18.2 us against 28.6).  The columns of W~ are split over wavefronts, 48 each,
 // while the grid has fewer than 2048 of them (144 x 288 x 28 12.9 us with one column, 10.1 with
 // three or more; 529 x 96 x 112, whose grid fills the device, 21.2 with one, 26.6 with two).
+// The epilogue has rm / 8 column tiles, which 2 or 4 wavefront columns share even where the columns
+// of W~ need fewer, within the same bound (the X-update alone in us with 1 / 2 / 4: 40 x 33 x 7, r =
+// 32 17.9 / 14.2 / 12.6; 678 x 32 x 25, r = 30 19.8 / 17.0 / 26.0; 20 x 17 x 9, r = 16 10.1 / 9.0 / -).
 static void agemm_shape(const Plan& p, int hk, int rm, int* rt, int* wc) {
   const int halo = hk >= 0 ? 2 * hk : 0;
   const long blocks4 = (long)((p.n1 + 63 - halo) / (64 - halo)) * p.nb;
   *rt = rm == 32 || (halo <= 16 && (blocks4 < 512 || p.n1 <= 32 - halo)) ? 2 : 4;
   const long waves = (long)((p.n1 + 16 * *rt - halo - 1) / (16 * *rt - halo)) * p.nb * *rt;
   const int most = (rm == 32 ? 8 : 16) / *rt, want = (p.n2 + 8 * AG_GROUPS - 1) / (8 * AG_GROUPS);
+  int tiles = rm / 8;
+  while (tiles > 1 && waves * tiles > 2048) tiles >>= 1;
   *wc = (int)(2048 / waves);
   if (*wc < 1) *wc = 1;
-  if (*wc > want) *wc = want;
+  if (*wc > want) *wc = want > tiles ? want : tiles;
   if (*wc > most) *wc = most;
 }
 
