@@ -928,6 +928,7 @@ tctf_status tctf_time_stage(tctf_ctx* c, int32_t stage, int32_t reps, double* me
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
+  if (stage == 0) tctf::launch_zgemm(p);   // Z~ of the current factors (stage 4 may use its buffer)
   HIP_TRY(hipEventRecord(e0, p.stream));
   for (int k = 0; k < reps; ++k) {
     switch (stage) {

@@ -26,7 +26,7 @@ struct Plan {
   int gseg;         // its order: lanes per row of the fused slice kernel's W-step, 0 on the
                     // three-launch path
   void* wt;         // W~ [n1][nb][n2] float2 (FP32) or packed bf16x2 (mixed)
-  float2* zt;       // Z~ [n1][nb][n2]
+  float2* zt;       // Z~ [n1][nb][n2], from its product to the slice work; row groups' G_X (launch_bgemm)
   float2* xt;       // X~ [nb][r][n1]
   float2* yt;       // Y~ [nb][r][n2]
   float2* rhs;      // right-hand side of the H_rho1 solve [nb][r][n1]

@@ -656,6 +656,8 @@ struct GramOut {
   int* qx_zero;  // [nb] 1 when I - eta P_X = 0
   double rho1, eta;
   int force_eigen;
+  double2* part; // S and D of npart row groups [nb][npart][2][r][r], upper tiles, or npart = 0
+  int npart;
 };
 
 // (re, im) tiles of a complex product conj(x) w summed over rows: lane (m, q) supplies
@@ -755,15 +757,14 @@ __device__ __forceinline__ void bg_mfma(const float2 (&xv)[BgShape<XL, WL>::KG][
 // before, the Gram in two launches on a graph branch beside the product: 7.3 + 11.5 us beside
 // 16.6, and 14 us for the branch's fork and join.  144 x 288 x 28, r = 8: 10.4 us (5.1 + 7.6
 // beside 6.6, and the fork and join, before).
+//
+// gramx_rows: the tiles of S and D over the runs of eight rows k0 .. k1 - 1, by the W wavefronts.
 template <int XL, int W>
-__device__ __forceinline__ void gramx_block(const float2* __restrict__ xt, int b, int n1, int r, const GramOut& go,
-                                            unsigned char* sm) {
-  constexpr int NT = XL * (XL + 1) / 2, KG = XL == 1 ? 4 : 2;
-  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, w = tid >> 6, m = lane & 15, q = lane >> 4, rr = r * r;
-  const int nks = (n1 + 7) >> 3, per = (nks + W - 1) / W, ks0 = min(nks, w * per), ks1 = min(nks, ks0 + per);
-  BgTile gs[NT], gd[NT];
-#pragma unroll
-  for (int k = 0; k < NT; ++k) gs[k].re = gs[k].im = gd[k].re = gd[k].im = v4d{0.0, 0.0, 0.0, 0.0};
+__device__ __forceinline__ void gramx_rows(const float2* __restrict__ xt, int b, int n1, int r, int k0, int k1,
+                                           BgTile (&gs)[XL * (XL + 1) / 2], BgTile (&gd)[XL * (XL + 1) / 2]) {
+  constexpr int KG = XL == 1 ? 4 : 2;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, m = lane & 15, q = lane >> 4;
+  const int per = (k1 - k0 + W - 1) / W, ks0 = min(k1, k0 + w * per), ks1 = min(k1, ks0 + per);
   const float2* xb = xt + (size_t)b * r * n1;
   float2 xa[KG][XL][3], xn[KG][XL][3];
   auto load = [&](int ks, float2 (&x)[KG][XL][3]) {
@@ -819,6 +820,40 @@ __device__ __forceinline__ void gramx_block(const float2* __restrict__ xt, int b
     if (ks + KG >= ks1) break;
     load(ks + 2 * KG, xa);
     prod(ks + KG, xn);
+  }
+}
+
+template <int XL, int W>
+__device__ __forceinline__ void gramx_block(const float2* __restrict__ xt, int b, int n1, int r, const GramOut& go,
+                                            unsigned char* sm) {
+  constexpr int NT = XL * (XL + 1) / 2;
+  const int tid = threadIdx.x, nt = blockDim.x, lane = tid & 63, w = tid >> 6, m = lane & 15, q = lane >> 4, rr = r * r;
+  BgTile gs[NT], gd[NT];
+#pragma unroll
+  for (int k = 0; k < NT; ++k) gs[k].re = gs[k].im = gd[k].re = gd[k].im = v4d{0.0, 0.0, 0.0, 0.0};
+  if (go.npart == 0) {
+    gramx_rows<XL, W>(xt, b, n1, r, 0, (n1 + 7) >> 3, gs, gd);
+  } else {
+    const double2* part = go.part + (size_t)b * go.npart * 2 * rr;
+    for (int g = w; g < go.npart; g += W) {
+      int t = 0;
+#pragma unroll
+      for (int a = 0; a < XL; ++a)
+#pragma unroll
+        for (int c = a; c < XL; ++c, ++t) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int s = 16 * a + q + 4 * e, u = 16 * c + m;
+            const bool in = s < r && u < r;
+            const double2 vs = ld_or(part, (size_t)2 * g * rr + s * r + u, in, make_double2(0.0, 0.0));
+            const double2 vd = ld_or(part, (size_t)(2 * g + 1) * rr + s * r + u, in, make_double2(0.0, 0.0));
+            gs[t].re[e] += vs.x;
+            gs[t].im[e] += vs.y;
+            gd[t].re[e] += vd.x;
+            gd[t].im[e] += vd.y;
+          }
+        }
+    }
   }
   bg_reduce<W>(gs, (double2*)sm, w, lane);
   bg_reduce<W>(gd, (double2*)sm, w, lane);
@@ -879,6 +914,38 @@ __device__ __forceinline__ void gramx_block(const float2* __restrict__ xt, int b
     }
   }
   if (tid == 0) go.qx_zero[b] = qzero ? 1 : 0;
+}
+
+// S and D of row group blockIdx.x of frequency blockIdx.y, runs of eight rows g per .. (g + 1) per,
+// for the G_X blocks of the next launch to add up.
+template <int XL>
+__global__ void __launch_bounds__(512) k_gramx_part(const float2* __restrict__ xt, int n1, int r, int per, double2* __restrict__ part) {
+  constexpr int NT = XL * (XL + 1) / 2;
+  extern __shared__ __align__(16) unsigned char psm[];
+  const int g = blockIdx.x, b = blockIdx.y, lane = threadIdx.x & 63, w = threadIdx.x >> 6, m = lane & 15, q = lane >> 4, rr = r * r;
+  BgTile gs[NT], gd[NT];
+#pragma unroll
+  for (int k = 0; k < NT; ++k) gs[k].re = gs[k].im = gd[k].re = gd[k].im = v4d{0.0, 0.0, 0.0, 0.0};
+  const int nks = (n1 + 7) >> 3, k0 = min(nks, g * per);
+  gramx_rows<XL, 8>(xt, b, n1, r, k0, min(nks, k0 + per), gs, gd);
+  bg_reduce<8>(gs, (double2*)psm, w, lane);
+  bg_reduce<8>(gd, (double2*)psm, w, lane);
+  if (w != 0) return;
+  double2* out = part + ((size_t)b * gridDim.x + g) * 2 * rr;
+  int t = 0;
+#pragma unroll
+  for (int a = 0; a < XL; ++a)
+#pragma unroll
+    for (int c = a; c < XL; ++c, ++t) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int s = 16 * a + q + 4 * e, u = 16 * c + m;
+        if (s < r && u < r) {
+          out[s * r + u] = make_double2(gs[t].re[e], gs[t].im[e]);
+          out[rr + s * r + u] = make_double2(gd[t].re[e], gd[t].im[e]);
+        }
+      }
+    }
 }
 
 // Blocks 0 .. nb - 1: G_X of frequency blockIdx.x (the longest chain, so they start first);
@@ -950,6 +1017,23 @@ static BgemmKernel bgemm_kernel_of(int bcg, int mixed, int waves) {
   return waves == 2 ? bgemm_kernel<XL, 2>(bcg, mixed) : bgemm_kernel<XL, 8>(bcg, mixed);
 }
 
+// Row groups of G_X in a launch of their own, 0: all rows in the block that inverts it.  Up to r = 16
+// that block's sums are no longer than the product's beside it, but at r > 16, or before an inverse by
+// the eigen route, they are the launch's chain; four groups or more of at least 96 rows each, and no
+// more blocks than compute units.  One iteration in us, one block / groups: 8192 x 32 x 3, r = 32
+// 533 / 388; 1500 x 24 x 112, r = 17 206 / 190; 384 x 24 x 5, r = 24 83.4 / 78.7; 600 x 24 x 200, r = 24
+// (two groups) 198 / 207; 4000 x 24 x 112, r = 16 199 / 220, by the eigen route 507 / 467; 1000 x 16 x
+// 12, r = 16, eigen 402 / 401.
+static int gramx_groups(const Plan& p) {
+  if (p.r <= 16 && !(p.force_eigen && p.n1 >= 1000)) return 0;
+  int g = p.n1 / 96;
+  if (g > 256 / p.nb) g = 256 / p.nb;
+  // the partials lie in Z~'s buffer: 32 r^2 bytes each in 8 n1 n2 per frequency
+  const long room = (long)p.n1 * p.n2 / (4 * p.r * p.r);
+  if (g > room) g = (int)room;
+  return g >= 4 ? g : 0;
+}
+
 // X~^* W~ -> bpart [nb][r][n2]; G_X, (H X~)^*(H X~), G_X^+ and I - eta P_X.
 void launch_bgemm(const Plan& p) {
   GramOut go;
@@ -961,6 +1045,15 @@ void launch_bgemm(const Plan& p) {
   go.rho1 = p.rho1;
   go.eta = p.eta;
   go.force_eigen = p.force_eigen;
+  go.part = (double2*)p.zt;   // Z~ is formed anew after this launch
+  go.npart = gramx_groups(p);
+  if (go.npart > 0) {
+    const int per = ((p.n1 + 7) / 8 + go.npart - 1) / go.npart;
+    const dim3 grid(go.npart, p.nb);
+    const size_t lds = bgemm_lds_bytes(p.r, 16, 8);
+    if (p.r <= 16) k_gramx_part<1><<<grid, 512, lds, p.stream>>>(p.xt, p.n1, p.r, per, go.part);
+    else k_gramx_part<2><<<grid, 512, lds, p.stream>>>(p.xt, p.n1, p.r, per, go.part);
+  }
   const int ncg = (p.n2 + p.bcg - 1) / p.bcg, waves = bgemm_waves(p);
   const size_t lds = bgemm_lds_bytes(p.r, p.bcg, waves);
   const BgemmKernel kernel = p.r <= 16 ? bgemm_kernel_of<1>(p.bcg, p.mixed, waves) : bgemm_kernel_of<2>(p.bcg, p.mixed, waves);
