@@ -952,8 +952,10 @@ __global__ void __launch_bounds__(512) k_gramx_part(const float2* __restrict__ x
 // the others: the product.  Block order of the product: the column groups of one frequency run
 // on one XCD (blocks are dealt to the eight XCDs in turn), so each XCD's L2 holds the X~ rows of
 // its own frequencies only.
+// The bound of 2 keeps the two-wavefront instances from the accumulator registers, whose moves cost
+// more than they save (12 x 12 x 8064: 37 us with them, 26 without).
 template <int XL, int WL, bool MX, int W>   // r <= 16 XL, 16 WL complex columns and W wavefronts per block, MX: W~ in BF16
-__global__ void __launch_bounds__(64 * W) k_bgemm(const void* __restrict__ wt, const float2* __restrict__ xt,
+__global__ void __launch_bounds__(64 * W, 2) k_bgemm(const void* __restrict__ wt, const float2* __restrict__ xt,
                                                       double2* __restrict__ bout, int n1, int n2, int r, int nb,
                                                       int ncg, GramOut go) {
   constexpr int KG = BgShape<XL, WL>::KG;
@@ -995,7 +997,7 @@ __global__ void __launch_bounds__(64 * W) k_bgemm(const void* __restrict__ wt, c
 }
 
 // Wavefronts per block: 8, or 2 where there are many frequencies of few rows (12 x 12 x 8064:
-// 139 us with 8, 36 with 2).
+// 139 us with 8, 26 with 2).
 static int bgemm_waves(const Plan& p) { return p.n1 <= 64 && p.nb >= 256 ? 2 : 8; }
 
 static size_t bgemm_lds_bytes(int r, int bcg, int waves) {
