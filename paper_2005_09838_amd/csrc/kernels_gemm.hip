@@ -1005,6 +1005,10 @@ static size_t bgemm_lds_bytes(int r, int bcg, int waves) {
   const size_t red = (size_t)(waves / 2) * (tiles > gtiles ? tiles : gtiles) * 4 * 64 * sizeof(double2);
   return red > pinv_lds_bytes(r) ? red : pinv_lds_bytes(r);
 }
+// More than half a compute unit's LDS: blocks of a launch with no more of them than units, in which
+// the matrix cores bound each, do not meet on one (three of 3600 x 2 x 26, r = 2, together 184 us per
+// iteration with the LDS that they use, 180 so).
+#define BG_LDS_ALONE (84 * 1024)
 
 bool bgemm_cols_valid(int r, int bcg) { return (bcg == 16 || bcg == 32) && r <= 32; }
 
@@ -1020,14 +1024,16 @@ static BgemmKernel bgemm_kernel_of(int bcg, int mixed, int waves) {
 }
 
 // Row groups of G_X in a launch of their own, 0: all rows in the block that inverts it.  Up to r = 16
-// that block's sums are no longer than the product's beside it, but at r > 16, or before an inverse by
-// the eigen route, they are the launch's chain; four groups or more of at least 96 rows each, and no
-// more blocks than compute units.  One iteration in us, one block / groups: 8192 x 32 x 3, r = 32
-// 533 / 388; 1500 x 24 x 112, r = 17 206 / 190; 384 x 24 x 5, r = 24 83.4 / 78.7; 600 x 24 x 200, r = 24
-// (two groups) 198 / 207; 4000 x 24 x 112, r = 16 199 / 220, by the eigen route 507 / 467; 1000 x 16 x
-// 12, r = 16, eigen 402 / 401.
+// and a few thousand rows that block's sums are no longer than the product's beside it, but at r >
+// 16, before an inverse by the eigen route, or for more rows and few frequencies they are the launch's
+// chain (and members of a batch whose chains meet on a compute unit share its matrix cores): groups of
+// at least 96 rows, four or more, and no more blocks than compute units.  One iteration in us, one
+// block / groups: 8192 x 32 x 3, r = 32 533 / 388; 1500 x 24 x 112, r = 17 206 / 190; 384 x 24 x 5, r =
+// 24 83.4 / 78.7; 600 x 24 x 200, r = 24 (two groups) 198 / 207; 8192 x 16 x 7, r = 16 170 / 165; 2000 x
+// 12 x 28, r = 12 76.3 / 76.2; 4000 x 24 x 112, r = 16 199 / 220, by the eigen route 507 / 467; 1000 x 16
+// x 12, r = 16, eigen 402 / 401; three of 6591 x 7 x 2, r = 4, together 250 / 190.
 static int gramx_groups(const Plan& p) {
-  if (p.r <= 16 && !(p.force_eigen && p.n1 >= 1000)) return 0;
+  if (p.r <= 16 && !(p.force_eigen ? p.n1 >= 1000 : p.n1 >= 2000 && p.nb <= 16)) return 0;
   int g = p.n1 / 96;
   if (g > 256 / p.nb) g = 256 / p.nb;
   // the partials lie in Z~'s buffer: 32 r^2 bytes each in 8 n1 n2 per frequency
@@ -1057,7 +1063,8 @@ void launch_bgemm(const Plan& p) {
     else k_gramx_part<2><<<grid, 512, lds, p.stream>>>(p.xt, p.n1, p.r, per, go.part);
   }
   const int ncg = (p.n2 + p.bcg - 1) / p.bcg, waves = bgemm_waves(p);
-  const size_t lds = bgemm_lds_bytes(p.r, p.bcg, waves);
+  size_t lds = bgemm_lds_bytes(p.r, p.bcg, waves);
+  if ((1 + ncg) * p.nb <= 256 && lds < BG_LDS_ALONE) lds = BG_LDS_ALONE;
   const BgemmKernel kernel = p.r <= 16 ? bgemm_kernel_of<1>(p.bcg, p.mixed, waves) : bgemm_kernel_of<2>(p.bcg, p.mixed, waves);
   if (lds > 65536) (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   kernel<<<p.nb + ncg * p.nb, 64 * waves, lds, p.stream>>>(p.wt, p.xt, p.bpart, p.n1, p.n2, p.r, p.nb, ncg, go);

@@ -18,6 +18,8 @@ pytestmark = pytest.mark.gpu
     (1000, 12, 4, 9, 1),     # ... and groups from 1000 rows on by the eigen route
     (600, 20, 126, 20, 0),   # 64 frequencies: four groups each
     (600, 20, 128, 20, 0),   # 65: one block each
+    (1999, 6, 5, 4, 0),      # up to r = 16 one block ...
+    (2000, 6, 5, 4, 0),      # ... and groups from 2000 rows on
     (2049, 18, 3, 18, 0),    # idle wavefronts in slice blocks of more than 2048 rows
     (2049, 14, 4, 13, 0),
     (2049, 12, 4, 12, 0),
