@@ -9,6 +9,7 @@
 #define TCTF_N1MAX 8192       // largest n1 (tridiagonal H_rho1 solve held in LDS)
 #define TCTF_N3MAX 8192       // largest tube length n3
 #define TCTF_SLICE_LDS_MAX (150 * 1024)
+#define TCTF_LDS_BYTES (160 * 1024)   // of a compute unit
 
 // Complex numbers: planar pairs in registers, float2 / double2 in memory.
 struct cf { float re, im; };

@@ -30,22 +30,41 @@ static int tube_threads(int n3, bool iter) {
   }
 }
 
-// A slice runs through the fused kernel when n3 is a generated length and its working set
-// (rows, pivot table, two flag words per 32 entries, twiddles) is within TCTF_SLICE_LDS_MAX:
-// the rule is on the sizes alone, so a shape's arithmetic (FP32 transforms here, FP64 on the
-// other path) does not change with this kernel's own LDS needs, which are smaller.
-bool slice_fused(int n2, int n3) {
-  if (!slice_supported(n3)) return false;
+// A slice runs through the fused kernel when n3 is a generated length and a working set of rows one
+// float past an odd stride, pivot table, two flag words per 32 entries and twiddles is within
+// TCTF_SLICE_LDS_MAX: the rule is on the sizes alone, so a shape's arithmetic (FP32 transforms here,
+// FP64 on the other path) does not change with this kernel's own LDS needs.  Those are less for most
+// lengths and more where lanes share a tube and its row is padded (529 x 349 x 96: 160324 bytes, rule
+// 153600), so that they fit a compute unit is checked for every size below.
+static constexpr size_t slice_rule_bytes(int n2, int n3) {
   const size_t nwr = ((size_t)n2 + 31) / 32, ld = (n3 % 2 == 0) ? n3 + 3 : n3 + 2;
   const size_t floats = (size_t)n2 * ld + 4 * (size_t)n2 + 2 * (size_t)n3 * nwr + 1 + 2 * (size_t)(n3 + 1);
-  return floats * sizeof(float) + 48 * sizeof(double) + 16 <= TCTF_SLICE_LDS_MAX;
-}
-
-static size_t slice_lds_bytes(int n2, int n3, bool iter) {
-  size_t floats = (size_t)n2 * (tube_ld(n3, iter) + 4) + 1;
-  if (tube_threads(n3, iter) > 1) floats += 2 * (size_t)(n3 + 1);   // twiddles of the LDS transforms
   return floats * sizeof(float) + 48 * sizeof(double) + 16;
 }
+bool slice_fused(int n2, int n3) { return slice_supported(n3) && slice_rule_bytes(n2, n3) <= TCTF_SLICE_LDS_MAX; }
+
+// What the kernel's layout takes (k_slice): rows of ld floats, pivot table, twiddles where lanes
+// share a tube, block sums.
+static constexpr size_t slice_bytes(int n2, int n3, int ld, int threads) {
+  const size_t floats = (size_t)n2 * (ld + 4) + 1 + (threads > 1 ? 2 * (size_t)(n3 + 1) : 0);
+  return floats * sizeof(float) + 48 * sizeof(double) + 16;
+}
+static size_t slice_lds_bytes(int n2, int n3, bool iter) {
+  return slice_bytes(n2, n3, tube_ld(n3, iter), tube_threads(n3, iter));
+}
+
+template <int N>
+static constexpr bool slice_fits() {
+  for (int n2 = 1; n2 <= TCTF_N2MAX; ++n2)
+    if (slice_rule_bytes(n2, N) <= TCTF_SLICE_LDS_MAX &&
+        (slice_bytes(n2, N, slice_ld<N, true>(), slice_tube_threads<N, true>()) > TCTF_LDS_BYTES ||
+         slice_bytes(n2, N, slice_ld<N, false>(), slice_tube_threads<N, false>()) > TCTF_LDS_BYTES))
+      return false;
+  return true;
+}
+#define TCTF_CASE(n) static_assert(slice_fits<n>(), "a slice that the rule sends to the fused kernel does not fit its LDS");
+TUBE_DFT_SIZES(TCTF_CASE)
+#undef TCTF_CASE
 
 int slice_default_path(int n2, int n3) {
   if (!slice_fused(n2, n3)) return SPATH_SPLIT;
