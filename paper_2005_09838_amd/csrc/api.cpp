@@ -54,7 +54,7 @@ struct StateHeader {
 
 struct Layout {
   size_t gp, wt, zt, xt, yt, rhs, bpart, gxm, dmat, gxp, qx, qx_zero, gym, gyp, qy, qy_zero, slice_obj, bin_obj, wtab, htab,
-      flag, ctr, zsp, wsp, csp, twg, rsig, rtx, rty, ranks, scal, xt_prev, yt_prev, wt_prev, stat_work, kkt, total;
+      flag, ctr, zsp, wsp, rowpart, twg, rsig, rtx, rty, ranks, scal, xt_prev, yt_prev, wt_prev, stat_work, kkt, total;
   size_t state_bytes;
   bool split;   // the three-launch slice path's buffers exist
 };
@@ -123,7 +123,7 @@ static Layout make_layout(const tctf_params& p) {
   const bool gen = p.autotune || dk.spath == tctf::SPATH_SPLIT;   // the three-launch slice path
   L.zsp = take(gen ? n1 * n2 * n3 * 4 : 0);
   L.wsp = take(gen ? n1 * n2 * n3 * 4 : 0);
-  L.csp = take(gen ? n1 * n2 * n3 * 4 : 0);
+  L.rowpart = take(gen ? tctf::slice_generic_part_doubles(p.n1, p.n2, p.n3) * 8 : 0);
   L.twg = take(gen ? n3 * 16 : 0);
   L.split = gen;
   L.rsig = take(nb * r * 8);
@@ -263,7 +263,7 @@ static void fill_plan(tctf_ctx* c, hipStream_t stream) {
   q.ctr = (uint32_t*)(w + L.ctr);
   q.zsp = (float*)(w + L.zsp);
   q.wsp = (float*)(w + L.wsp);
-  q.csp = (float*)(w + L.csp);
+  q.rowpart = (double*)(w + L.rowpart);
   q.twg = L.split ? (double2*)(w + L.twg) : nullptr;
   q.rsig = (double*)(w + L.rsig);
   q.rtx = (cd*)(w + L.rtx);

@@ -47,10 +47,11 @@ struct Plan {
   int* flag;        // non-finite detector
   uint32_t* ctr;    // iteration counter of the BF16 rounding bits (advanced by each X-step)
   // the three-launch slice path (tube lengths outside the generated set, or slices larger
-  // than the fused kernel's LDS): spatial Z and W, partials of the objective, roots of unity
+  // than the fused kernel's LDS): spatial Z and W, partials of each OD row's three objective terms
+  // (slice_generic_part_doubles), roots of unity
   float* zsp;       // [n1][n2][n3]
   float* wsp;       // [n1][n2][n3]
-  float* csp;       // [n1][n2][n3]
+  double* rowpart;  // [n1][blocks per OD row][3]
   double2* twg;     // [n3] (cos, sin)(2 pi m / n3); NULL without that path
   // step 5 (rank adjustment)
   double* rsig;     // [nb][r] singular values of Z~_b, descending
@@ -116,6 +117,7 @@ int slice_default_path(int n2, int n3);
 bool slice_path_valid(int path, int n2, int n3);
 bool slice_supported(int n3);
 bool slice_fused(int n2, int n3);          // the fused LDS slice kernel applies
+size_t slice_generic_part_doubles(int n1, int n2, int n3);
 void launch_slice_generic(const Plan& p, int mode, float* w_out, float* z_out, int w_from_g);
 bool slice_hosts_pinvy(const Plan& p);   // the iteration's slice launch also forms G_Y^+
 size_t slice_launch_lds_bytes(const Plan& p);

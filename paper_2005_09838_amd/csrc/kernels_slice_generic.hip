@@ -142,6 +142,24 @@ __global__ void k_gen_rows(const double* __restrict__ part, int n1, int nchunk, 
   out[e] = v;
 }
 
+// Blocks of k_gen_wstep: segments of at most 16 columns and no more of them than that needs, so that
+// the runs of rows are long; no more rows per block than there are, in whole wavefronts.
+struct WstepShape {
+  int ls, lk, nchunk;
+};
+static WstepShape wstep_shape(int n2, int n3) {
+  WstepShape w = {0, 8, 0};
+  while (((n2 + (1 << w.ls) - 1) >> w.ls) > 16) ++w.ls;   // n2 <= 1024: ls <= 6
+  w.lk -= w.ls;
+  while (w.lk > 0 && w.ls + w.lk > 6 && (1 << (w.lk - 1)) >= n3) --w.lk;
+  w.nchunk = (n3 + (1 << w.lk) - 1) >> w.lk;
+  return w;
+}
+size_t slice_generic_part_doubles(int n1, int n2, int n3) {
+  const size_t nchunk = wstep_shape(n2, n3).nchunk;
+  return nchunk > 1 ? 3 * nchunk * n1 : 0;
+}
+
 void launch_slice_generic(const Plan& p, int mode, float* w_out, float* z_out, int w_from_g) {
   const long n = (long)p.n1 * p.n2 * p.n3, slice = (long)p.n2 * p.n3;
   const bool need_z = !(mode == SLICE_RESULT && w_from_g && z_out == nullptr);
@@ -149,13 +167,8 @@ void launch_slice_generic(const Plan& p, int mode, float* w_out, float* z_out, i
     launch_tube_inv(p, SPEC_F32, p.zt, p.n2, (long)p.nb * p.n2, 1, p.zsp, z_out, slice, p.n3, p.n1, p.n2, 1.0 / p.n3);
   else
     launch_zero(p, p.zsp, (size_t)n * 4);
-  // segments of at most 16 columns and no more of them than that needs, so that the runs of rows
-  // are long; no more rows per block than there are, in whole wavefronts
-  int ls = 0, lk = 8;
-  while (((p.n2 + (1 << ls) - 1) >> ls) > 16) ++ls;   // n2 <= 1024: ls <= 6
-  lk -= ls;
-  while (lk > 0 && ls + lk > 6 && (1 << (lk - 1)) >= p.n3) --lk;
-  const int nchunk = (p.n3 + (1 << lk) - 1) >> lk, threads = 1 << (ls + lk), len = (p.n2 + (1 << ls) - 1) >> ls;
+  const WstepShape ws = wstep_shape(p.n2, p.n3);
+  const int ls = ws.ls, lk = ws.lk, nchunk = ws.nchunk, threads = 1 << (ls + lk), len = (p.n2 + (1 << ls) - 1) >> ls;
   double* rows = mode == SLICE_KKT ? p.kkt : p.slice_obj;
   GenWArgs a;
   a.z = p.zsp;
@@ -163,7 +176,7 @@ void launch_slice_generic(const Plan& p, int mode, float* w_out, float* z_out, i
   a.wtab = p.wtab;
   a.w = p.wsp;
   a.w_out = w_out;
-  a.part = nchunk > 1 ? (double*)p.csp : rows;   // csp holds 24 nchunk bytes per OD row wherever nchunk > 1
+  a.part = nchunk > 1 ? p.rowpart : rows;
   a.n2 = p.n2;
   a.n3 = p.n3;
   a.mu = p.mu;
