@@ -265,6 +265,8 @@ static void fill_plan(tctf_ctx* c, hipStream_t stream) {
   q.wsp = (float*)(w + L.wsp);
   q.rowpart = (double*)(w + L.rowpart);
   q.twg = L.split ? (double2*)(w + L.twg) : nullptr;
+  q.fft = tctf::fft64_plan(p.n3);
+  q.fft_half = tctf::fft64_plan(p.n3 % 2 == 0 ? p.n3 / 2 : 1);
   q.rsig = (double*)(w + L.rsig);
   q.rtx = (cd*)(w + L.rtx);
   q.rty = (cd*)(w + L.rty);

@@ -3,14 +3,9 @@
 // complex sequence (c = x_0 + i x_1), which serves odd lengths as well as even ones.
 #pragma once
 #include "common.h"
+#include "kernels.h"
 
 namespace tctf {
-
-#define FFT64_MAX_PASSES 14   // 2^13 as twos and fours, and any other length up to 8192
-struct Fft64Plan {
-  int n, passes;
-  int radix[FFT64_MAX_PASSES];
-};
 
 #define FFT64_PER 8   // complex values per thread: P N <= FFT64_PER blockDim.x
 
@@ -223,7 +218,5 @@ __device__ inline void fft64(cd* x, int P, const Fft64Plan& pl, const cd* tw, in
     Ns *= R;
   }
 }
-
-Fft64Plan fft64_plan(int n);
 
 }  // namespace tctf

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "common.h"
+#include "fft64_plan.h"
 
 namespace tctf {
 
@@ -53,6 +54,7 @@ struct Plan {
   float* wsp;       // [n1][n2][n3]
   double* rowpart;  // [n1][blocks per OD row][3]
   double2* twg;     // [n3] (cos, sin)(2 pi m / n3); NULL without that path
+  Fft64Plan fft, fft_half;   // of tubes of n3, and of n3 / 2 where n3 is even
   // step 5 (rank adjustment)
   double* rsig;     // [nb][r] singular values of Z~_b, descending
   cd* rtx;          // [nb][r][r] factor rotations of X~ and Y~

@@ -7,39 +7,6 @@
 
 namespace tctf {
 
-// The fewest passes over the radices of dft_small (of two such plans the one with the smaller
-// largest radix), prime factors past 7 as passes of their own.  Odd radices first: the first pass
-// writes its outputs R apart, which an even R would put into few LDS banks.
-static void fft64_factor(int n, int cap, int* cur, int depth, int* best, int* passes) {
-  if (depth >= *passes) return;
-  if (n == 1) {
-    *passes = depth;
-    for (int k = 0; k < depth; ++k) best[k] = cur[k];
-    return;
-  }
-  for (int r : {12, 10, 9, 8, 7, 6, 5, 4, 3, 2})
-    if (r <= cap && n % r == 0) {
-      cur[depth] = r;
-      fft64_factor(n / r, r, cur, depth + 1, best, passes);
-    }
-}
-Fft64Plan fft64_plan(int n) {
-  Fft64Plan pl;
-  pl.n = n;
-  pl.passes = 0;
-  for (int r = 11; r <= n; r += 2)
-    while (n % r == 0 && r % 3 && r % 5 && r % 7) {   // what is left of r's smaller factors is gone: r is prime
-      pl.radix[pl.passes++] = r;
-      n /= r;
-    }
-  int cur[FFT64_MAX_PASSES], best[FFT64_MAX_PASSES], passes = FFT64_MAX_PASSES;
-  fft64_factor(n, 12, cur, 0, best, &passes);
-  for (int odd = 1; odd >= 0; --odd)
-    for (int k = 0; k < passes; ++k)
-      if ((best[k] & 1) == odd) pl.radix[pl.passes++] = best[k];
-  return pl;
-}
-
 template <int KIND> struct SpecOf { typedef float2 type; };
 template <> struct SpecOf<SPEC_F64> { typedef double2 type; };
 
@@ -59,11 +26,11 @@ __device__ __forceinline__ void spec_store(void* out, size_t at, double re, doub
 // Block (x, y): up to 2 PP tubes (y, q), q = 2 PP x ..., as PP complex sequences in LDS, then the
 // roots of unity unless the caller's table holds them.  A sequence carries two tubes: on the
 // inverse C[k] = A[k] + i B[k] over the conjugate-symmetric extension of both spectra, on the
-// forward A = (C[k] + conj C[N - k]) / 2, B = (C[k] - conj C[N - k]) / (2 i).  What bounds it:
-// LDS traffic and the barriers of the passes (12 x 12 x 8064: 25.3 us for 72 blocks of one pair and
-// four passes, 29.6 with six of radices up to 8, 13.9 ms as direct sums; 288 x 28 x 144: 10.9 us
-// with two passes, 16.7 with four and twice the values per block, direct 115).  NT: at most 256
-// threads hold a butterfly of 12 in registers, 1024 would not at the others' expense.
+// forward A = (C[k] + conj C[N - k]) / 2, B = (C[k] - conj C[N - k]) / (2 i); either tube carries the
+// FP64 rounding of the larger.  What bounds it: LDS traffic and the barriers of the passes (288 x 28
+// x 144: 10.9 us with two passes, 16.7 with four and twice the values per block, direct sums 115;
+// 72 pairs of 8064, too few for pairs, 25.3 us with four passes, 29.6 with six of radices up to 8).
+// NT: at most 256 threads hold a butterfly of 12 in registers, 1024 would not at the others' expense.
 struct Tube64 {
   long bs, ps, qs;   // strides of the spectrum
   long sp, sq;       // strides of the spatial tubes
@@ -389,7 +356,7 @@ static void tube_inv(const Plan& p, const void* in, T* out, T* out2, Tube64 t, i
   }
   if (tube64_half(p, pairs)) {
     const int M = p.n3 / 2, threads = tube64_half_threads(M);
-    k_tube64_half_inv<KIND, T><<<dim3(t.Q, P), threads, M * sizeof(cd), p.stream>>>(in, out, out2, t, fft64_plan(p.n3 / 2));
+    k_tube64_half_inv<KIND, T><<<dim3(t.Q, P), threads, M * sizeof(cd), p.stream>>>(in, out, out2, t, p.fft_half);
     return;
   }
   int nt;
@@ -397,7 +364,7 @@ static void tube_inv(const Plan& p, const void* in, T* out, T* out2, Tube64 t, i
   const dim3 grid = tube64_shape(&t, p.n3, P, &nt, &lds);
   const auto k = nt <= 256 ? k_tube64_inv<KIND, T, 256> : k_tube64_inv<KIND, T, 1024>;
   if (lds > 65536) (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  k<<<grid, nt, lds, p.stream>>>(in, out, out2, t, fft64_plan(p.n3));
+  k<<<grid, nt, lds, p.stream>>>(in, out, out2, t, p.fft);
 }
 template <int KIND, typename T>
 static bool tube_fwd(const Plan& p, const T* in, void* out, Tube64 t, int P) {
@@ -410,7 +377,7 @@ static bool tube_fwd(const Plan& p, const T* in, void* out, Tube64 t, int P) {
   }
   if (tube64_half(p, pairs)) {
     const int M = p.n3 / 2, threads = tube64_half_threads(M);
-    k_tube64_half_fwd<KIND, T><<<dim3(t.Q, P), threads, M * sizeof(cd), p.stream>>>(in, out, t, fft64_plan(p.n3 / 2), p.ctr);
+    k_tube64_half_fwd<KIND, T><<<dim3(t.Q, P), threads, M * sizeof(cd), p.stream>>>(in, out, t, p.fft_half, p.ctr);
     return true;
   }
   int nt;
@@ -418,7 +385,7 @@ static bool tube_fwd(const Plan& p, const T* in, void* out, Tube64 t, int P) {
   const dim3 grid = tube64_shape(&t, p.n3, P, &nt, &lds);
   const auto k = nt <= 256 ? k_tube64_fwd<KIND, T, 256> : k_tube64_fwd<KIND, T, 1024>;
   if (lds > 65536) (void)hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  k<<<grid, nt, lds, p.stream>>>(in, out, t, fft64_plan(p.n3), p.ctr);
+  k<<<grid, nt, lds, p.stream>>>(in, out, t, p.fft, p.ctr);
   return true;
 }
 
