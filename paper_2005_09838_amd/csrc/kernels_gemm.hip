@@ -1024,16 +1024,16 @@ static BgemmKernel bgemm_kernel_of(int bcg, int mixed, int waves) {
 }
 
 // Row groups of G_X in a launch of their own, 0: all rows in the block that inverts it.  Up to r = 16
-// and a few thousand rows that block's sums are no longer than the product's beside it, but at r >
-// 16, before an inverse by the eigen route, or for more rows and few frequencies they are the launch's
-// chain (and members of a batch whose chains meet on a compute unit share its matrix cores): groups of
-// at least 96 rows, four or more, and no more blocks than compute units.  One iteration in us, one
+// that block's sums are no longer than the product's beside it, but at r > 16, or for thousands of
+// rows with few frequencies or an inverse by the eigen route after them, they are the launch's chain
+// (and members of a batch whose chains meet on a compute unit share its matrix cores): groups of at
+// least 96 rows, four or more, and no more blocks than compute units.  One iteration in us, one
 // block / groups: 8192 x 32 x 3, r = 32 533 / 388; 1500 x 24 x 112, r = 17 206 / 190; 384 x 24 x 5, r =
 // 24 83.4 / 78.7; 600 x 24 x 200, r = 24 (two groups) 198 / 207; 8192 x 16 x 7, r = 16 170 / 165; 2000 x
 // 12 x 28, r = 12 76.3 / 76.2; 4000 x 24 x 112, r = 16 199 / 220, by the eigen route 507 / 467; 1000 x 16
 // x 12, r = 16, eigen 402 / 401; three of 6591 x 7 x 2, r = 4, together 250 / 190.
 static int gramx_groups(const Plan& p) {
-  if (p.r <= 16 && !(p.force_eigen ? p.n1 >= 1000 : p.n1 >= 2000 && p.nb <= 16)) return 0;
+  if (p.r <= 16 && !(p.n1 >= 2000 && (p.force_eigen || p.nb <= 16))) return 0;
   int g = p.n1 / 96;
   if (g > 256 / p.nb) g = 256 / p.nb;
   // the partials lie in Z~'s buffer: 32 r^2 bytes each in 8 n1 n2 per frequency

@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
     (384, 24, 5, 17, 0),     # four groups of 96 rows
     (389, 33, 3, 32, 0),     # a short last group, the largest rank
     (1001, 20, 7, 18, 1),    # ten groups before the eigen route
-    (999, 12, 4, 9, 1),      # one block up to r = 16 ...
-    (1000, 12, 4, 9, 1),     # ... and groups from 1000 rows on by the eigen route
+    (1999, 12, 34, 9, 1),    # 18 frequencies, up to r = 16: one block ...
+    (2000, 12, 34, 9, 1),    # ... and groups from 2000 rows on by the eigen route
     (600, 20, 126, 20, 0),   # 64 frequencies: four groups each
     (600, 20, 128, 20, 0),   # 65: one block each
     (1999, 6, 5, 4, 0),      # up to r = 16 one block ...
