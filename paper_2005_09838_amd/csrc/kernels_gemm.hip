@@ -43,7 +43,7 @@ __device__ __forceinline__ v4d mfma4d(double a, double b, v4d c) {
 // 12.0 / 11.4 / 11.6; 36 x 48 x 7, r 3 4.2 / 4.1 / 3.1.
 // PINV: the first npinv blocks instead form G_Y^+ and I - eta P_Y of frequency blockIdx.x for
 // the next X-step (pinvy_block): independent work that runs beside the product (an instance of
-// its own, since its registers would halve the product's wavefronts).
+// its own, since the inverse takes more registers than a product of r <= 16).
 #define ZG_ROWS 64
 #define ZG_COLS 32
 template <int RM, bool PINV>   // r <= RM: every loop below has a compile-time trip count
@@ -256,14 +256,11 @@ static void zgemm(const Plan& p, int npinv) {
   k<<<grid, 256, lds, p.stream>>>(p.xt, p.yt, p.zt, p.n1, p.n2, p.r, p.nb, npinv, pinvy_args(p));
 }
 
-// with_pinv: G_Y^+ too, in the product's launch while its blocks are two per compute unit or
-// fewer, in a launch before it beyond: there the product's blocks wait behind rounds of inverses
-// and run at their occupancy.  One iteration in us, together / apart: 288 x 28 x 144 78.1 / 82.0,
-// 12 x 12 x 1008 56.4 / 57.4, 12 x 12 x 2016 74.6 / 70.1, 12 x 12 x 8064 201.5 / 171.4.
+// with_pinv: G_Y^+ too, in blocks ahead of the product's.  One iteration in us, in this launch / in one
+// before it: 288 x 28 x 144 66.1 / 69.9, 12 x 12 x 2016 63.0 / 66.1, 40 x 40 x 1100, r = 30 340 / 353,
+// 12 x 12 x 8064 134.6 / 135.7.
 void launch_zgemm(const Plan& p, int with_pinv) {
-  const bool apart = with_pinv && p.nb > 512;
-  if (apart) launch_pinvy(p, p.stream);
-  const int npinv = with_pinv && !apart ? p.nb : 0;
+  const int npinv = with_pinv ? p.nb : 0;
   if (p.r <= 8) zgemm<8>(p, npinv);
   else if (p.r <= 16) zgemm<16>(p, npinv);
   else zgemm<32>(p, npinv);

@@ -131,8 +131,8 @@ __global__ void __launch_bounds__(NT) k_tube64_fwd(const T* __restrict__ in, voi
 
 // ---- one even tube per block through the complex sequence c[m] = x[2 m] + i x[2 m + 1] of half its
 // length M: long tubes that are too few to fill the device as pairs.  512 threads of up to eight
-// values, which leaves each the registers of its widest butterfly.  12 x 12 x 8064: 19.7 us inverse
-// and 23.8 forward for 144 blocks, 25.3 and 24.7 for 72 of pairs.
+// values, which leaves each the registers of its widest butterfly.  12 x 12 x 8064: 19.1 us inverse
+// and 23.4 forward for 144 blocks, 25.3 and 24.7 for 72 of pairs.
 template <int KIND, typename T>
 __global__ void __launch_bounds__(512) k_tube64_half_inv(const void* __restrict__ in, T* __restrict__ out,
                                                           T* __restrict__ out2, Tube64 t, Fft64Plan pl) {
@@ -244,8 +244,8 @@ __global__ void __launch_bounds__(256) k_tube_direct_fwd(const T* __restrict__ i
 // ---- host side
 // Whether tubes go through sequences of half their length, a block each: long even ones (with the
 // table of roots) of which a compute unit holds one.  Both transforms and the W-step in us, pairs /
-// halves: 12 x 12 x 8064 58.3 / 50.2, 10 x 10 x 4032 36.8 / 30.7, 12 x 12 x 2688 31.5 / 28.2,
-// 12 x 12 x 2048 26.9 / 25.8; 22 x 22 x 2048 (242 pairs) 35.2 / 39.2.
+// halves: 12 x 12 x 8064 57.5 / 47.5, 10 x 10 x 4032 34.4 / 29.1, 12 x 12 x 2688 30.4 / 26.6,
+// 12 x 12 x 2048 25.9 / 25.0, 16 x 16 x 2048 29.6 / 28.2; 22 x 22 x 2048 (242 pairs) 34.5 / 36.4.
 static bool tube64_half(const Plan& p, long pairs) { return p.n3 % 2 == 0 && p.n3 >= 2048 && pairs <= 128; }
 
 // Threads of a block on a sequence of half the length, of M values.
